@@ -109,6 +109,15 @@ struct ProfScope {
     HIP_TRY(hipGetLastError());                                                    \
   } while (0)
 
+// the emission kernel of the call (translation-symmetric or plain)
+#define EMIT(name, scatter, nbl)                                                   \
+  do {                                                                             \
+    if (c.ts)                                                                      \
+      LAUNCH(name, (k_emit<W, F32, scatter, nbl, true>), rows, EMIT_THREADS, ea);  \
+    else                                                                           \
+      LAUNCH(name, (k_emit<W, F32, scatter, nbl, false>), rows, EMIT_THREADS, ea); \
+  } while (0)
+
 #define TRY(expr)                    \
   do {                               \
     int rc_ = (expr);                \
@@ -250,6 +259,10 @@ int alpha_kind(double2 a) {
 // workgroups fit a CU as there are CUs) and 128 rows of operator terms
 constexpr int64_t COMM_ROWS_MAX = 1024, TERM_ROWS_MAX = (1 << 17) / EMIT_THREADS;
 static_assert(COMM_ROWS_MAX + TERM_ROWS_MAX <= SC_ROWS_MAX, "k_scan_cols covers every count row");
+// Above this many tiles the strings of a tile are sorted by support and H is
+// pruned to each wave's window (2 to 3 times fewer pairs tested); below, the
+// pair tests take about a microsecond and the sort's loads and barriers more.
+constexpr int EMIT_WINDOW_TILES = 32;
 constexpr int MAX_PASS_BITS = 12;
 constexpr int DIRECT_MAX_F = 22;  // at most 2^22 buckets in a direct merge
 constexpr int PART_NBL = 12;  // at most 2^12 partitions (MAX_PASS_BITS)
@@ -258,8 +271,21 @@ constexpr int PART_NBL = 12;  // at most 2^12 partitions (MAX_PASS_BITS)
 constexpr int SPLIT_ROWS = 1024;
 static_assert(SPLIT_ROWS <= SC_ROWS_MAX, "k_scan_cols covers every split row");
 
-inline void plan_rows(bool comm, int64_t nO, int64_t nterm_rec, int* comm_rows, int* term_rows) {
-  *comm_rows = comm ? (int)std::min<int64_t>((nO + EMIT_THREADS - 1) / EMIT_THREADS, COMM_ROWS_MAX) : 0;
+// An operator of few tiles would leave most CUs idle: its tiles are shared out
+// over H (*hseg workgroups each, at least HSEG_MIN entries of H per share), up
+// to HSEG_ROWS rows, which the count matrix holds room for in any case.  Ten
+// noisy steps at 2^14 strings (16 tiles, |H| = 180) spent 102 + 61 us per
+// commutator in the scatter and the count on 16 of 256 CUs: 16.5 -> 11.7 ms;
+// a commutator of 77,777 two-word strings 304 -> 229 us (2^12 bins below 2^22
+// possible records are part of both).
+constexpr int64_t HSEG_ROWS = 256, HSEG_MIN = 8;
+inline void plan_rows(bool comm, int64_t nH, int64_t nO, int64_t nterm_rec, int* comm_rows,
+                      int* term_rows, int* hseg) {
+  const int64_t tiles = comm ? std::min<int64_t>((nO + EMIT_THREADS - 1) / EMIT_THREADS, COMM_ROWS_MAX) : 0;
+  *hseg = 1;
+  if (comm)
+    *hseg = (int)std::max<int64_t>(1, std::min<int64_t>(HSEG_ROWS / tiles, nH / HSEG_MIN));
+  *comm_rows = (int)tiles * *hseg;
   *term_rows = nterm_rec > 0
                    ? (int)std::min<int64_t>((nterm_rec + EMIT_THREADS - 1) / EMIT_THREADS, TERM_ROWS_MAX)
                    : 0;
@@ -446,8 +472,8 @@ int Engine::run(Call& c) {
     g_last_error = "H has more strings than one merge bucket holds";
     return PAULI_EINVAL;
   }
-  int comm_rows = 0, term_rows = 0;
-  plan_rows(comm, c.O.n, nterm_rec, &comm_rows, &term_rows);
+  int comm_rows = 0, term_rows = 0, hseg = 1;
+  plan_rows(comm, c.H.n, c.O.n, nterm_rec, &comm_rows, &term_rows, &hseg);
   const int rows = comm_rows + term_rows;
 
   Bufs1<W> b1;
@@ -605,6 +631,8 @@ int Engine::run(Call& c) {
     ea.product = c.product ? 1 : 0;
     ea.ts_n = c.ts;
     ea.comm_rows = comm_rows;
+    ea.hseg = hseg;
+    ea.windows = !c.product && (int64_t)comm_rows / hseg > EMIT_WINDOW_TILES ? 1 : 0;
     ea.comm_group = (uint32_t)c.comm_group;
     if (comm) {
       ea.Ox = c.O.x;
@@ -632,12 +660,15 @@ int Engine::run(Call& c) {
     // 2^nbl hash bins per pass: NBINS_LOG while the call fits one pass,
     // NBINS_LOG_MP (twice the records per pass) when it needs several, and
     // NBINS_LOG_SMALL for calls of at most 2^18 records even if every pair
-    // emits one (the per-call bin tables then cost a sixteenth)
+    // emits one, NBINS_LOG_MID for at most 2^22 (the per-call bin tables then
+    // cost a sixteenth and a quarter)
     int nbl = NBINS_LOG;
     const unsigned long long rec_bound =
         (comm ? (unsigned long long)c.H.n * (unsigned long long)c.O.n : 0ull) +
         (unsigned long long)nterm_rec;
     if (rec_bound <= (1ull << (NBINS_LOG_SMALL + 8))) nbl = NBINS_LOG_SMALL;
+    else if (rec_bound <= (1ull << (NBINS_LOG_MID + 10)) && (!comm || c.H.n < (1 << (NBINS_LOG_MID - 3))))
+      nbl = NBINS_LOG_MID;
     auto count_pass = [&](int pass_bits, uint32_t pass_id, bool read = true,
                           unsigned long long spec_cap = 0ull) -> int {
       ea.pass_bits = pass_bits;
@@ -647,7 +678,7 @@ int Engine::run(Call& c) {
       const uint32_t nzero = pass_id == 0 ? (uint32_t)(HREP * SEL0_BINS) : 0u;
       if (nbl == NBINS_LOG_SMALL) {
         constexpr int NBS = 1 << NBINS_LOG_SMALL;
-        LAUNCH("k_emit_count", (k_emit<W, F32, false, NBINS_LOG_SMALL>), rows, EMIT_THREADS, ea);
+        EMIT("k_emit_count", false, NBINS_LOG_SMALL);
         if (rows <= SMALL_SCAN_ROWS) {
           LAUNCH("k_scan_small", k_scan_small, HREP, 1024, counts, rows, bin_base, dctl, zero,
                  nzero);
@@ -657,13 +688,19 @@ int Engine::run(Call& c) {
           LAUNCH("k_scan_bins", k_scan_bins<NBINS_LOG_SMALL>, 1, 1024, bin_total, bin_base, dctl,
                  zero, nzero);
         }
+      } else if (nbl == NBINS_LOG_MID) {
+        constexpr int NBM = 1 << NBINS_LOG_MID;
+        EMIT("k_emit_count", false, NBINS_LOG_MID);
+        LAUNCH("k_scan_cols", k_scan_cols, NBM / SC_COLS, SC_COLS * SC_NSEG, counts, rows, bin_total, dctl, NBM);
+        LAUNCH("k_scan_bins", k_scan_bins<NBINS_LOG_MID>, 1, 1024, bin_total, bin_base, dctl, zero,
+               nzero, spec_cap, (unsigned int)merge_cap<W>());
       } else if (nbl == NBINS_LOG) {
-        LAUNCH("k_emit_count", (k_emit<W, F32, false, NBINS_LOG>), rows, EMIT_THREADS, ea);
+        EMIT("k_emit_count", false, NBINS_LOG);
         LAUNCH("k_scan_cols", k_scan_cols, NBINS / SC_COLS, SC_COLS * SC_NSEG, counts, rows, bin_total, dctl, NBINS);
         LAUNCH("k_scan_bins", k_scan_bins<NBINS_LOG>, 1, 1024, bin_total, bin_base, dctl, zero,
                nzero, spec_cap, (unsigned int)merge_cap<W>());
       } else {
-        LAUNCH("k_emit_count", (k_emit<W, F32, false, NBINS_LOG_MP>), rows, EMIT_THREADS, ea);
+        EMIT("k_emit_count", false, NBINS_LOG_MP);
         LAUNCH("k_scan_cols", k_scan_cols, NBINS_MP / SC_COLS, SC_COLS * SC_NSEG, counts, rows, bin_total, dctl,
                NBINS_MP);
         LAUNCH("k_scan_bins", k_scan_bins<NBINS_LOG_MP>, 1, 1024, bin_total, bin_base, dctl, zero,
@@ -674,9 +711,9 @@ int Engine::run(Call& c) {
     // source ids fold into the key bits implied by the bin unless an index
     // needs more than 11 bits (H above 2047 strings, canonicalisation lists)
     // (translation-symmetric calls carry (H entry, rotation) as the source id)
-    // (7 bits over 2^10 bins)
+    // (7 bits over 2^10 bins, 9 over 2^12)
     auto wide_for = [&](int bins_log) {
-      const int64_t max_h = bins_log == NBINS_LOG_SMALL ? (1 << (NBINS_LOG_SMALL - 3)) - 1 : 2047;
+      const int64_t max_h = (1 << (std::min(bins_log, NBINS_LOG) - 3)) - 1;
       bool w = comm && (c.H.n > max_h || c.ts);
       for (int t = 0; t < c.n_terms; t++) w = w || c.tlist[t];
       return w;
@@ -702,9 +739,9 @@ int Engine::run(Call& c) {
       } else {
         planned = true;
       }
-    } else if (nbl == NBINS_LOG && ctl_event &&
+    } else if (nbl != NBINS_LOG_SMALL && ctl_event &&
                rec_bound <= 7ull * (1ull << NBINS_LOG) * (unsigned long long)merge_cap<W>()) {
-      // A call that may fit one pass over 2^14 bins (at most seven passes'
+      // A call that may fit one pass over 2^12 or 2^14 bins (at most seven passes'
       // worth of possible records) is laid out for as many records as the
       // workspace holds beside the rest of that pass; the count's control
       // block goes to the host behind an event and the scatter is launched
@@ -712,8 +749,8 @@ int Engine::run(Call& c) {
       // makes the scatter stand down when the records do not fit the layout
       // or a bin exceeds the merge capacity; the host then plans from the
       // count it has read, as below.
-      const bool w14 = wide_for(NBINS_LOG);
-      const uint32_t mb = (1u << NBINS_LOG) << 2;
+      const bool w14 = wide_for(nbl);
+      const uint32_t mb = (1u << nbl) << 2;
       const size_t per = RB + KB + sizeof(double2) + (w14 ? 4 : 0) + (want_select ? 12 : 0) +
                          (c.out.to_arena ? (size_t)(16 * W + 16) : 0);
       const size_t fixed = (size_t)mb * (9 * 4 + sizeof(double2) + (want_select ? 12 : 0)) +
@@ -741,7 +778,10 @@ int Engine::run(Call& c) {
         ea.rsrc_wide = b2.rsrc_wide;
         ea.wide = w14 ? 1 : 0;
         ea.skip = &dctl->spec_fail;
-        LAUNCH("k_emit_scatter", (k_emit<W, F32, true, NBINS_LOG>), rows, EMIT_THREADS, ea);
+        if (nbl == NBINS_LOG_MID)
+          EMIT("k_emit_scatter", true, NBINS_LOG_MID);
+        else
+          EMIT("k_emit_scatter", true, NBINS_LOG);
         ea.skip = nullptr;
         g_stats.host_syncs++;
         HIP_TRY(hipEventSynchronize(ctl_event));
@@ -755,7 +795,7 @@ int Engine::run(Call& c) {
     } else {
       TRY(count_pass(0, 0));
     }
-    if (!planned && nbl == NBINS_LOG_SMALL && hctl->maxg[0] > (unsigned int)merge_cap<W>()) {
+    if (!planned && nbl < NBINS_LOG && hctl->maxg[0] > (unsigned int)merge_cap<W>()) {
       // a small call whose records crowd one bin: count again over 2^14 bins
       nbl = NBINS_LOG;
       TRY(count_pass(0, 0));
@@ -771,7 +811,7 @@ int Engine::run(Call& c) {
     // of one string share a bin), so a pass that still overflows restarts the
     // loop with one more pass bit
     // the count pass measured every bin exactly
-    int pass_bits = nbl == NBINS_LOG_SMALL ? 0 : plan_pass_bits<W>(hctl->maxg[0], &nbl);
+    int pass_bits = nbl < NBINS_LOG ? 0 : plan_pass_bits<W>(hctl->maxg[0], &nbl);
     // Several passes bin each partition over 2^14 instead of 2^15 bins when
     // the 2^14 bins are expected to stay within 0.8 of the merge's capacity
     // (the merge then takes single bins where it would take pairs of 2^15
@@ -851,13 +891,13 @@ int Engine::run(Call& c) {
                  1 << PART_NBL, pcounts, bin_total);
           ea.counts = pcounts;
         } else {
-          LAUNCH("k_emit_part_count", (k_emit<W, F32, false, PART_NBL>), rows, EMIT_THREADS, ea);
+          EMIT("k_emit_part_count", false, PART_NBL);
           LAUNCH("k_scan_cols", k_scan_cols, (1 << PART_NBL) / SC_COLS, SC_COLS * SC_NSEG, counts, rows, bin_total, dctl,
                  1 << PART_NBL);
         }
         LAUNCH("k_scan_part", k_scan_part, 1, 1024, bin_total, npass, pbase, (1 << PART_NBL) + 1,
                dctl);
-        LAUNCH("k_emit_part_scatter", (k_emit<W, F32, true, PART_NBL>), rows, EMIT_THREADS, ea);
+        EMIT("k_emit_part_scatter", true, PART_NBL);
         ea.counts = counts;
         first_counts = false;  // bin_total now holds partition, then split, totals
         ea.part = 0;
@@ -910,7 +950,7 @@ int Engine::run(Call& c) {
           while (g_log > 0 &&
                  (double)pe_all > std::ldexp(0.85 * SCAP, NBINS_LOG_SMALL - g_log))
             g_log--;
-          LAUNCH("k_emit_scatter", (k_emit<W, F32, true, NBINS_LOG_SMALL>), rows, EMIT_THREADS, ea);
+          EMIT("k_emit_scatter", true, NBINS_LOG_SMALL);
           ma.g_log = g_log;
           ma.nbins_log = nbl;
           ma.digit_shift = nbl - g_log;
@@ -960,11 +1000,13 @@ int Engine::run(Call& c) {
         else if (scattered)
           ;  // launched before the count was read
         else if (nbl == NBINS_LOG_SMALL)
-          LAUNCH("k_emit_scatter", (k_emit<W, F32, true, NBINS_LOG_SMALL>), rows, EMIT_THREADS, ea);
+          EMIT("k_emit_scatter", true, NBINS_LOG_SMALL);
+        else if (nbl == NBINS_LOG_MID)
+          EMIT("k_emit_scatter", true, NBINS_LOG_MID);
         else if (nbl == NBINS_LOG)
-          LAUNCH("k_emit_scatter", (k_emit<W, F32, true, NBINS_LOG>), rows, EMIT_THREADS, ea);
+          EMIT("k_emit_scatter", true, NBINS_LOG);
         else
-          LAUNCH("k_emit_scatter", (k_emit<W, F32, true, NBINS_LOG_MP>), rows, EMIT_THREADS, ea);
+          EMIT("k_emit_scatter", true, NBINS_LOG_MP);
         ma.g_log = g_log;
         ma.nbins_log = pnbl;
         ma.digit_shift = pass_bits + pnbl - g_log;
@@ -1398,8 +1440,8 @@ void dry_call(Arena& ar, const DryCall& d, unsigned long long* pe_out) {
     ar.take((size_t)nH * sizeof(double2));
   }
   const bool comm = d.comm && nH > 0 && d.nO > 0;
-  int comm_rows = 0, term_rows = 0;
-  plan_rows(comm, d.nO, d.nterm, &comm_rows, &term_rows);
+  int comm_rows = 0, term_rows = 0, hseg = 1;
+  plan_rows(comm, nH, d.nO, d.nterm, &comm_rows, &term_rows, &hseg);
   Bufs1<W> b1;
   take_bufs1<W>(ar, comm, nH, d.n_keep, comm_rows + term_rows, b1);
   const unsigned long long pe =

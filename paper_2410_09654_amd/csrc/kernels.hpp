@@ -76,7 +76,9 @@ struct EmitArgs {
   int product;  // plain product A B (every pair, i^e h_a c_b) instead of [A, B]
   int ts_n;     // > 0: translation-symmetric operators on ts_n periodic sites; every
                 // emitted string is replaced by its orbit representative
-  int comm_rows;
+  int comm_rows;  // tile_rows x hseg
+  int hseg;       // workgroups that share a tile, each every hseg-th entry of H
+  int windows;    // tiles sorted by lowest site, H pruned to each wave's window
   uint32_t comm_group;
   const uint64_t* Ox;
   const uint64_t* Oz;
@@ -164,7 +166,9 @@ __device__ __forceinline__ uint32_t layout_row(uint32_t b, uint32_t n) {
   return b < n8 ? (b & 7u) * (n8 >> 3) + (b >> 3) : b;
 }
 
-template <int W, bool F32, bool SCATTER, int NBL>
+// TS: translation-symmetric operators (a.ts_n > 0), a kernel of its own because the search for
+// the representative takes registers that the plain pair loop needs.
+template <int W, bool F32, bool SCATTER, int NBL, bool TS>
 // Eight waves per SIMD (two workgroups per CU) where registers and LDS allow;
 // two-word strings need more than 64 registers per lane in the pair loop and
 // 2^15 bins fill the LDS of a CU, so those aim at four.
@@ -225,25 +229,28 @@ __attribute__((amdgpu_waves_per_eu(W == 1 && NBL <= 14 ? 8 : 4))) void k_emit(Em
     // site, so a wave holds strings of nearby support and loops only over the
     // H strings whose sites can overlap its window [wlo, whi].  A pair whose
     // supports do not overlap commutes, so skipping it changes nothing.
+    // Operators of few tiles are shared out over H too (hseg workgroups per
+    // tile, each every hseg-th entry): see plan_rows
     constexpr int SITES = 64 * W;
+    constexpr int HB = TS ? 1 : 4;  // entries of H per step (the representative search leaves no registers)
     __shared__ uint32_t scnt[SITES + 2];
     __shared__ uint16_t sperm[EMIT_THREADS];
     const V* Oc = reinterpret_cast<const V*>(a.Oc);
     const int64_t ntiles = (a.nO + EMIT_THREADS - 1) / EMIT_THREADS;
-    for (int64_t tile = row; tile < ntiles; tile += a.comm_rows) {
+    const int tile_rows = a.comm_rows / a.hseg, seg = row % a.hseg;
+    for (int64_t tile = row / a.hseg; tile < ntiles; tile += tile_rows) {
+      int64_t i = tile * EMIT_THREADS + tid;
+      if (a.windows) {
       // lowest and highest site of this thread's string (empty or padding
       // strings sort last, with site SITES)
       int lo = SITES, hi = -1;
-      {
-        const int64_t i0 = tile * EMIT_THREADS + tid;
-        if (i0 < a.nO) {
+      if (i < a.nO) {
 #pragma unroll
-          for (int w = W - 1; w >= 0; w--) {
-            const uint64_t s = a.Ox[(size_t)w * a.Ocap + i0] | a.Oz[(size_t)w * a.Ocap + i0];
-            if (s) {
-              lo = 64 * w + __builtin_ctzll(s);
-              if (hi < 0) hi = 64 * w + 63 - __builtin_clzll(s);
-            }
+        for (int w = W - 1; w >= 0; w--) {
+          const uint64_t s = a.Ox[(size_t)w * a.Ocap + i] | a.Oz[(size_t)w * a.Ocap + i];
+          if (s) {
+            lo = 64 * w + __builtin_ctzll(s);
+            if (hi < 0) hi = 64 * w + 63 - __builtin_clzll(s);
           }
         }
       }
@@ -277,8 +284,9 @@ __attribute__((amdgpu_waves_per_eu(W == 1 && NBL <= 14 ? 8 : 4))) void k_emit(Em
       __syncthreads();
       sperm[scnt[lo] + rk] = (uint16_t)tid;
       __syncthreads();
-      const int64_t i = tile * EMIT_THREADS + sperm[tid];
+      i = tile * EMIT_THREADS + sperm[tid];
       __syncthreads();  // scnt / sperm are rewritten by the next tile
+      }
       const bool valid = i < a.nO;
       uint64_t xb[W], zb[W];
       V cb;
@@ -289,6 +297,8 @@ __attribute__((amdgpu_waves_per_eu(W == 1 && NBL <= 14 ? 8 : 4))) void k_emit(Em
       }
       if (valid) cb = Oc[i];
       else { cb.x = 0; cb.y = 0; }
+      int hfirst = 0, hend = a.nH;
+      if (a.windows) {
       // the wave's site window
       int slo = SITES, shi = -1;
 #pragma unroll
@@ -305,11 +315,13 @@ __attribute__((amdgpu_waves_per_eu(W == 1 && NBL <= 14 ? 8 : 4))) void k_emit(Em
         wlo = min(wlo, __shfl_xor(wlo, d, 64));
         whi = max(whi, __shfl_xor(whi, d, 64));
       }
-      // the product keeps every pair (identity strings included); the
-      // commutator only pairs that can overlap
-      if (whi < 0 && !a.product) continue;  // nothing but empty strings: all commute
-      const int hfirst = a.product ? 0 : (int)a.hstart[max(wlo - *a.hspan, 0)];
-      const int hend = a.product ? a.nH : (int)a.hstart[whi + 1];
+      if (whi < 0) continue;  // nothing but empty strings: all commute
+      hfirst = (int)a.hstart[max(wlo - *a.hspan, 0)];
+      hend = (int)a.hstart[whi + 1];
+      }
+      // this workgroup's entries: positions congruent to seg modulo hseg (which
+      // strings share a wave, and so its window, differs between workgroups)
+      hfirst += (seg + a.hseg - hfirst % a.hseg) % a.hseg;
 
       // Handle one queued (lane, H position) pair per lane.
       auto process = [&](uint32_t entry, bool active) {
@@ -344,7 +356,8 @@ __attribute__((amdgpu_waves_per_eu(W == 1 && NBL <= 14 ? 8 : 4))) void k_emit(Em
         const int e = (pa + pb + 2 * pz - pc) & 3;
         // translation symmetry: several O strings can meet the same H entry
         // in one orbit; (H entry, rotation) orders their contributions
-        const int rot = a.ts_n ? ts_representative<W>(c.w, a.ts_n) : 0;
+        int rot = 0;
+        if constexpr (TS) rot = ts_representative<W>(c.w, a.ts_n);
         const uint32_t horig = a.Hidx[h];
         const double2 hd = a.Hc[horig];
         // FP32 records: the product of the FP64 H coefficient and the stored
@@ -357,16 +370,27 @@ __attribute__((amdgpu_waves_per_eu(W == 1 && NBL <= 14 ? 8 : 4))) void k_emit(Em
           prod = cmul(hd, bc);
         }
         deposit(c, a.product ? times_ie(prod, e) : times_2ie(prod, e), a.comm_group,
-                a.ts_n ? horig * 256u + (uint32_t)rot : horig);
+                TS ? horig * 256u + (uint32_t)rot : horig);
       };
 
+      // the range is the same for the whole wave: scalar loop counter and loads
+      hfirst = __builtin_amdgcn_readfirstlane(hfirst);
+      hend = __builtin_amdgcn_readfirstlane(hend);
       uint32_t qn = 0;  // wave-uniform queue fill
-      for (int h = hfirst; h < hend; ++h) {
-        const uint64_t* hk = a.Hk + (size_t)h * (2 * W);
-        uint32_t par = 0;
+      for (int h0 = hfirst; h0 < hend; h0 += HB * a.hseg) {
+       // parities of HB entries, whose loads are issued together
+       uint32_t par[HB];
 #pragma unroll
-        for (int w = 0; w < W; w++) par += __popcll((hk[w] & zb[w]) ^ (hk[W + w] & xb[w]));
-        const bool emit = valid && (a.product || (par & 1u));
+       for (int u = 0; u < HB; u++) {
+        const uint64_t* hk = a.Hk + (size_t)min(h0 + u * a.hseg, hend - 1) * (2 * W);
+        par[u] = 0;
+#pragma unroll
+        for (int w = 0; w < W; w++) par[u] += __popcll((hk[w] & zb[w]) ^ (hk[W + w] & xb[w]));
+       }
+#pragma unroll
+       for (int u = 0; u < HB; u++) {
+        const int h = h0 + u * a.hseg;
+        const bool emit = valid && h < hend && (a.product || (par[u] & 1u));
         const uint64_t m = __ballot(emit);
         if (m) {
           const uint32_t pos = qn + mbcnt64(m);
@@ -383,6 +407,7 @@ __attribute__((amdgpu_waves_per_eu(W == 1 && NBL <= 14 ? 8 : 4))) void k_emit(Em
             qn = rem;
           }
         }
+       }
       }
       if (qn) {
         wave_sync();
@@ -406,7 +431,7 @@ __attribute__((amdgpu_waves_per_eu(W == 1 && NBL <= 14 ? 8 : 4))) void k_emit(Em
           raw.w[w] = a.tx[t][(size_t)w * a.tcap[t] + k];
           raw.w[W + w] = a.tz[t][(size_t)w * a.tcap[t] + k];
         }
-        if (a.ts_n) (void)ts_representative<W>(raw.w, a.ts_n);
+        if constexpr (TS) (void)ts_representative<W>(raw.w, a.ts_n);
         V val;
         if (a.tf32[t]) {
           const float2 f = reinterpret_cast<const float2*>(a.tc[t])[k];

@@ -1,0 +1,58 @@
+"""GPU parity of small and middle-sized calls at the edges of their planning rules, bit for bit
+against the CPU oracle: both sum each string's contributions in ascending H index, so equal
+inputs give equal bits (tolerance 0)."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from helpers import assert_canonical_unique, gpu_available
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
+
+
+@pytest.fixture(scope="module")
+def pk():
+    import paper_2410_09654_amd as pk
+    pk._lib.load()
+    return pk
+
+
+def raw(pk, h, dtype=0):
+    return pk.PauliOp.from_raw(h.n_qubits, h.x, h.z, h.coef, dtype=dtype)
+
+
+def same(got, want, what):
+    assert_canonical_unique(got)
+    g, w = got.as_dict(), want.as_dict()
+    assert set(g) == set(w), f"{what}: {len(set(w) - set(g))} missing, {len(set(g) - set(w))} extra"
+    off = [k for k in w if g[k] != w[k]]
+    assert not off, f"{what}: {len(off)} coefficients differ"
+
+
+# tiles of 1024 strings shared out over H (up to 256 workgroups, at least 8 entries of H each),
+# pruned to site windows above 32 tiles; 2^10, 2^12 and 2^14 bins (bounds of 2^18 and 2^22
+# pairs), H indices kept aside above 127 and 511
+@pytest.mark.parametrize("n,nh,no", [(12, 7, 1), (12, 16, 1), (30, 8, 1023), (64, 15, 1025),
+                                     (40, 127, 2064), (40, 128, 2049), (64, 17, 32 * 1024),
+                                     (64, 33, 32 * 1024 + 5), (100, 64, 3001), (70, 511, 600),
+                                     (70, 512, 600), (64, 40, 104858), (64, 41, 104858)])
+def test_tiles_shared_over_h(pk, n, nh, no):
+    print(f"commutator n={n} nh={nh} no={no}", flush=True)
+    H = wl.random_local_strings(n, nh, 3 if nh < 100 else 5, seed=nh)
+    O = wl.random_local_strings(n, no, 12, seed=no)
+    ws = pk.Workspace(256 << 20)
+    tr = dict(max_len=14, max_strings=20000)
+    got = pk.commutator(raw(pk, H), raw(pk, O), pk.Trunc(**tr), ws=ws).to_host()
+    want = oracle.truncate(oracle.commutator(H, O), oracle.Trunc(**tr))
+    same(got, want, "commutator")
+
+
+@pytest.mark.parametrize("n,nh,no", [(12, 9, 1), (30, 17, 1025), (70, 24, 3001)])
+def test_products_shared_over_h(pk, n, nh, no):
+    print(f"product n={n} nh={nh} no={no}", flush=True)
+    H = wl.random_operator(n, nh, seed=nh, density=0.2)
+    O = wl.random_local_strings(n, no, 8, seed=no)
+    ws = pk.Workspace(256 << 20)
+    same(pk.multiply(raw(pk, H), raw(pk, O), ws=ws).to_host(), oracle.product(H, O), "product")
