@@ -2646,6 +2646,9 @@ int pauli_mlp_train(const pauli_mlp* net, const float* x, const float* t, const 
   float* part = (float*)ar.take((size_t)nblk_max * NPARAM * 4);
   double* lpart = (double*)ar.take((size_t)nblk_max * 16);
   if (ar.short_) return ws_short(ar, ws);
+  // W2 transposed for the backward product, where the workspace has room for it
+  uint16_t* w2t = (uint16_t*)ar.take((size_t)NHID * NHID * 2);
+  if (w2t) LAUNCH("k_w2_transpose", k_w2_transpose, NHID * NHID / 256, 256, net->params_bf16, w2t);
   const int64_t spe = (n + batch - 1) / batch;  // minibatches per epoch
   int64_t step = t0;
   for (int64_t e = 0; e < epochs; e++) {
@@ -2656,6 +2659,7 @@ int pauli_mlp_train(const pauli_mlp* net, const float* x, const float* t, const 
       StepArgs sa;
       sa.params = net->params;
       sa.pb = net->params_bf16;
+      sa.w2t = w2t;
       sa.X = x;
       sa.T = t;
       sa.Mk = mask;
@@ -2663,14 +2667,14 @@ int pauli_mlp_train(const pauli_mlp* net, const float* x, const float* t, const 
       sa.rows = rows;
       sa.part = part;
       sa.lpart = lpart;
-      LAUNCH("k_mlp_step", k_mlp_step, nblk, 256, sa);
+      LAUNCH("k_mlp_step", k_mlp_step, nblk, STEP_THREADS, sa);
       step++;
       const float c1 = (float)(1.0 - std::pow(b1, (double)step));
       const float c2 = (float)(1.0 - std::pow(b2, (double)step));
       LAUNCH("k_mlp_reduce_adam", k_mlp_reduce_adam, (NPARAM + 255) / 256, 256, part, nblk,
              net->grads, net->params, net->adam_m, net->adam_v, net->params_bf16, (float)lr,
              (float)b1, (float)(1.0 - b1), (float)b2, (float)(1.0 - b2), (float)eps, c1, c2,
-             lpart, losses + e * spe + k);
+             lpart, losses + e * spe + k, w2t);
     }
   }
   HIP_TRY(hipStreamSynchronize(stream));

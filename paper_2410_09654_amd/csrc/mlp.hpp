@@ -11,6 +11,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "device_common.hpp"
+
 namespace pauli {
 namespace mlp {
 
@@ -190,22 +192,33 @@ __global__ void k_adam(float* p, const float* g, float* m, float* v, uint16_t* p
 }
 
 // ---------------------------------------------------------------------------
-// Fused training step.  One block of 256 threads (four waves) takes SR rows
-// of the minibatch (row i of the minibatch is row order[i] of the training
-// set): forward, masked MSE and backward with every activation in LDS and
-// every matrix product on the matrix cores (the same BF16 operands, FP32
-// accumulation and epilogues as the layer-by-layer kernels above), then
-// writes its rows' share of every parameter gradient to part[block][NPARAM]
-// and of the loss to lpart[block] (sum mask (y - t)^2 and the minibatch's
-// sum of mask).  k_mlp_reduce_adam sums the shares in block order and takes
-// the Adam step.  Rows beyond the minibatch are zero with zero mask, so they
-// contribute nothing.
+// Fused training step.  One block of 1024 threads (sixteen waves, wave w on
+// hidden columns 16 w .. 16 w + 15) takes SR rows of the minibatch (row i of
+// the minibatch is row order[i] of the training set): forward, masked MSE and
+// backward with every activation in LDS and every matrix product on the
+// matrix cores (the same BF16 operands, FP32 accumulation and epilogues as the
+// layer-by-layer kernels above), then writes its rows' share of every
+// parameter gradient to part[block][NPARAM] and of the loss to lpart[block]
+// (sum mask (y - t)^2 and the minibatch's sum of mask).  k_mlp_reduce_adam
+// sums the shares in block order and takes the Adam step.  Rows beyond the
+// minibatch are zero with zero mask, so they contribute nothing.
+//
+// Bound: the chain of eight dependent products with a barrier after each, on
+// as many CUs as the minibatch has SR-row blocks.  Four waves that walked
+// the tiles in turn and read the transposed operands as single 16-bit words
+// took 50.7 us for 256 rows; sixteen waves, activations held in both orders
+// (row-major for the next layer, column-major for the weight gradients, so
+// every operand is one 16-byte LDS read), weights loaded ahead of the product
+// that needs them and Z in registers: 22.7 us (a run of
+// 256-row minibatches 58.8 -> 31.6 us a minibatch).
 // ---------------------------------------------------------------------------
 constexpr int SR = 32;  // minibatch rows per block
+constexpr int STEP_THREADS = 1024;
 
 struct StepArgs {
   const float* params;   // fp32 master weights (biases)
   const uint16_t* pb;    // bf16 weights
+  const uint16_t* w2t;   // bf16 W2 transposed (nullptr: read from pb by columns)
   const float* X;        // [n][16] training inputs
   const float* T;        // [n][16] targets
   const float* Mk;       // [n][16] target mask
@@ -234,182 +247,266 @@ __device__ __forceinline__ bf16x8 bf8_strided(const uint16_t* p, int stride) {
 __device__ __forceinline__ floatx4 mfma(bf16x8 a, bf16x8 b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
+// Barrier that orders the block's LDS accesses only: loads from memory stay in
+// flight across it (__syncthreads waits for them).
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+// d[0] = d[0] + ... + d[255]: d[t] += d[t + s] for s = 128, ..., 1, from s = 32
+// on inside the first wave
+__device__ __forceinline__ void tree256(double* d, int tid) {
+  lds_barrier();
+  if (tid < 64) {
+    double v = (d[tid] + d[tid + 128]) + (d[tid + 64] + d[tid + 192]);
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) v += __shfl_down(v, s, 64);
+    if (tid == 0) d[0] = v;
+  }
+  lds_barrier();
+}
 
-__global__ __launch_bounds__(256) void k_mlp_step(StepArgs a) {
+__global__ __launch_bounds__(STEP_THREADS) void k_mlp_step(StepArgs a) {
+  constexpr int RS = NHID + 8;  // row-major row (16-bit words; 16-byte aligned, off the bank stride)
+  constexpr int CS = SR + 8;    // column-major row
+  constexpr int ZS = NHID + 4;
+  static_assert(NHID == 16 * (STEP_THREADS / 64) && SR == 32, "one column tile per wave, two row tiles");
   __shared__ __align__(16) uint16_t xb[SR][NIN];
-  __shared__ __align__(16) float z1[SR][NHID];      // Z1, then dZ1
-  __shared__ __align__(16) uint16_t y1b[SR][NHID];  // bf16 GELU(Z1), then bf16 dZ1
-  __shared__ __align__(16) float z2[SR][NHID];      // Z2, then dZ2
-  __shared__ __align__(16) uint16_t y2b[SR][NHID];  // bf16 GELU(Z2), then bf16 dZ2
-  __shared__ float yv[SR][NOUT];                    // Y, then dY
+  __shared__ __align__(16) uint16_t xT[NIN][CS];
+  __shared__ __align__(16) uint16_t y1b[SR][RS];   // bf16 GELU(Z1)
+  __shared__ __align__(16) uint16_t y1T[NHID][CS]; // the same by columns, then bf16 dZ1
+  __shared__ __align__(16) uint16_t y2b[SR][RS];   // bf16 GELU(Z2), then bf16 dZ2
+  __shared__ __align__(16) uint16_t y2T[NHID][CS];
+  __shared__ float zf[SR][ZS];                     // dZ2, then dZ1 (bias gradients)
+  __shared__ float yv[SR][NOUT];                   // Y, then dY
   __shared__ __align__(16) uint16_t dyb[SR][NOUT];
-  __shared__ int32_t rid[SR];
+  __shared__ __align__(16) uint16_t dyT[NOUT][CS];
   __shared__ double dred[256];
+  __shared__ float mk[4096];                       // mask values, 256 rows at a time
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int r = lane & 15, kq = (lane >> 4) * 8, rq = (lane >> 4) * 4;
   const int row0 = blockIdx.x * SR;
   const uint16_t* W1 = a.pb + OFF_W1;
   const uint16_t* W2 = a.pb + OFF_W2;
   const uint16_t* W3 = a.pb + OFF_W3;
-  const float* B1 = a.params + OFF_B1;
-  const float* B2 = a.params + OFF_B2;
-  const float* B3 = a.params + OFF_B3;
   float* G = a.part + (size_t)blockIdx.x * NPARAM;
+  const int n = wv * 16 + r;  // this lane's hidden column
 
-  // rows of this block and the minibatch's mask count (every block sums the
-  // same values in the same order)
-  if (tid < SR) rid[tid] = row0 + tid < a.rows ? a.order[row0 + tid] : -1;
-  double c = 0.0;
-  for (int e = tid; e < a.rows * NOUT; e += 256) c += (double)a.Mk[(size_t)a.order[e / NOUT] * NOUT + e % NOUT];
-  dred[tid] = c;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (tid < s) dred[tid] += dred[tid + s];
-    __syncthreads();
+  // Loads in two rounds: the rows of this block and of the minibatch's mask
+  // (every index clamped, so that no branch comes between loads) with the
+  // forward weights of this wave's columns, then what those rows hold.
+  // Thread t of the first half takes input and output t % 16 of row t / 16.
+  static_assert(NIN == NOUT && SR * NIN == STEP_THREADS / 2, "one input and one output per thread");
+  const int xr = (tid & 511) / NIN, xj = tid % NIN;
+  const bool have = tid < SR * NIN && row0 + xr < a.rows;
+  const int id = a.order[min(row0 + xr, a.rows - 1)];
+  const int nmask = a.rows * NOUT;
+  int mid[4];
+#pragma unroll
+  for (int q = 0; q < 4; q++) mid[q] = a.order[min(q * STEP_THREADS + tid, nmask - 1) / NOUT];
+  const bf16x8 w1 = kq < NIN ? *reinterpret_cast<const bf16x8*>(W1 + n * NIN + kq) : bf8_zero();
+  const float bias1 = a.params[OFF_B1 + n], bias2 = a.params[OFF_B2 + n];
+  bf16x8 w2[NHID / 32];
+#pragma unroll
+  for (int k = 0; k < NHID / 32; k++)
+    w2[k] = *reinterpret_cast<const bf16x8*>(W2 + n * NHID + k * 32 + kq);
+  const float tx = a.X[(size_t)id * NIN + xj];
+  const float tt = a.T[(size_t)id * NOUT + xj], tm = a.Mk[(size_t)id * NOUT + xj];
+  // the minibatch's mask, summed further down (every block sums the same
+  // values in the same order)
+  float mv[4];
+#pragma unroll
+  for (int q = 0; q < 4; q++) mv[q] = a.Mk[(size_t)mid[q] * NOUT + tid % NOUT];
+  if (tid < SR * NIN) {
+    const uint16_t v = have ? f2bf(tx) : (uint16_t)0;
+    xb[xr][xj] = v;
+    xT[xj][xr] = v;
   }
-  const double cnt = dred[0];
-  for (int e = tid; e < SR * NIN; e += 256) {
-    const int rr = e / NIN, j = e % NIN;
-    xb[rr][j] = rid[rr] >= 0 ? f2bf(a.X[(size_t)rid[rr] * NIN + j]) : (uint16_t)0;
-  }
-  __syncthreads();
+  lds_barrier();
 
   // Z1 = Xb W1^T + b1 (K = 16: lanes of k >= 16 supply zeros), Y1 = GELU(Z1)
-  for (int tt = wv; tt < 2 * (NHID / 16); tt += 4) {
-    const int mt = tt / (NHID / 16), n = (tt % (NHID / 16)) * 16 + r;
+  float z1[2][4], z2[2][4];
+#pragma unroll
+  for (int mt = 0; mt < 2; mt++) {
     const bf16x8 av = kq < NIN ? bf8_lds(&xb[mt * 16 + r][kq]) : bf8_zero();
-    const bf16x8 bv = kq < NIN ? *reinterpret_cast<const bf16x8*>(W1 + n * NIN + kq) : bf8_zero();
-    const floatx4 acc = mfma(av, bv, floatx4{0.f, 0.f, 0.f, 0.f});
+    const floatx4 acc = mfma(av, w1, floatx4{0.f, 0.f, 0.f, 0.f});
+    ushort4 t;
+    uint16_t* tv = reinterpret_cast<uint16_t*>(&t);
 #pragma unroll
     for (int q = 0; q < 4; q++) {
-      const float v = acc[q] + B1[n];
-      z1[mt * 16 + rq + q][n] = v;
-      y1b[mt * 16 + rq + q][n] = f2bf(gelu(v));
+      z1[mt][q] = acc[q] + bias1;
+      tv[q] = f2bf(gelu(z1[mt][q]));
+      y1b[mt * 16 + rq + q][n] = tv[q];
     }
+    *reinterpret_cast<ushort4*>(&y1T[n][mt * 16 + rq]) = t;
   }
-  __syncthreads();
+  lds_barrier();
   // Z2 = Y1b W2^T + b2, Y2 = GELU(Z2)
-  for (int tt = wv; tt < 2 * (NHID / 16); tt += 4) {
-    const int mt = tt / (NHID / 16), n = (tt % (NHID / 16)) * 16 + r;
+#pragma unroll
+  for (int mt = 0; mt < 2; mt++) {
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < NHID; k0 += 32)
-      acc = mfma(bf8_lds(&y1b[mt * 16 + r][k0 + kq]),
-                 *reinterpret_cast<const bf16x8*>(W2 + n * NHID + k0 + kq), acc);
+#pragma unroll
+    for (int k = 0; k < NHID / 32; k++) acc = mfma(bf8_lds(&y1b[mt * 16 + r][k * 32 + kq]), w2[k], acc);
+    ushort4 t;
+    uint16_t* tv = reinterpret_cast<uint16_t*>(&t);
 #pragma unroll
     for (int q = 0; q < 4; q++) {
-      const float v = acc[q] + B2[n];
-      z2[mt * 16 + rq + q][n] = v;
-      y2b[mt * 16 + rq + q][n] = f2bf(gelu(v));
+      z2[mt][q] = acc[q] + bias2;
+      tv[q] = f2bf(gelu(z2[mt][q]));
+      y2b[mt * 16 + rq + q][n] = tv[q];
     }
+    *reinterpret_cast<ushort4*>(&y2T[n][mt * 16 + rq]) = t;
   }
-  __syncthreads();
+  // the backward weights: W2 by columns (over the forward ones), W3 by columns
+#pragma unroll
+  for (int k = 0; k < NHID / 32; k++)
+    w2[k] = a.w2t ? *reinterpret_cast<const bf16x8*>(a.w2t + n * NHID + k * 32 + kq)
+                  : bf8_strided(W2 + (size_t)(k * 32 + kq) * NHID + n, NHID);
+  const bf16x8 w3 = kq < NOUT ? bf8_strided(W3 + (size_t)kq * NHID + n, NHID) : bf8_zero();
+#pragma unroll
+  for (int q = 0; q < 4; q++)
+    mk[q * STEP_THREADS + tid] = q * STEP_THREADS + tid < nmask ? mv[q] : 0.f;
+  lds_barrier();
   // Y = Y2b W3^T + b3
   if (wv < 2) {
-    const int mt = wv, n = r;
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < NHID; k0 += 32)
-      acc = mfma(bf8_lds(&y2b[mt * 16 + r][k0 + kq]),
-                 *reinterpret_cast<const bf16x8*>(W3 + n * NHID + k0 + kq), acc);
 #pragma unroll
-    for (int q = 0; q < 4; q++) yv[mt * 16 + rq + q][n] = acc[q] + B3[n];
+    for (int k0 = 0; k0 < NHID; k0 += 32)
+      acc = mfma(bf8_lds(&y2b[wv * 16 + r][k0 + kq]),
+                 *reinterpret_cast<const bf16x8*>(W3 + r * NHID + k0 + kq), acc);
+    const float bias3 = a.params[OFF_B3 + r];
+#pragma unroll
+    for (int q = 0; q < 4; q++) yv[wv * 16 + rq + q][r] = acc[q] + bias3;
   }
-  __syncthreads();
+  // the minibatch's mask count: thread t < 256 adds entries t, t + 256, ...
+  double c = 0.0;
+  for (int e0 = 0; e0 < nmask; e0 += 4096) {
+    if (e0) {
+      lds_barrier();
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        const int e = e0 + q * STEP_THREADS + tid;
+        mk[q * STEP_THREADS + tid] = e < nmask ? a.Mk[(size_t)a.order[e / NOUT] * NOUT + e % NOUT] : 0.f;
+      }
+      lds_barrier();
+    }
+    if (tid >= 768)  // (not the waves of the product above)
+#pragma unroll
+      for (int q = 0; q < 16; q++) c += (double)mk[q * 256 + tid - 768];
+  }
+  if (tid >= 768) dred[tid - 768] = c;
+  tree256(dred, tid);
+  const double cnt = dred[0];
+  lds_barrier();  // dred is reused below
   // masked MSE share and dY = 2 mask (y - t) / sum(mask)
-  double err = 0.0;
-  for (int e = tid; e < SR * NOUT; e += 256) {
-    const int rr = e / NOUT, j = e % NOUT;
+  __shared__ double derr[SR * NOUT];
+  if (tid < SR * NOUT) {
+    double err = 0.0;
     float g = 0.f;
-    if (rid[rr] >= 0) {
-      const size_t o = (size_t)rid[rr] * NOUT + j;
-      const double m = a.Mk[o];
-      const double d = (double)yv[rr][j] - (double)a.T[o];
-      err += m * d * d;
+    if (have) {
+      const double m = tm;
+      const double d = (double)yv[xr][xj] - (double)tt;
+      err = m * d * d;
       g = cnt > 0 ? (float)(2.0 * m * d / cnt) : 0.f;
     }
-    yv[rr][j] = g;
-    dyb[rr][j] = f2bf(g);
+    derr[tid] = err;
+    yv[xr][xj] = g;
+    dyb[xr][xj] = f2bf(g);
+    dyT[xj][xr] = f2bf(g);
   }
-  dred[tid] = err;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (tid < s) dred[tid] += dred[tid + s];
-    __syncthreads();
-  }
-  if (tid == 0) {
-    a.lpart[2 * blockIdx.x] = dred[0];
-    a.lpart[2 * blockIdx.x + 1] = cnt;
-  }
+  lds_barrier();
+  if (tid < 256) dred[tid] = derr[tid] + derr[tid + 256];
   // db3 (fixed row order) and dW3 = dYb^T Y2b (M = 16, N = 256, K = SR)
   if (tid < NOUT) {
     float sm = 0.f;
     for (int rr = 0; rr < SR; rr++) sm += yv[rr][tid];
     G[OFF_B3 + tid] = sm;
   }
-  for (int nt = wv; nt < NHID / 16; nt += 4) {
-    const int n = nt * 16 + r;
-    const floatx4 acc = mfma(bf8_strided(&dyb[kq][r], NOUT), bf8_strided(&y2b[kq][n], NHID),
-                             floatx4{0.f, 0.f, 0.f, 0.f});
+  {
+    const floatx4 acc = mfma(bf8_lds(&dyT[r][kq]), bf8_lds(&y2T[n][kq]), floatx4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
     for (int q = 0; q < 4; q++) G[OFF_W3 + (size_t)(rq + q) * NHID + n] = acc[q];
   }
-  __syncthreads();
-  // dY2 = dYb W3 (K = 16), dZ2 = dY2 GELU'(Z2) over Z2, bf16 copy over Y2b
-  for (int tt = wv; tt < 2 * (NHID / 16); tt += 4) {
-    const int mt = tt / (NHID / 16), n = (tt % (NHID / 16)) * 16 + r;
+  wave_sync();  // y2T is rewritten by the wave that has just read it
+  // dY2 = dYb W3 (K = 16), dZ2 = dY2 GELU'(Z2); its bf16 copies replace Y2
+  // (each wave read only its own columns of y2T; y2b was read before the barrier)
+#pragma unroll
+  for (int mt = 0; mt < 2; mt++) {
     const bf16x8 av = kq < NOUT ? bf8_lds(&dyb[mt * 16 + r][kq]) : bf8_zero();
-    const bf16x8 bv = kq < NOUT ? bf8_strided(W3 + (size_t)kq * NHID + n, NHID) : bf8_zero();
-    const floatx4 acc = mfma(av, bv, floatx4{0.f, 0.f, 0.f, 0.f});
+    const floatx4 acc = mfma(av, w3, floatx4{0.f, 0.f, 0.f, 0.f});
+    ushort4 t;
+    uint16_t* tv = reinterpret_cast<uint16_t*>(&t);
 #pragma unroll
     for (int q = 0; q < 4; q++) {
       const int rr = mt * 16 + rq + q;
-      const float g = acc[q] * gelu_grad(z2[rr][n]);
-      z2[rr][n] = g;
-      y2b[rr][n] = f2bf(g);
+      const float g = acc[q] * gelu_grad(z2[mt][q]);
+      tv[q] = f2bf(g);
+      zf[rr][n] = g;
+      y2b[rr][n] = tv[q];
     }
+    *reinterpret_cast<ushort4*>(&y2T[n][mt * 16 + rq]) = t;
   }
-  __syncthreads();
-  // db2 and dW2 = dZ2b^T Y1b (M = N = 256, K = SR)
-  {
+  tree256(dred, tid);
+  if (tid == 0) {
+    a.lpart[2 * blockIdx.x] = dred[0];
+    a.lpart[2 * blockIdx.x + 1] = cnt;
+  }
+  // db2 and dW2 = dZ2b^T Y1b (M = N = 256, K = SR): this wave's 16 rows
+  if (tid < NHID) {
     float sm = 0.f;
-    for (int rr = 0; rr < SR; rr++) sm += z2[rr][tid];
+#pragma unroll
+    for (int rr = 0; rr < SR; rr++) sm += zf[rr][tid];
     G[OFF_B2 + tid] = sm;
   }
-  for (int tt = wv; tt < (NHID / 16) * (NHID / 16); tt += 4) {
-    const int m0 = (tt / (NHID / 16)) * 16, n = (tt % (NHID / 16)) * 16 + r;
-    const floatx4 acc = mfma(bf8_strided(&y2b[kq][m0 + r], NHID), bf8_strided(&y1b[kq][n], NHID),
-                             floatx4{0.f, 0.f, 0.f, 0.f});
+  {
+    const bf16x8 av = bf8_lds(&y2T[n][kq]);
+#pragma unroll 4
+    for (int nt = 0; nt < NHID / 16; nt++) {
+      const floatx4 acc = mfma(av, bf8_lds(&y1T[nt * 16 + r][kq]), floatx4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-    for (int q = 0; q < 4; q++) G[OFF_W2 + (size_t)(m0 + rq + q) * NHID + n] = acc[q];
-  }
-  __syncthreads();
-  // dY1 = dZ2b W2, dZ1 = dY1 GELU'(Z1) over Z1, bf16 copy over Y1b
-  for (int tt = wv; tt < 2 * (NHID / 16); tt += 4) {
-    const int mt = tt / (NHID / 16), n = (tt % (NHID / 16)) * 16 + r;
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < NHID; k0 += 32)
-      acc = mfma(bf8_lds(&y2b[mt * 16 + r][k0 + kq]),
-                 bf8_strided(W2 + (size_t)(k0 + kq) * NHID + n, NHID), acc);
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      const int rr = mt * 16 + rq + q;
-      const float g = acc[q] * gelu_grad(z1[rr][n]);
-      z1[rr][n] = g;
-      y1b[rr][n] = f2bf(g);
+      for (int q = 0; q < 4; q++) G[OFF_W2 + (size_t)(wv * 16 + rq + q) * NHID + nt * 16 + r] = acc[q];
     }
   }
-  __syncthreads();
+  // dY1 = dZ2b W2, dZ1 = dY1 GELU'(Z1); its bf16 copy replaces Y1
+  float g1[2][4];
+#pragma unroll
+  for (int mt = 0; mt < 2; mt++) {
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < NHID / 32; k++) acc = mfma(bf8_lds(&y2b[mt * 16 + r][k * 32 + kq]), w2[k], acc);
+#pragma unroll
+    for (int q = 0; q < 4; q++) g1[mt][q] = acc[q] * gelu_grad(z1[mt][q]);
+  }
+  lds_barrier();  // every wave has read y1T and the bias sums zf
+#pragma unroll
+  for (int mt = 0; mt < 2; mt++) {
+    ushort4 t;
+    uint16_t* tv = reinterpret_cast<uint16_t*>(&t);
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      tv[q] = f2bf(g1[mt][q]);
+      zf[mt * 16 + rq + q][n] = g1[mt][q];
+    }
+    *reinterpret_cast<ushort4*>(&y1T[n][mt * 16 + rq]) = t;
+  }
+  lds_barrier();
   // db1 and dW1 = dZ1b^T Xb (M = 256, N = 16, K = SR)
-  {
+  if (tid < NHID) {
     float sm = 0.f;
-    for (int rr = 0; rr < SR; rr++) sm += z1[rr][tid];
+#pragma unroll
+    for (int rr = 0; rr < SR; rr++) sm += zf[rr][tid];
     G[OFF_B1 + tid] = sm;
   }
-  for (int mt = wv; mt < NHID / 16; mt += 4) {
-    const floatx4 acc = mfma(bf8_strided(&y1b[kq][mt * 16 + r], NHID), bf8_strided(&xb[kq][r], NIN),
-                             floatx4{0.f, 0.f, 0.f, 0.f});
+  {
+    const floatx4 acc = mfma(bf8_lds(&y1T[n][kq]), bf8_lds(&xT[r][kq]), floatx4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-    for (int q = 0; q < 4; q++) G[OFF_W1 + (size_t)(mt * 16 + rq + q) * NIN + r] = acc[q];
+    for (int q = 0; q < 4; q++) G[OFF_W1 + (size_t)(wv * 16 + rq + q) * NIN + r] = acc[q];
   }
+}
+
+// bf16 W2, transposed (see StepArgs::w2t; k_mlp_reduce_adam keeps it current).
+__global__ void k_w2_transpose(const uint16_t* pb, uint16_t* w2t) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;  // over W2, row-major
+  if (i < NHID * NHID) w2t[(i % NHID) * NHID + i / NHID] = pb[OFF_W2 + i];
 }
 
 // Gradient = the blocks' shares summed in block order; Adam step; the
@@ -417,7 +514,7 @@ __global__ __launch_bounds__(256) void k_mlp_step(StepArgs a) {
 __global__ void k_mlp_reduce_adam(const float* part, int nblk, float* grads, float* p, float* m,
                                   float* v, uint16_t* pb, float lr, float b1, float omb1, float b2,
                                   float omb2, float eps, float c1, float c2, const double* lpart,
-                                  double* loss) {
+                                  double* loss, uint16_t* w2t) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i == 0) {
     double e = 0.0;
@@ -426,17 +523,28 @@ __global__ void k_mlp_reduce_adam(const float* part, int nblk, float* grads, flo
     *loss = cnt > 0 ? e / cnt : 0.0;
   }
   if (i >= NPARAM) return;
+  const float m0 = m[i], v0 = v[i], p0 = p[i];
+  // shares loaded eight at a time, added in block order
   float gi = 0.f;
-  for (int b = 0; b < nblk; b++) gi += part[(size_t)b * NPARAM + i];
+  for (int b0 = 0; b0 < nblk; b0 += 8) {
+    float g8[8];
+#pragma unroll
+    for (int q = 0; q < 8; q++) g8[q] = b0 + q < nblk ? part[(size_t)(b0 + q) * NPARAM + i] : 0.f;
+#pragma unroll
+    for (int q = 0; q < 8; q++)
+      if (b0 + q < nblk) gi += g8[q];
+  }
   grads[i] = gi;
-  const float mi = b1 * m[i] + omb1 * gi;
-  const float vi = b2 * v[i] + omb2 * gi * gi;
+  const float mi = b1 * m0 + omb1 * gi;
+  const float vi = b2 * v0 + omb2 * gi * gi;
   m[i] = mi;
   v[i] = vi;
   const float mh = mi / c1, vh = vi / c2;
-  const float pi = p[i] - lr * mh / (sqrtf(vh) + eps);
+  const float pi = p0 - lr * mh / (sqrtf(vh) + eps);
   p[i] = pi;
   pb[i] = f2bf(pi);
+  const int64_t w = i - OFF_W2;
+  if (w2t && w >= 0 && w < NHID * NHID) w2t[(w % NHID) * NHID + w / NHID] = f2bf(pi);
 }
 
 }  // namespace mlp

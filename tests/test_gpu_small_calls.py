@@ -56,3 +56,31 @@ def test_products_shared_over_h(pk, n, nh, no):
     O = wl.random_local_strings(n, no, 8, seed=no)
     ws = pk.Workspace(256 << 20)
     same(pk.multiply(raw(pk, H), raw(pk, O), ws=ws).to_host(), oracle.product(H, O), "product")
+
+
+# minibatches that end inside a 32-row block, longer than the 256 rows whose mask is read ahead,
+# and a workspace with no room for the transposed weights: the same bits as with it
+@pytest.mark.parametrize("n,batch", [(31, 32), (300, 256), (700, 300), (513, 512)])
+def test_training_without_transposed_weights(pk, n, batch):
+    import torch
+    from paper_2410_09654_amd import surrogate
+    print(f"train n={n} batch={batch}", flush=True)
+    g = torch.Generator().manual_seed(n)
+    x = 1.0 + 0.2 * torch.randn((n, 16), generator=g)
+    t = 1.0 + 0.2 * torch.randn((n, 16), generator=g)
+    m = (torch.rand((n, 16), generator=g) < 0.7).float()
+    nblk = (batch + 31) // 32
+    least = -(-nblk * surrogate.param_offsets()[1] * 4 // 256) * 256 + -(-nblk * 16 // 256) * 256
+
+    class Least:  # exactly the gradient shares and the loss shares
+        def __init__(self):
+            self.buf = torch.empty(least, dtype=torch.uint8, device="cuda")
+
+        def c_struct(self):
+            return pk._lib.PauliWsC(self.buf.data_ptr(), least, 0)
+
+    nets = [surrogate.BnSurrogate(seed=1), surrogate.BnSurrogate(seed=1, ws=Least())]
+    hist = [net.train(x, t, m, epochs=3, batch=batch, seed=2) for net in nets]
+    assert hist[0] == hist[1]
+    assert torch.equal(nets[0].params, nets[1].params)
+    assert hist[0][-1] < hist[0][0]
