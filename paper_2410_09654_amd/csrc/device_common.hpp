@@ -17,7 +17,9 @@ namespace pauli {
 
 constexpr int NBINS_LOG = 14;
 constexpr int NBINS = 1 << NBINS_LOG;   // hash bins of a call that fits one pass
-constexpr int NBINS_LOG_SMALL = 10;     // hash bins of a call of at most 2^18 records
+constexpr unsigned long long APPEND_MAX = 1ull << 18;  // possible records of a call that appends
+                                        // to fixed buckets, with no count pass
+constexpr int NBL_APPEND = 6;           // NBL of its emission kernel (which bins nothing in LDS)
 constexpr int NBINS_LOG_MID = 12;       // hash bins of a call of at most 2^22 records
 constexpr int NBINS_LOG_MP = 15;        // hash bins per pass of a call that needs
 constexpr int NBINS_MP = 1 << NBINS_LOG_MP;  // several (twice the records per pass)
@@ -27,6 +29,9 @@ constexpr int MERGE_CAP = 1984;         // max records of one merge bucket (LDS:
 // W = 2 too (52 bytes per record in FP64).
 template <int W>
 constexpr int merge_cap() { return W == 1 ? MERGE_CAP : 1344; }
+// Records a bucket of an append call has room for: at most 1024 on average.
+template <int W>
+constexpr int append_cap() { return W == 1 ? 1408 : 1344; }
 constexpr int MERGE_THREADS = 1024;   // 16 waves; two merge blocks per CU (8 waves/SIMD)
 // Small-bucket merge: 512 threads and an LDS footprint of at most 53 KiB
 // (keys, values and source ids per record plus the 8 KiB digit table), so
@@ -210,8 +215,26 @@ DEV int num_cmp(const uint64_t* a, const uint64_t* b) {
 
 // Translations T_r, r in [0, N), that leave the string (x, z) unchanged:
 // N / p for the string's period p (the smallest divisor r of N with T_r s = s).
+// A string with a nontrivial one is left unchanged by T_{N/q} for a prime q of
+// N, so the few such rotations are tried first (`top`: bit N/q - 1 set for
+// every prime q; 128 bits); almost every string ends there.  With all divisors
+// tried for every string the norm of a 50-site step took 140 of 650 us.
+struct TsTop {
+  uint64_t w[2];
+};
 template <int W>
-DEV int ts_stabilizers(const uint64_t* x, const uint64_t* z, int N) {
+DEV int ts_stabilizers(const uint64_t* x, const uint64_t* z, int N, TsTop top) {
+  bool any = false;
+#pragma unroll
+  for (int h = 0; h < 2; h++)
+    for (uint64_t m = top.w[h]; m; m &= m - 1) {
+      const int r = 64 * h + __builtin_ctzll(m) + 1;
+      uint64_t tx[W], tz[W];
+      ts_rot_down<W>(x, N, r, tx);
+      ts_rot_down<W>(z, N, r, tz);
+      any = any || (num_cmp<W>(tx, x) == 0 && num_cmp<W>(tz, z) == 0);
+    }
+  if (!any) return 1;
   for (int r = 1; r < N; r++) {
     if (N % r) continue;
     uint64_t tx[W], tz[W];
@@ -464,6 +487,41 @@ DEV uint32_t block_exclusive_scan(uint32_t v, uint32_t* tmp, uint32_t* total) {
   *total = __shfl(t, nw - 1, 64);
   __syncthreads();  // tmp may be reused by the next scan
   return before + x - v;
+}
+
+// ---------------------------------------------------------------------------
+// Work for the last block of a grid.  Blocks hand their results over with
+// agent-scope stores (st_agent: written through this XCD's L2) or atomics,
+// then call last_block: every wave waits until its stores are acknowledged
+// and one thread draws a ticket.  The block that draws the last one learns it
+// (true for all its threads), drops what its caches may hold of the others'
+// results and puts the ticket back to zero for the next launch.  No block
+// waits for another.  A ticket costs one atomic per block where a kernel of
+// its own costs 2.5 us or more, so the grids that use it hold at most about a
+// thousand blocks.
+// ---------------------------------------------------------------------------
+template <typename T>
+DEV void st_agent(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+DEV void st_agent(double2* p, double2 v) {
+  st_agent(&p->x, v.x);
+  st_agent(&p->y, v.y);
+}
+DEV bool last_block(unsigned int* ticket) {
+  __shared__ unsigned int s_last;
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned int t =
+        __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_last = t == gridDim.x - 1 ? 1u : 0u;
+    if (s_last) st_agent(ticket, 0u);
+  }
+  __syncthreads();
+  if (!s_last) return false;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  return true;
 }
 
 }  // namespace pauli

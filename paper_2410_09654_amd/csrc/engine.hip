@@ -118,6 +118,11 @@ struct ProfScope {
       LAUNCH(name, (k_emit<W, F32, scatter, nbl, false>), rows, EMIT_THREADS, ea); \
   } while (0)
 
+// both scans of a count matrix over 2^nbl bins
+#define SCAN(nbl, counts, rows, spec_cap, mcap)                                    \
+  LAUNCH("k_scan", k_scan<nbl>, (1 << nbl) / SC_COLS, SC_COLS * SC_NSEG, counts,   \
+         rows, bin_total, bin_base, dctl, spec_cap, mcap)
+
 #define TRY(expr)                    \
   do {                               \
     int rc_ = (expr);                \
@@ -250,6 +255,19 @@ int alpha_kind(double2 a) {
   return A_GENERAL;
 }
 
+// rotations N/q, q the primes of N, as ts_stabilizers takes them
+TsTop ts_top(int N) {
+  TsTop t = {{0, 0}};
+  int m = N;
+  for (int q = 2; q <= m; q++)
+    if (m % q == 0) {
+      const int r = N / q - 1;
+      if (N > 1) t.w[r >> 6] |= 1ull << (r & 63);
+      while (m % q == 0) m /= q;
+    }
+  return t;
+}
+
 // ---------------------------------------------------------------------------
 // Planning and scratch layout of one engine call, shared by the engine and
 // pauli_workspace_query (which lays the same buffers out on an empty arena).
@@ -265,6 +283,9 @@ static_assert(COMM_ROWS_MAX + TERM_ROWS_MAX <= SC_ROWS_MAX, "k_scan_cols covers 
 constexpr int EMIT_WINDOW_TILES = 32;
 constexpr int MAX_PASS_BITS = 12;
 constexpr int DIRECT_MAX_F = 22;  // at most 2^22 buckets in a direct merge
+constexpr int64_t STREAM_MAX = 1 << 20;  // canonical terms up to here are streamed for their bounds
+constexpr uint32_t MERGE_ONE_WAVE = 512;  // buckets that the full-size merge takes at once (two
+                                          // blocks on each of 256 CUs)
 constexpr int PART_NBL = 12;  // at most 2^12 partitions (MAX_PASS_BITS)
 // blocks binning one partition: 1024 (one per CU, LDS-bound, so four
 // rounds) write shorter per-(block, bin) runs and beat 256 and 512
@@ -393,6 +414,7 @@ struct Engine {
   hipStream_t stream;
   Ctl* dctl = nullptr;
   Ctl* hctl = nullptr;
+  bool pinned = false;  // *hctl is pinned: the device writes the final control block there
   // the count's copy to the host beside the scatter (pinned control block only):
   // recorded after the scan on the call's stream, then on a side stream
   // after the copy
@@ -404,6 +426,13 @@ struct Engine {
   int read_ctl() {
     g_stats.host_syncs++;
     HIP_TRY(hipMemcpyAsync(hctl, dctl, sizeof(Ctl), hipMemcpyDeviceToHost, stream));
+    HIP_TRY(hipStreamSynchronize(stream));
+    g_prof.resolve();
+    return PAULI_OK;
+  }
+  // waits for the stream; the device has written the control block to *hctl
+  int wait_ctl() {
+    g_stats.host_syncs++;
     HIP_TRY(hipStreamSynchronize(stream));
     g_prof.resolve();
     return PAULI_OK;
@@ -434,7 +463,7 @@ int ws_short(Arena& ar, pauli_ws* ws) {
 template <int W, bool F32>
 int Engine::run(Call& c) {
   const size_t KB = sizeof(Key<W>);
-  const size_t RB = sizeof(Rec<W, F32>);
+  constexpr size_t RB = sizeof(Rec<W, F32>);
   ar->bottom = 0;
   const size_t top0 = ar->top;
   memset(&g_stats, 0, sizeof(g_stats));
@@ -476,8 +505,41 @@ int Engine::run(Call& c) {
   plan_rows(comm, c.H.n, c.O.n, nterm_rec, &comm_rows, &term_rows, &hseg);
   const int rows = comm_rows + term_rows;
 
+  // canonical linear combinations are merged from their terms (below), calls
+  // of at most 2^18 possible records append to fixed buckets
+  bool direct = !run_emit && !comm && c.n_terms > 0 && !c.ts && !c.product &&
+                nterm_rec < ((int64_t)1 << 31);
+  for (int t = 0; t < c.n_terms && direct; t++) {
+    direct = !c.tlist[t];
+    for (int u = 0; u < t; u++) direct = direct && c.tgroup[u] != c.tgroup[t];
+  }
+  const bool want_select = tr && tr->max_strings > 0;
+  const unsigned long long rec_bound =
+      (comm ? (unsigned long long)c.H.n * (unsigned long long)c.O.n : 0ull) +
+      (unsigned long long)nterm_rec;
+  bool append = !direct && !run_counted && rows > 0 && rec_bound <= APPEND_MAX;
+  constexpr int ACAP = append_cap<W>();
+  int append_F = 1;
+  while (rec_bound > (1024ull << append_F)) append_F++;
   Bufs1<W> b1;
+  Bufs2 b2;
   take_bufs1<W>(*ar, comm, c.H.n, n_keep, rows, b1);
+  if (append && !ar->short_) {
+    const size_t mark_bottom = ar->bottom, mark_need = ar->need;
+    // the records lie where the count matrix would
+    static_assert(((size_t)ACAP << 8) * RB <= (size_t)256 * NBINS_MP * 4,
+                  "the records of an append call fit the count matrix");
+    take_bufs2<W, F32>(*ar, (size_t)ACAP << append_F, true, false, 1u << append_F, want_select, b2,
+                       false);
+    b2.recs = b1.counts;
+    if (ar->short_) {  // the workspace holds the counted layout only
+      ar->bottom = mark_bottom;
+      ar->need = mark_need;
+      ar->short_ = false;
+      append = false;
+      b2 = Bufs2();
+    }
+  }
   dctl = b1.dctl;
   uint64_t* Hk = b1.Hk;
   uint32_t* Hidx = b1.Hidx;
@@ -493,9 +555,10 @@ int Engine::run(Call& c) {
   uint32_t* h0sum = b1.h0sum;
   unsigned long long* psum = b1.psum;
   if (ar->short_) return PAULI_EWORKSPACE;
-  if (!hctl) TRY(host_ctl(&hctl));
-  // the control block starts at zero (cleared by k_prep_h when there is one)
-  if (!comm || rows == 0) TRY(zero_u32(dctl, sizeof(Ctl) / 4));
+  if (!hctl) {
+    TRY(host_ctl(&hctl));
+    pinned = true;
+  }
 
   auto write_empty = [&]() -> int {
     if (c.out.to_arena) {
@@ -515,11 +578,36 @@ int Engine::run(Call& c) {
     }
     return write_empty();
   }
-  if (comm) {
-    LAUNCH("k_prep_h", (k_prep_h<W>), 1, 1024, c.H.x, c.H.z, c.H.cap, (int)c.H.n, Hk, Hidx,
-           hstart, hspan, (uint32_t*)dctl, (uint32_t)(sizeof(Ctl) / 4));
+  {
+    // clears the control block and the level-0 |c|^2 histogram, lays out H
+    PrepArgs pr;
+    memset(&pr, 0, sizeof(pr));
+    if (comm) {
+      pr.x = c.H.x;
+      pr.z = c.H.z;
+      pr.cap = c.H.cap;
+      pr.n = (int)c.H.n;
+    }
+    pr.packed = Hk;
+    pr.hidx = Hidx;
+    pr.hstart = hstart;
+    pr.hspan = hspan;
+    if (n_keep && n_keep <= KEEP_PREP) {
+      pr.kx = keep->x;
+      pr.kz = keep->z;
+      pr.kcap = keep->capacity;
+      pr.n_keep = (int)n_keep;
+      pr.keep_mk = keep_mk;
+    }
+    pr.hist0 = hist0;
+    if (append) {
+      pr.cursor = bin_base;
+      pr.n_cursor = 1 << append_F;
+    }
+    pr.ctl = dctl;
+    LAUNCH("k_prep", (k_prep<W>), PREP_BLOCKS, 1024, pr);
   }
-  if (n_keep) {
+  if (n_keep > KEEP_PREP) {
     LAUNCH("k_mix_keys", (k_mix_keys<W>), (n_keep + 255) / 256, 256, keep->x, keep->z,
            keep->capacity, n_keep, keep_mk, &dctl->bad_keep);
   }
@@ -533,10 +621,7 @@ int Engine::run(Call& c) {
   // empty and the call is redone by emission (run_emit), as it is when strings
   // crowd one bucket beyond the merge's capacity.
   unsigned long long pe_all = 0;
-  bool planned = false;  // one pass planned from the sizes alone (no count read)
   bool scattered = false;  // one pass over 2^14 bins scattered before the count was read
-  const bool want_select = tr && tr->max_strings > 0;
-  Bufs2 b2;
   MergeArgs ma;
   uint32_t nbk = 0;  // buckets written so far
   int npass = 1;
@@ -567,12 +652,6 @@ int Engine::run(Call& c) {
     ma.ctl = dctl;
     ma.defer = nullptr;
   };
-  bool direct = !run_emit && !comm && c.n_terms > 0 && !c.ts && !c.product &&
-                nterm_rec < ((int64_t)1 << 31);
-  for (int t = 0; t < c.n_terms && direct; t++) {
-    direct = !c.tlist[t];
-    for (int u = 0; u < t; u++) direct = direct && c.tgroup[u] != c.tgroup[t];
-  }
   if (direct) {
     // 2^F buckets of at most 0.85 of the small merge's capacity on average
     constexpr int SCAP = small_merge_cap<W, F32>();
@@ -587,6 +666,8 @@ int Engine::run(Call& c) {
     tv.n_terms = c.n_terms;
     tv.F = F;
     tv.bounds = tbounds;
+    uint32_t streamed = 0;  // terms whose bounds come from one pass over them
+    int64_t nstream = 0;
     for (int t = 0; t < c.n_terms; t++) {
       const OpV& T = c.T[t];
       tv.tx[t] = T.x;
@@ -596,25 +677,35 @@ int Engine::run(Call& c) {
       tv.tc[t] = T.c;
       tv.tf32[t] = T.f32;
       tv.tgroup[t] = (uint32_t)c.tgroup[t];
-      if (!T.canon && T.n > 1)
-        LAUNCH("k_check_sorted", (k_check_sorted<W>),
-               (int)std::min<int64_t>((T.n + 255) / 256, 4096), 256, T.x, T.z, T.cap, T.n,
-               &dctl->unsorted);
+      if (!T.canon || T.n <= STREAM_MAX) {
+        streamed |= 1u << t;
+        nstream += T.n + 1;
+      }
     }
+    if (streamed)
+      LAUNCH("k_term_stream", (k_term_stream<W>), (nstream + 255) / 256, 256, tv, streamed, tbounds,
+             &dctl->unsorted);
     const int64_t nbounds = (int64_t)c.n_terms * (nb + 1);
-    LAUNCH("k_term_bounds", (k_term_bounds<W>), (nbounds + 255) / 256, 256, tv, tbounds);
-    TRY(zero_u32(hist0, (size_t)HREP * SEL0_BINS));
+    const uint32_t search = ((1u << c.n_terms) - 1u) & ~streamed;
+    if (search)
+      LAUNCH("k_term_bounds", (k_term_bounds<W>), (nbounds + 255) / 256, 256, tv, search, tbounds);
     merge_common();
     ma.tv = tv;
     ma.nbins_log = F;
     ma.digit_shift = F;
-    ma.defer = b1.defer;
-    // buckets above the small variant's capacity go to the full-size one
-    LAUNCH("k_merge_small", (k_merge<W, F32, MERGE_SMALL_THREADS, SCAP, MERGE_SMALL, true>), nb,
-           MERGE_SMALL_THREADS, ma);
-    LAUNCH("k_merge_deferred",
-           (k_merge<W, F32, MERGE_THREADS, merge_cap<W>(), MERGE_LIST, true>),
-           std::min<uint32_t>(nb, 512), MERGE_THREADS, ma);
+    if (nb <= MERGE_ONE_WAVE) {
+      // every bucket has a CU: the full-size variant takes them all at once
+      LAUNCH("k_merge", (k_merge<W, F32, MERGE_THREADS, merge_cap<W>(), MERGE_GRID, true>), nb,
+             MERGE_THREADS, ma);
+    } else {
+      ma.defer = b1.defer;
+      // buckets above the small variant's capacity go to the full-size one
+      LAUNCH("k_merge_small", (k_merge<W, F32, MERGE_SMALL_THREADS, SCAP, MERGE_SMALL, true>), nb,
+             MERGE_SMALL_THREADS, ma);
+      LAUNCH("k_merge_deferred",
+             (k_merge<W, F32, MERGE_THREADS, merge_cap<W>(), MERGE_LIST, true>),
+             std::min<uint32_t>(nb, 512), MERGE_THREADS, ma);
+    }
     nbk = nb;
     pe_all = (unsigned long long)nterm_rec;
   }
@@ -657,89 +748,68 @@ int Engine::run(Call& c) {
     ea.bin_base = bin_base;
     ea.max_len = (c.mode == M_PLAIN && tr) ? tr->max_len : 0;
 
+    if (append) {
+      // A call of at most 2^18 possible records needs no count: 2^append_F
+      // buckets whose mean stays within 1024 even if every possible record is
+      // emitted, records appended by atomics on the bucket cursors (the merge sorts them), every bucket merged at once.  A
+      // bucket above the capacity sends the call round again with the count
+      // read first.  Count, scan and the deferral list took 19 of the 59 us
+      // that the kernels of a step of a few hundred strings took.
+      ea.recs = b2.recs;
+      ea.rsrc_wide = b2.rsrc_wide;
+      ea.wide = 1;
+      ea.cursor = bin_base;
+      ea.append_F = append_F;
+      ea.append_cap = (uint32_t)ACAP;
+      EMIT("k_emit_append", true, NBL_APPEND);
+      merge_common();
+      ma.bin_count = bin_base;
+      ma.append_cap = ea.append_cap;
+      ma.recs = b2.recs;
+      ma.rsrc_wide = b2.rsrc_wide;
+      ma.wide = 1;
+      ma.nbins_log = append_F;
+      ma.digit_shift = append_F;
+      nbk = 1u << append_F;
+      LAUNCH("k_merge", (k_merge<W, F32, MERGE_THREADS, merge_cap<W>(), MERGE_GRID>), nbk,
+             MERGE_THREADS, ma);
+      pe_all = rec_bound;
+    } else {
     // 2^nbl hash bins per pass: NBINS_LOG while the call fits one pass,
     // NBINS_LOG_MP (twice the records per pass) when it needs several, and
-    // NBINS_LOG_SMALL for calls of at most 2^18 records even if every pair
-    // emits one, NBINS_LOG_MID for at most 2^22 (the per-call bin tables then
-    // cost a sixteenth and a quarter)
+    // NBINS_LOG_MID for calls of at most 2^22 records even if every pair emits
+    // one (the per-call bin tables then cost a quarter)
     int nbl = NBINS_LOG;
-    const unsigned long long rec_bound =
-        (comm ? (unsigned long long)c.H.n * (unsigned long long)c.O.n : 0ull) +
-        (unsigned long long)nterm_rec;
-    if (rec_bound <= (1ull << (NBINS_LOG_SMALL + 8))) nbl = NBINS_LOG_SMALL;
-    else if (rec_bound <= (1ull << (NBINS_LOG_MID + 10)) && (!comm || c.H.n < (1 << (NBINS_LOG_MID - 3))))
+    if (rec_bound <= (1ull << (NBINS_LOG_MID + 10)) && (!comm || c.H.n < (1 << (NBINS_LOG_MID - 3))))
       nbl = NBINS_LOG_MID;
     auto count_pass = [&](int pass_bits, uint32_t pass_id, bool read = true,
                           unsigned long long spec_cap = 0ull) -> int {
       ea.pass_bits = pass_bits;
       ea.pass_id = pass_id;
-      // the first count pass of a merge sequence also clears the level-0 |c|^2 histogram
-      uint32_t* zero = pass_id == 0 ? hist0 : (uint32_t*)nullptr;
-      const uint32_t nzero = pass_id == 0 ? (uint32_t)(HREP * SEL0_BINS) : 0u;
-      if (nbl == NBINS_LOG_SMALL) {
-        constexpr int NBS = 1 << NBINS_LOG_SMALL;
-        EMIT("k_emit_count", false, NBINS_LOG_SMALL);
-        if (rows <= SMALL_SCAN_ROWS) {
-          LAUNCH("k_scan_small", k_scan_small, HREP, 1024, counts, rows, bin_base, dctl, zero,
-                 nzero);
-        } else {
-          LAUNCH("k_scan_cols", k_scan_cols, NBS / SC_COLS, SC_COLS * SC_NSEG, counts, rows,
-                 bin_total, dctl, NBS);
-          LAUNCH("k_scan_bins", k_scan_bins<NBINS_LOG_SMALL>, 1, 1024, bin_total, bin_base, dctl,
-                 zero, nzero);
-        }
-      } else if (nbl == NBINS_LOG_MID) {
-        constexpr int NBM = 1 << NBINS_LOG_MID;
+      const unsigned int mcap = merge_cap<W>();
+      if (nbl == NBINS_LOG_MID) {
         EMIT("k_emit_count", false, NBINS_LOG_MID);
-        LAUNCH("k_scan_cols", k_scan_cols, NBM / SC_COLS, SC_COLS * SC_NSEG, counts, rows, bin_total, dctl, NBM);
-        LAUNCH("k_scan_bins", k_scan_bins<NBINS_LOG_MID>, 1, 1024, bin_total, bin_base, dctl, zero,
-               nzero, spec_cap, (unsigned int)merge_cap<W>());
+        SCAN(NBINS_LOG_MID, counts, rows, spec_cap, mcap);
       } else if (nbl == NBINS_LOG) {
         EMIT("k_emit_count", false, NBINS_LOG);
-        LAUNCH("k_scan_cols", k_scan_cols, NBINS / SC_COLS, SC_COLS * SC_NSEG, counts, rows, bin_total, dctl, NBINS);
-        LAUNCH("k_scan_bins", k_scan_bins<NBINS_LOG>, 1, 1024, bin_total, bin_base, dctl, zero,
-               nzero, spec_cap, (unsigned int)merge_cap<W>());
+        SCAN(NBINS_LOG, counts, rows, spec_cap, mcap);
       } else {
         EMIT("k_emit_count", false, NBINS_LOG_MP);
-        LAUNCH("k_scan_cols", k_scan_cols, NBINS_MP / SC_COLS, SC_COLS * SC_NSEG, counts, rows, bin_total, dctl,
-               NBINS_MP);
-        LAUNCH("k_scan_bins", k_scan_bins<NBINS_LOG_MP>, 1, 1024, bin_total, bin_base, dctl, zero,
-               nzero);
+        SCAN(NBINS_LOG_MP, counts, rows, 0ull, mcap);
       }
       return read ? read_ctl() : PAULI_OK;
     };
     // source ids fold into the key bits implied by the bin unless an index
     // needs more than 11 bits (H above 2047 strings, canonicalisation lists)
     // (translation-symmetric calls carry (H entry, rotation) as the source id)
-    // (7 bits over 2^10 bins, 9 over 2^12)
+    // (9 bits over 2^12 bins)
     auto wide_for = [&](int bins_log) {
       const int64_t max_h = (1 << (std::min(bins_log, NBINS_LOG) - 3)) - 1;
       bool w = comm && (c.H.n > max_h || c.ts);
       for (int t = 0; t < c.n_terms; t++) w = w || c.tlist[t];
       return w;
     };
-    // A call of at most 2^18 possible records runs one pass over 2^10 bins
-    // planned from its sizes alone (records laid out at that bound, a fixed
-    // bucket width), so the host reads nothing before the output size; the
-    // count's bins are checked then, and a call whose strings crowd a bucket
-    // is redone with the count read first.
-    if (nbl == NBINS_LOG_SMALL && !run_counted) {
-      TRY(count_pass(0, 0, false));
-      const size_t mark_bottom = ar->bottom, mark_need = ar->need;
-      take_bufs2<W, F32>(*ar, (size_t)std::max<unsigned long long>(rec_bound, 1),
-                         wide_for(NBINS_LOG_SMALL), false, (1u << NBINS_LOG_SMALL) << 2,
-                         want_select, b2);
-      if (ar->short_) {
-        // the workspace holds the exact layout only: read the count
-        ar->bottom = mark_bottom;
-        ar->need = mark_need;
-        ar->short_ = false;
-        run_counted = true;
-        TRY(read_ctl());
-      } else {
-        planned = true;
-      }
-    } else if (nbl != NBINS_LOG_SMALL && ctl_event &&
+    if (ctl_event &&
                rec_bound <= 7ull * (1ull << NBINS_LOG) * (unsigned long long)merge_cap<W>()) {
       // A call that may fit one pass over 2^12 or 2^14 bins (at most seven passes'
       // worth of possible records) is laid out for as many records as the
@@ -795,17 +865,17 @@ int Engine::run(Call& c) {
     } else {
       TRY(count_pass(0, 0));
     }
-    if (!planned && nbl < NBINS_LOG && hctl->maxg[0] > (unsigned int)merge_cap<W>()) {
-      // a small call whose records crowd one bin: count again over 2^14 bins
+    if (nbl < NBINS_LOG && hctl->maxg[0] > (unsigned int)merge_cap<W>()) {
+      // records that crowd one bin of 2^12: count again over 2^14 bins
       nbl = NBINS_LOG;
       TRY(count_pass(0, 0));
     }
-    if (!planned && hctl->bad_keep) return PAULI_EINVAL;
-    if (!planned && (hctl->overflow & 2u)) {
+    if (hctl->bad_keep) return PAULI_EINVAL;
+    if (hctl->overflow & 2u) {
       g_last_error = "more than 2^32 records in one pass";
       return PAULI_EINTERNAL;
     }
-    pe_all = planned ? rec_bound : hctl->pe_total;
+    pe_all = hctl->pe_total;
     // passes over disjoint hash ranges keep every bucket within the merge capacity; the
     // largest bin does not always halve with each extra pass bit (all records
     // of one string share a bin), so a pass that still overflows restarts the
@@ -818,7 +888,7 @@ int Engine::run(Call& c) {
     // bins): half the destinations and count rows for the pass binning, and
     // its 64 KB bin table lets two blocks share a CU.
     int pnbl = nbl;  // bins per pass of the merge (and of the pass binning)
-    if (!planned && nbl == NBINS_LOG_MP && pass_bits > 0 &&
+    if (nbl == NBINS_LOG_MP && pass_bits > 0 &&
         (double)hctl->maxg[0] <= std::ldexp(0.8 * merge_cap<W>(), pass_bits))
       pnbl = NBINS_LOG;
     const int table_bits = std::min(pass_bits + 2, MAX_PASS_BITS);
@@ -827,7 +897,7 @@ int Engine::run(Call& c) {
     // ----- records, U, bucket tables, candidate lists -------------------------
     const bool wide = wide_for(nbl);
     const bool partitioned = nbl == NBINS_LOG_MP;
-    if (!planned && !scattered) {
+    if (!scattered) {
       take_bufs2<W, F32>(*ar, ptot, wide, partitioned, max_buckets, want_select, b2);
       if (ar->short_) return PAULI_EWORKSPACE;
     }
@@ -918,20 +988,12 @@ int Engine::run(Call& c) {
         if (pass_bits > 0) {
           // bin partition p: histogram, scans (and the host check below)
           sp.part = (uint32_t)p;
-          uint32_t* zero = p == 0 ? hist0 : (uint32_t*)nullptr;
-          const uint32_t nzero = p == 0 ? (uint32_t)(HREP * SEL0_BINS) : 0u;
           if (pnbl == NBINS_LOG) {
             LAUNCH("k_split_count", (k_split<W, F32, false, NBINS_LOG>), SPLIT_ROWS, 1024, sp);
-            LAUNCH("k_scan_cols", k_scan_cols, NBINS / SC_COLS, SC_COLS * SC_NSEG, scounts,
-                   SPLIT_ROWS, bin_total, dctl, NBINS);
-            LAUNCH("k_scan_bins", k_scan_bins<NBINS_LOG>, 1, 1024, bin_total, bin_base, dctl, zero,
-                   nzero);
+            SCAN(NBINS_LOG, scounts, SPLIT_ROWS, 0ull, 0u);
           } else {
             LAUNCH("k_split_count", (k_split<W, F32, false, NBINS_LOG_MP>), SPLIT_ROWS, 1024, sp);
-            LAUNCH("k_scan_cols", k_scan_cols, NBINS_MP / SC_COLS, SC_COLS * SC_NSEG, scounts,
-                   SPLIT_ROWS, bin_total, dctl, NBINS_MP);
-            LAUNCH("k_scan_bins", k_scan_bins<NBINS_LOG_MP>, 1, 1024, bin_total, bin_base, dctl,
-                   zero, nzero);
+            SCAN(NBINS_LOG_MP, scounts, SPLIT_ROWS, 0ull, 0u);
           }
           TRY(read_ctl());
         } else if (nbl == NBINS_LOG_MP) {
@@ -939,34 +1001,6 @@ int Engine::run(Call& c) {
           // overwrites the first count pass's NBINS_LOG-bin prefixes and totals
           TRY(count_pass(pass_bits, (uint32_t)p));
           first_counts = false;
-        }
-        if (planned) {
-          // buckets of 2^g bins whose mean stays within 0.85 of the small
-          // merge's capacity even if every possible record is emitted; the
-          // merges and the deferral list take whatever arrives, and a bucket
-          // above the full-size merge's capacity sends the call round again
-          constexpr int SCAP = small_merge_cap<W, F32>();
-          int g_log = 4;
-          while (g_log > 0 &&
-                 (double)pe_all > std::ldexp(0.85 * SCAP, NBINS_LOG_SMALL - g_log))
-            g_log--;
-          EMIT("k_emit_scatter", true, NBINS_LOG_SMALL);
-          ma.g_log = g_log;
-          ma.nbins_log = nbl;
-          ma.digit_shift = nbl - g_log;
-          ma.pass_bits = 0;
-          ma.pass_id = 0;
-          ma.u_off = 0;
-          ma.bucket_off = 0;
-          const uint32_t nb_pass = (uint32_t)((1u << nbl) >> g_log);
-          ma.defer = b1.defer;
-          LAUNCH("k_merge_small", (k_merge<W, F32, MERGE_SMALL_THREADS, SCAP, MERGE_SMALL>),
-                 nb_pass, MERGE_SMALL_THREADS, ma);
-          // deferrals are rare here: a few blocks loop over the list
-          LAUNCH("k_merge_deferred", (k_merge<W, F32, MERGE_THREADS, merge_cap<W>(), MERGE_LIST>),
-                 std::min<uint32_t>(nb_pass, 16), MERGE_THREADS, ma);
-          nbk = nb_pass;
-          continue;
         }
         if (pass_bits > 0 && p == 0 && hctl->part_total != pe_all) {
           char msg[160];
@@ -988,6 +1022,7 @@ int Engine::run(Call& c) {
           }
           pass_bits++;
           done = false;
+          TRY(zero_u32(hist0, (size_t)HREP * SEL0_BINS));  // the earlier passes' merges filled it
           break;
         }
         int g_log = 4;
@@ -999,8 +1034,6 @@ int Engine::run(Call& c) {
           LAUNCH("k_split_scatter", (k_split<W, F32, true, NBINS_LOG_MP>), SPLIT_ROWS, 1024, sp);
         else if (scattered)
           ;  // launched before the count was read
-        else if (nbl == NBINS_LOG_SMALL)
-          EMIT("k_emit_scatter", true, NBINS_LOG_SMALL);
         else if (nbl == NBINS_LOG_MID)
           EMIT("k_emit_scatter", true, NBINS_LOG_MID);
         else if (nbl == NBINS_LOG)
@@ -1037,6 +1070,7 @@ int Engine::run(Call& c) {
         nbk += nb_pass;
         u_off += pe;
       }
+    }
     }
   }
   void* uk = b2.uk;
@@ -1075,12 +1109,13 @@ int Engine::run(Call& c) {
   // ----- Lanczos: b_n from the untruncated sum, then divide and filter -------
   const double lanczos_floor_b = 1e-13 * (c.b_prev > 1.0 ? c.b_prev : 1.0);
   if (c.mode == M_LANCZOS) {
+    const int nblk = (int)std::min<uint32_t>((nbk + 3) / 4, NORM_BLOCKS);
     if (c.ts)
-      LAUNCH("k_norm_bucket_ts", (k_norm_bucket_ts<W>), nbk, 256, b_ubase, b_slots, uk, uc,
-             c.ts, norm_part);
+      LAUNCH("k_norm", (k_norm<W, true>), nblk, 256, b_ubase, b_slots, uk, uc, c.ts, ts_top(c.ts),
+             nbk, norm_part, dctl);
     else
-      LAUNCH("k_norm_bucket", k_norm_bucket, nbk, 256, b_ubase, b_slots, uc, norm_part);
-    LAUNCH("k_reduce_dd", k_reduce_dd, 1, 1024, norm_part, nbk, &dctl->norm_hi);
+      LAUNCH("k_norm", (k_norm<W, false>), nblk, 256, b_ubase, b_slots, uk, uc, 0, TsTop{{0, 0}},
+             nbk, norm_part, dctl);
     // b_n and the breakdown test are taken on the device (no read here); a
     // breakdown leaves nothing to keep, and the host reports it with the
     // output size
@@ -1090,6 +1125,7 @@ int Engine::run(Call& c) {
     sa.b_slots = b_slots;
     sa.b_surv = b_surv;
     sa.b_keep = b_keep;
+    sa.nbk = nbk;
     sa.uk = uk;
     sa.uc = uc;
     sa.norm2 = &dctl->norm_hi;
@@ -1102,7 +1138,8 @@ int Engine::run(Call& c) {
     sa.n_keep = (int)n_keep;
     sa.hist0 = hist0;
     sa.ctl = dctl;
-    LAUNCH("k_scale_filter", (k_scale_filter<W>), nbk, 256, sa);
+    LAUNCH("k_scale_filter", (k_scale_filter<W>),
+           (int)std::min<uint32_t>((nbk + 7) / 8, SCALE_BLOCKS), 512, sa);
   }
 
   // ----- top-M threshold, output offsets and write, decided on the device ---
@@ -1118,7 +1155,11 @@ int Engine::run(Call& c) {
   s2.keep_mk = keep_mk;
   s2.n_keep = (int)n_keep;
   s2.nbk = nbk;
+  s2.b_surv = b_surv;
+  s2.b_keep = b_keep;
+  s2.b_obase = b_obase;
   s2.ctl = dctl;
+  s2.hctl = pinned ? hctl : nullptr;
   if (want_select) {
     // the candidate lists of the multi-level select double as these lists
     s2.list0 = cand[1];
@@ -1140,16 +1181,15 @@ int Engine::run(Call& c) {
   pa.hist1 = want_select ? histL[1] : nullptr;
   pa.psum = psum;
   pa.h0sum = h0sum;
+  pa.b_obase = b_obase;
   pa.ctl = dctl;
-  LAUNCH("k_plan_sums", k_plan_sums, 3 * PLAN_PARTS, 1024, pa);
-  LAUNCH("k_sel_plan", k_sel_plan, 1, 1024, pa);
+  pa.hctl = pinned ? hctl : nullptr;
+  LAUNCH("k_plan", k_plan, !want_select && nbk <= PLAN_ONE ? 1 : 3 * PLAN_PARTS, 1024, pa);
   if (want_select) {
-    LAUNCH("k_sel_pass1", (k_sel_pass1<W>), nchunk, 256, s2);
-    LAUNCH("k_sel_pick1", k_sel_pick1, 1, 1024, histL[1], dctl);
-    LAUNCH("k_sel_narrow", (k_sel_narrow<W>), nchunk, 256, s2);
-    LAUNCH("k_sel_finish", (k_sel_finish<W>), 1, 1024, s2);
+    const int nsel = (int)std::min<uint32_t>((nbk + 15) / 16, SEL_BLOCKS);
+    LAUNCH("k_sel_pass1", (k_sel_pass1<W>), nsel, 1024, s2);
+    LAUNCH("k_sel_narrow", (k_sel_narrow<W>), nsel, 1024, s2);
   }
-  LAUNCH("k_scan_out", k_scan_out, 1, 1024, b_surv, b_keep, b_abv, b_bcnt, nbk, b_obase, dctl);
 
   WriteArgs wa;
   memset(&wa, 0, sizeof(wa));
@@ -1194,7 +1234,7 @@ int Engine::run(Call& c) {
     wa.ocap = o->capacity;
   }
   LAUNCH("k_write_out", (k_write_out<W>), nchunk, 256, wa, nbk);
-  TRY(read_ctl());
+  TRY(pinned ? wait_ctl() : read_ctl());
   if (direct && (hctl->unsorted || hctl->overflow)) {
     // a term out of canonical order (the buckets were left empty), or strings
     // crowded into one bucket beyond the merge's capacity: redo by emission,
@@ -1203,14 +1243,14 @@ int Engine::run(Call& c) {
     run_emit = true;
     return run<W, F32>(c);
   }
-  if (planned && (hctl->overflow || hctl->maxg[0] > (unsigned int)merge_cap<W>())) {
-    // strings crowded into one bucket of the planned pass: redo with the
-    // count read first, whose plan splits them
+  if (append && hctl->overflow) {
+    // strings crowded into one bucket: redo with the count read first, whose
+    // plan splits them
     ar->top = top0;
     run_counted = true;
     return run<W, F32>(c);
   }
-  if (planned) {
+  if (append) {
     if (hctl->bad_keep) return PAULI_EINVAL;
     g_stats.emitted = (int64_t)hctl->pe_total;
   }
@@ -1454,7 +1494,7 @@ void dry_call(Arena& ar, const DryCall& d, unsigned long long* pe_out) {
   const uint32_t max_buckets = (uint32_t)(1u << nbl) << table_bits;
   Bufs2 b2;
   // source ids aside as the engine decides (7-bit H indices over 2^10 bins)
-  const int64_t max_h = pe <= (1ull << (NBINS_LOG_SMALL + 8)) ? (1 << (NBINS_LOG_SMALL - 3)) - 1 : 2047;
+  const int64_t max_h = pe <= APPEND_MAX ? 127 : 2047;
   take_bufs2<W, F32>(ar, (size_t)std::max<unsigned long long>(pe, 1), d.wide || (comm && (nH > max_h || d.ts)),
                      nbl == NBINS_LOG_MP, max_buckets, d.select, b2);
   if (d.out_arena >= 0) {
@@ -1867,17 +1907,17 @@ int pauli_norm2_ts1d(const pauli_op* A, double* out, pauli_ws* ws, void* stream_
   if (W == 1) {
     if (f32)
       LAUNCH("k_norm_part_ts", (k_norm_part_ts<1, true>), blocks, 256, A->x, A->z, A->capacity,
-             A->coef, A->size, N, part);
+             A->coef, A->size, N, ts_top(N), part);
     else
       LAUNCH("k_norm_part_ts", (k_norm_part_ts<1, false>), blocks, 256, A->x, A->z, A->capacity,
-             A->coef, A->size, N, part);
+             A->coef, A->size, N, ts_top(N), part);
   } else {
     if (f32)
       LAUNCH("k_norm_part_ts", (k_norm_part_ts<2, true>), blocks, 256, A->x, A->z, A->capacity,
-             A->coef, A->size, N, part);
+             A->coef, A->size, N, ts_top(N), part);
     else
       LAUNCH("k_norm_part_ts", (k_norm_part_ts<2, false>), blocks, 256, A->x, A->z, A->capacity,
-             A->coef, A->size, N, part);
+             A->coef, A->size, N, ts_top(N), part);
   }
   LAUNCH("k_reduce_dd", k_reduce_dd, 1, 1024, part, (uint32_t)blocks, res);
   double h[2];

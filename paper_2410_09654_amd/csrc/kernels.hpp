@@ -6,8 +6,7 @@
 //                   anticommuting pair the product string's mixed key picks a
 //                   hash bin; per-workgroup bin histograms (LDS) -> counts
 //                   matrix [rows][NBINS]; operator terms are binned the same way
-//   k_scan_cols / k_scan_bins
-//                   column prefix of the counts matrix, bin bases, bucket sizes
+//   k_scan          column prefix of the counts matrix, bin bases, bucket sizes
 //   k_emit<SCATTER> the same pair loop, writing records (mixed key, value,
 //                   source id) at their bin's cursor
 //   k_merge         one workgroup per bucket of bins: records -> LDS, counting
@@ -15,6 +14,8 @@
 //                   range, then every run of equal keys is folded in ascending
 //                   source id (the canonical summation order), filtered, and
 //                   written compactly; level-0 histogram of |c|^2 for top-M
+//   k_norm, k_scale_filter
+//                   Lanczos steps: b_n from the merged strings, division, filters
 //   k_select / k_level1 / k_cand_level / k_finish / k_count_boundary
 //                   exact radix select of the M-th largest (|c|^2, key) pair
 //   k_scan_buckets / k_write
@@ -59,11 +60,12 @@ struct Ctl {
   unsigned int ndefer;           // buckets deferred to the full-size merge (this pass)
   unsigned int unsorted;         // a term of a direct merge is not in canonical order
   unsigned int spec_fail;        // a scatter launched before the count was read stands down
+  unsigned int ticket[4];        // last_block: scan, norm, plan, select
 };
 
 struct EmitArgs {
   // commutator group: H packed [nH][2W] raw words in ascending order of their
-  // lowest site (k_prep_h), with each entry's index in the caller's H and the
+  // lowest site (k_prep), with each entry's index in the caller's H and the
   // first entry whose lowest site is >= s (hstart[s], s = 0 .. 64W + 1);
   // O word-major
   const uint64_t* Hk;
@@ -117,6 +119,12 @@ struct EmitArgs {
   uint32_t* rsrc_wide; // source ids when they do not fit the folded bits
   int wide;
   const unsigned int* skip;  // scatter: nothing to do when *skip != 0 (nullable)
+  // append mode (small calls, no count pass): bucket b (top append_F key bits)
+  // holds up to append_cap records from b append_cap on, taken in any order by
+  // atomics on cursor[b], which counts on beyond append_cap; wide ids
+  uint32_t* cursor;
+  int append_F;
+  uint32_t append_cap;
 };
 
 template <bool F32>
@@ -183,9 +191,12 @@ __attribute__((amdgpu_waves_per_eu(W == 1 && NBL <= 14 ? 8 : 4))) void k_emit(Em
   const int row = blockIdx.x;
   const uint32_t lrow = layout_row(blockIdx.x, gridDim.x);
   if (SCATTER && a.skip && *a.skip) return;
+  constexpr bool append = SCATTER && NBL == NBL_APPEND;
   if (SCATTER) {
-    const uint32_t* crow = a.counts + (size_t)lrow * NB;
-    for (int i = tid; i < NB; i += EMIT_THREADS) hist[i] = a.bin_base[i] + crow[i];
+    if (!append) {
+      const uint32_t* crow = a.counts + (size_t)lrow * NB;
+      for (int i = tid; i < NB; i += EMIT_THREADS) hist[i] = a.bin_base[i] + crow[i];
+    }
   } else {
     for (int i = tid; i < NB; i += EMIT_THREADS) hist[i] = 0u;
   }
@@ -196,6 +207,18 @@ __attribute__((amdgpu_waves_per_eu(W == 1 && NBL <= 14 ? 8 : 4))) void k_emit(Em
   auto deposit = [&](const Key<W>& raw, V val, uint32_t group, uint32_t index) {
     if (a.max_len > 0 && key_length<W>(raw) > a.max_len) return;
     Key<W> mk = mix_key<W>(raw);
+    if constexpr (append) {
+      const int AF = a.append_F;
+      const uint32_t b = (uint32_t)(mk.w[0] >> (64 - AF));
+      const uint32_t at = atomicAdd(&a.cursor[b], 1u);
+      if (at < a.append_cap) {
+        const size_t pos = (size_t)b * a.append_cap + at;
+        mk.w[0] &= ~0ull >> AF;
+        recs[pos] = make_rec<W, F32>(mk, val);
+        a.rsrc_wide[pos] = (group << GROUP_SHIFT) | index;
+      }
+      return;
+    }
     if (a.part) {
       const uint32_t pid = (uint32_t)(mk.w[0] >> (64 - a.pass_bits));
       const uint32_t pos = atomicAdd(&hist[pid], 1u);
@@ -603,12 +626,10 @@ __global__ __launch_bounds__(1024) void k_part_from_bins(const uint32_t* counts,
 // SC_COLS columns: thread (segment g, column b) loads rows
 // [SC_SEG g, SC_SEG g + SC_SEG) of column b all at once, the segment sums of
 // a column are combined in LDS, and each thread writes its rows' prefixes.
-// rows <= SC_NSEG * SC_SEG.
+// rows <= SC_NSEG * SC_SEG.  Totals above 32 bits set *overflow |= 2.
 constexpr int SC_COLS = 32, SC_SEG = 36, SC_NSEG = 32;
 constexpr int SC_ROWS_MAX = SC_SEG * SC_NSEG;
-__global__ __launch_bounds__(SC_COLS * SC_NSEG) void k_scan_cols(uint32_t* counts, int rows,
-                                                                 uint32_t* bin_total, Ctl* ctl,
-                                                                 int nbins) {
+DEV void scan_cols(uint32_t* counts, int rows, uint32_t* bin_total, Ctl* ctl, int nbins) {
   __shared__ unsigned long long ssum[SC_NSEG][SC_COLS];
   const int col = threadIdx.x % SC_COLS, seg = threadIdx.x / SC_COLS;
   const int b = blockIdx.x * SC_COLS + col;
@@ -623,186 +644,130 @@ __global__ __launch_bounds__(SC_COLS * SC_NSEG) void k_scan_cols(uint32_t* count
   for (int q = 0; q < SC_SEG; q++) s += c[q];
   ssum[seg][col] = s;
   __syncthreads();
+  const int last = (rows - 1) / SC_SEG;  // last segment that holds rows
   unsigned long long run = 0;
-  for (int g = 0; g < seg; g++) run += ssum[g][col];
+  if (seg <= last)
+    for (int g = 0; g < seg; g++) run += ssum[g][col];
 #pragma unroll
   for (int q = 0; q < SC_SEG; q++) {
     if (on && r0 + q < rows) counts[(size_t)(r0 + q) * nbins + b] = (uint32_t)run;
     run += c[q];
   }
-  if (on && seg == SC_NSEG - 1) {  // the last segment's running sum is the column total
+  if (on && seg == last) {  // the last segment's running sum is the column total
     if (run > 0xFFFFFFFFull) atomicOr(&ctl->overflow, 2u);
-    bin_total[b] = (uint32_t)run;
+    st_agent(&bin_total[b], (uint32_t)run);
   }
 }
-
-// Both scans of a count pass over 2^10 bins with at most SMALL_SCAN_ROWS
-// emission rows, in block 0: thread t turns column t of the count matrix
-// into row prefixes (as k_scan_cols), then the block scans the 1024 bin
-// totals into bin bases and takes the largest totals over aligned groups of
-// 1, 2, 4, 8, 16 bins (as k_scan_bins).  All blocks of the grid clear a share
-// of `zero`.  Such calls hold at most 2^18 records, so no total overflows 32
-// bits.
-constexpr int SMALL_SCAN_ROWS = 32;
-__global__ __launch_bounds__(1024) void k_scan_small(uint32_t* counts, int rows,
-                                                     uint32_t* bin_base, Ctl* ctl, uint32_t* zero,
-                                                     uint32_t nzero) {
-  constexpr int NB = 1 << NBINS_LOG_SMALL;
-  static_assert(NB == 1024, "one thread per bin");
-  __shared__ uint32_t scan_tmp[1024 / 64 + 1];
-  __shared__ uint32_t tot[NB];
-  __shared__ unsigned int gmax[5];
-  const int t = threadIdx.x;
-  // every block clears its share of `zero`; block 0 also scans
-  {
-    const uint32_t nv = nzero / 4, per = (nv + gridDim.x - 1) / gridDim.x;
-    const uint32_t z0 = blockIdx.x * per, z1 = min(nv, z0 + per);
-    for (uint32_t i = z0 + t; i < z1; i += 1024)
-      reinterpret_cast<uint4*>(zero)[i] = make_uint4(0u, 0u, 0u, 0u);
-  }
-  if (blockIdx.x != 0) return;
-  if (t < 5) gmax[t] = 0u;
-  uint32_t c[SMALL_SCAN_ROWS];
-#pragma unroll
-  for (int r = 0; r < SMALL_SCAN_ROWS; r++) c[r] = r < rows ? counts[(size_t)r * NB + t] : 0u;
-  uint32_t run = 0;
-#pragma unroll
-  for (int r = 0; r < SMALL_SCAN_ROWS; r++) {
-    if (r < rows) counts[(size_t)r * NB + t] = run;
-    run += c[r];
-  }
-  tot[t] = run;
-  uint32_t total;
-  const uint32_t pre = block_exclusive_scan(run, scan_tmp, &total);  // barriers: tot, gmax set
-  bin_base[t] = pre;
-  if (t == 0) bin_base[NB] = total;
-#pragma unroll
-  for (int lg = 0; lg < 5; lg++) {
-    const int g = 1 << lg;
-    if ((t & (g - 1)) == 0) {
-      uint32_t m = 0;
-      for (int q = 0; q < g; q++) m += tot[t + q];
-      atomicMax(&gmax[lg], m);
-    }
-  }
-  __syncthreads();
-  if (t == 0) {
-    ctl->pe_total = total;
-    ctl->ndefer = 0u;
-    for (int lg = 0; lg < 5; lg++) ctl->maxg[lg] = gmax[lg];
-  }
+__global__ __launch_bounds__(SC_COLS * SC_NSEG) void k_scan_cols(uint32_t* counts, int rows,
+                                                                 uint32_t* bin_total, Ctl* ctl,
+                                                                 int nbins) {
+  scan_cols(counts, rows, bin_total, ctl, nbins);
 }
 
-// Exclusive scan of the bin totals (one block of 1024 threads, of which the
-// first scan_bins_threads<NBL>() hold the bins: thread t owns the BPT >= 16
-// consecutive bins from t BPT, read and written as 16-byte vectors) and the
-// largest total over aligned groups of 1, 2, 4, 8, 16 bins.  Also clears
-// `zero` (nzero words) when given, with every thread: the level-0 |c|^2
-// histogram of the merges that follow this count pass.
+// Both scans of a count pass: every block turns its columns into row prefixes
+// (scan_cols), then the last block scans the 2^NBL bin totals into bin bases
+// and takes the largest totals over aligned groups of 1, 2, 4, 8, 16 bins:
+// thread t owns the BPT consecutive bins from t BPT; groups wider than BPT are
+// combined in LDS.
 template <int NBL>
-constexpr int scan_bins_threads() { return (1 << NBL) / 16 < 1024 ? (1 << NBL) / 16 : 1024; }
-template <int NBL>
-__global__ __launch_bounds__(1024) void k_scan_bins(const uint32_t* bin_total, uint32_t* bin_base,
-                                                    Ctl* ctl, uint32_t* zero, uint32_t nzero,
-                                                    unsigned long long spec_cap = 0ull,
-                                                    unsigned int merge_cap = 0u) {
+__global__ __launch_bounds__(1024) void k_scan(uint32_t* counts, int rows, uint32_t* bin_total,
+                                               uint32_t* bin_base, Ctl* ctl,
+                                               unsigned long long spec_cap,
+                                               unsigned int merge_cap) {
+  static_assert(SC_COLS * SC_NSEG == 1024, "one block size for both parts");
   constexpr int NB = 1 << NBL;
-  constexpr int TH = scan_bins_threads<NBL>();
-  constexpr int NWV = TH / 64;
-  constexpr int BPT = NB / TH;
-  static_assert(BPT >= 16 && BPT * TH == NB && BPT % 4 == 0 && NWV >= 1 && NWV <= 16,
-                "k_scan_bins covers the bins with TH threads");
-  __shared__ unsigned long long tmp[1024 / 64 + 1];
-  __shared__ unsigned int gmax[16][5];
+  constexpr int BPT = NB / 1024;
+  static_assert(BPT * 1024 == NB, "every thread owns whole bins");
+  scan_cols(counts, rows, bin_total, ctl, NB);
+  if (!last_block(&ctl->ticket[0])) return;
+  __shared__ unsigned long long tmp[17];
+  __shared__ unsigned int gmax[5];
+  __shared__ uint32_t gsum[1024];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  // every thread of the block clears (nzero is a multiple of 4 and `zero`
-  // 16-byte aligned: histogram replicas); the first TH threads, whole waves,
-  // hold the bins, the others take part with empty bins
-  for (uint32_t i = t; i < nzero / 4; i += blockDim.x)
-    reinterpret_cast<uint4*>(zero)[i] = make_uint4(0u, 0u, 0u, 0u);
-  const bool act = t < TH;
+  if (t < 5) gmax[t] = 0u;
   uint32_t v[BPT];
-  const uint4* src = reinterpret_cast<const uint4*>(bin_total) + (size_t)t * (BPT / 4);
+  if constexpr (BPT >= 4) {
+    const uint4* src = reinterpret_cast<const uint4*>(bin_total) + (size_t)t * (BPT / 4);
 #pragma unroll
-  for (int q = 0; q < BPT / 4; q++) {
-    const uint4 c = act ? src[q] : make_uint4(0u, 0u, 0u, 0u);
-    v[4 * q] = c.x;
-    v[4 * q + 1] = c.y;
-    v[4 * q + 2] = c.z;
-    v[4 * q + 3] = c.w;
+    for (int q = 0; q < BPT / 4; q++) {
+      const uint4 c = src[q];
+      v[4 * q] = c.x;
+      v[4 * q + 1] = c.y;
+      v[4 * q + 2] = c.z;
+      v[4 * q + 3] = c.w;
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < BPT; q++) v[q] = bin_total[t * BPT + q];
   }
   unsigned long long s = 0;
 #pragma unroll
   for (int k = 0; k < BPT; k++) s += v[k];
-  unsigned int lm[5];
-#pragma unroll
-  for (int lg = 0; lg < 5; lg++) {
-    const int g = 1 << lg;
-    unsigned int best = 0;
-#pragma unroll
-    for (int k = 0; k < BPT; k += g) {
-      unsigned long long acc = 0;
-#pragma unroll
-      for (int q = 0; q < g; q++) acc += v[k + q];
-      const unsigned int a = acc > 0xFFFFFFFFull ? 0xFFFFFFFFu : (unsigned int)acc;
-      best = a > best ? a : best;
-    }
-    // wave maximum, then one entry per wave
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-      const unsigned int o = __shfl_xor(best, d, 64);
-      best = o > best ? o : best;
-    }
-    lm[lg] = best;
-  }
-  if (lane == 0)
-#pragma unroll
-    for (int lg = 0; lg < 5; lg++) gmax[wv][lg] = lm[lg];
-  // block exclusive scan (u64)
+  gsum[t] = s > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)s;
+  // block exclusive scan (u64); its barriers also publish gsum and gmax
   unsigned long long x = s;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
-    unsigned long long y = __shfl_up(x, d, 64);
+    const unsigned long long y = __shfl_up(x, d, 64);
     if (lane >= d) x += y;
   }
   if (lane == 63) tmp[wv] = x;
   __syncthreads();
-  unsigned long long w = lane < NWV ? tmp[lane] : 0ull;
+  unsigned long long w = lane < 16 ? tmp[lane] : 0ull;
 #pragma unroll
   for (int d = 1; d < 16; d <<= 1) {
-    unsigned long long y = __shfl_up(w, d, 64);
+    const unsigned long long y = __shfl_up(w, d, 64);
     if (lane >= d) w += y;
   }
   const unsigned long long before = wv > 0 ? __shfl(w, wv - 1, 64) : 0ull;
-  const unsigned long long total = __shfl(w, NWV - 1, 64);
+  const unsigned long long total = __shfl(w, 15, 64);
   unsigned long long pre = before + x - s;
-  uint4* dst = reinterpret_cast<uint4*>(bin_base) + (size_t)t * (BPT / 4);
+  uint32_t o[BPT];
 #pragma unroll
-  for (int q = 0; q < (act ? BPT / 4 : 0); q++) {
-    uint4 o;
-    o.x = (uint32_t)pre;
-    pre += v[4 * q];
-    o.y = (uint32_t)pre;
-    pre += v[4 * q + 1];
-    o.z = (uint32_t)pre;
-    pre += v[4 * q + 2];
-    o.w = (uint32_t)pre;
-    pre += v[4 * q + 3];
-    dst[q] = o;
+  for (int q = 0; q < BPT; q++) {
+    o[q] = (uint32_t)pre;
+    pre += v[q];
   }
+  if constexpr (BPT >= 4) {
+    uint4* dst = reinterpret_cast<uint4*>(bin_base) + (size_t)t * (BPT / 4);
+#pragma unroll
+    for (int q = 0; q < BPT / 4; q++)
+      dst[q] = make_uint4(o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]);
+  } else {
+#pragma unroll
+    for (int q = 0; q < BPT; q++) bin_base[t * BPT + q] = o[q];
+  }
+#pragma unroll
+  for (int lg = 0; lg < 5; lg++) {
+    const int g = 1 << lg;
+    unsigned int best = 0;
+    if (g <= BPT) {
+#pragma unroll
+      for (int k = 0; k < BPT; k += g) {
+        unsigned long long acc = 0;
+#pragma unroll
+        for (int q = 0; q < (g <= BPT ? g : 1); q++) acc += v[k + q];
+        best = max(best, acc > 0xFFFFFFFFull ? 0xFFFFFFFFu : (unsigned int)acc);
+      }
+    } else if ((t & (g / BPT - 1)) == 0) {
+      unsigned long long acc = 0;
+      for (int q = 0; q < g / BPT; q++) acc += gsum[t + q];
+      best = acc > 0xFFFFFFFFull ? 0xFFFFFFFFu : (unsigned int)acc;
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) best = max(best, (unsigned int)__shfl_xor((int)best, d, 64));
+    if (lane == 0) atomicMax(&gmax[lg], best);
+  }
+  __syncthreads();
   if (t == 0) {
     bin_base[NB] = (uint32_t)total;
     ctl->pe_total = total;
     ctl->ndefer = 0u;
     if (total > 0xFFFFFFFFull) ctl->overflow |= 2u;
-    for (int lg = 0; lg < 5; lg++) {
-      unsigned int m = 0;
-      for (int q = 0; q < NWV; q++) m = gmax[q][lg] > m ? gmax[q][lg] : m;
-      ctl->maxg[lg] = m;
-    }
+    for (int lg = 0; lg < 5; lg++) ctl->maxg[lg] = gmax[lg];
     // a scatter already launched for a single pass laid out for spec_cap
     // records stands down unless the records fit and every bin fits a bucket
-    if (spec_cap) ctl->spec_fail = (total > spec_cap || ctl->maxg[0] > merge_cap) ? 1u : 0u;
+    if (spec_cap) ctl->spec_fail = (total > spec_cap || gmax[0] > merge_cap) ? 1u : 0u;
   }
 }
 
@@ -811,8 +776,8 @@ __global__ __launch_bounds__(1024) void k_scan_bins(const uint32_t* bin_total, u
 // term in canonical order (ascending mixed key, distinct strings) holds the
 // strings of hash bucket b (the top F bits of the mixed key) as one
 // contiguous run, so the merge can read each bucket straight from the terms:
-// k_term_bounds finds the runs, k_check_sorted confirms the order of terms
-// the engine did not write itself.
+// k_term_stream and k_term_bounds find the runs, the former also confirms the
+// order of terms the engine did not write itself.
 // ---------------------------------------------------------------------------
 struct TermView {
   int n_terms;
@@ -838,16 +803,41 @@ DEV Key<W> load_raw(const uint64_t* x, const uint64_t* z, int64_t cap, int64_t i
   return raw;
 }
 
-// *flag |= 1 when the mixed keys of the n strings do not strictly ascend.
+// Bucket bounds of terms by one pass over them (each thread one string):
+// string i starts every bucket after string i - 1's up to its own.  Sets
+// *flag when mixed keys do not strictly ascend (bounds are then not used).
+// Used for terms the engine did not write, which have to be read to check
+// their order in any case, and for short ones, whose binary search below is a
+// chain of dependent loads (9 us for 16384 strings, and 2 us for the check as
+// a kernel of its own; 3.9 us here).
 template <int W>
-__global__ __launch_bounds__(256) void k_check_sorted(const uint64_t* x, const uint64_t* z,
-                                                      int64_t cap, int64_t n, unsigned int* flag) {
+__global__ __launch_bounds__(256) void k_term_stream(TermView v, uint32_t mask, uint32_t* bounds,
+                                                     unsigned int* flag) {
+  const uint32_t nb = 1u << v.F;
+  int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
   bool bad = false;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x + 1; i < n;
-       i += (int64_t)gridDim.x * 256) {
-    const Key<W> a = mix_key<W>(load_raw<W>(x, z, cap, i - 1));
-    const Key<W> b = mix_key<W>(load_raw<W>(x, z, cap, i));
-    bad = bad || key_cmp<W>(a, b) >= 0;
+#pragma unroll
+  for (int t = 0; t < MAX_TERMS; t++) {
+    if (t >= v.n_terms || !((mask >> t) & 1u)) continue;
+    const int64_t n = v.tn[t];
+    if (id >= 0 && id <= n) {
+      uint32_t* bt = bounds + (size_t)t * (nb + 1);
+      int64_t from = 0, to = nb;  // bounds [from, to] are i
+      if (id > 0) {
+        const Key<W> p = mix_key<W>(load_raw<W>(v.tx[t], v.tz[t], v.tcap[t], id - 1));
+        from = (v.F ? (int64_t)(p.w[0] >> (64 - v.F)) : 0) + 1;
+        if (id < n) {
+          const Key<W> m = mix_key<W>(load_raw<W>(v.tx[t], v.tz[t], v.tcap[t], id));
+          bad = bad || key_cmp<W>(p, m) >= 0;
+          to = v.F ? (int64_t)(m.w[0] >> (64 - v.F)) : 0;
+        }
+      } else if (n > 0) {
+        const Key<W> m = mix_key<W>(load_raw<W>(v.tx[t], v.tz[t], v.tcap[t], 0));
+        to = v.F ? (int64_t)(m.w[0] >> (64 - v.F)) : 0;
+      }
+      for (int64_t b = from; b <= to; b++) bt[b] = (uint32_t)id;
+    }
+    id -= n + 1;
   }
   if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(flag, 1u);
 }
@@ -855,11 +845,12 @@ __global__ __launch_bounds__(256) void k_check_sorted(const uint64_t* x, const u
 // bounds[t][b], b = 0 .. 2^F: the first string of term t whose bucket is at
 // least b (binary search over the canonical order; one thread per entry).
 template <int W>
-__global__ __launch_bounds__(256) void k_term_bounds(TermView v, uint32_t* bounds) {
+__global__ __launch_bounds__(256) void k_term_bounds(TermView v, uint32_t mask, uint32_t* bounds) {
   const int64_t nb1 = ((int64_t)1 << v.F) + 1;
   const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (id >= nb1 * v.n_terms) return;
   const int t = (int)(id / nb1);
+  if (!((mask >> t) & 1u)) return;
   const uint64_t b = (uint64_t)(id - (int64_t)t * nb1);
   int64_t lo = 0, hi = v.tn[t];
   if (v.F == 0) {
@@ -877,6 +868,8 @@ __global__ __launch_bounds__(256) void k_term_bounds(TermView v, uint32_t* bound
 
 struct MergeArgs {
   const uint32_t* bin_base;
+  const uint32_t* bin_count;  // append mode: records of bucket j (from j append_cap on)
+  uint32_t append_cap;
   int nbins_log;  // hash bins of the call: 2^nbins_log per pass
   int g_log;
   int digit_shift;
@@ -1061,7 +1054,13 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
         b1 += s1;
       }
     }
-    if (a.ctl->unsorted) b1 = b0;  // the call is redone by emission
+    if (a.ctl->unsorted) b0 = b1 = 0u;  // the call is redone by emission
+  } else if (MODE == MERGE_GRID && a.bin_count) {
+    const uint32_t cnt = a.bin_count[j];
+    b0 = j * a.append_cap;
+    // records beyond the bucket's room were not written: the call is redone
+    b1 = b0 + (cnt > a.append_cap ? (uint32_t)CAP + 1u : cnt);
+    if (tid == 0) atomicAdd(&a.ctl->pe_total, (unsigned long long)cnt);
   } else {
     b0 = a.bin_base[j << a.g_log];
     b1 = a.bin_base[(j + 1) << a.g_log];
@@ -1154,7 +1153,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
     s_al[tid] = a.alpha[tid];
   }
   const int G = 1 << a.g_log;
-  if (!DIRECT && tid <= G) sbb[tid] = a.bin_base[(j << a.g_log) + tid];
+  if (!DIRECT && tid <= G && G > 1) sbb[tid] = a.bin_base[(j << a.g_log) + tid];
   if (tid == 0) {
     s_collide = 0;
     s_pk = 0u;
@@ -1549,53 +1548,37 @@ __global__ __launch_bounds__(256) void k_trace(const uint64_t* x, const uint64_t
   }
 }
 
-// Lanczos: double-double partial of sum |c|^2 over one bucket of the merged,
-// untruncated O'_n (fixed reduction order).
-__global__ __launch_bounds__(256) void k_norm_bucket(const uint32_t* b_ubase,
-                                                     const uint32_t* b_slots, const double2* uc,
-                                                     double2* part) {
-  __shared__ double rh[4], rl[4];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const uint32_t b = blockIdx.x;
-  const uint32_t ub = b_ubase[b], ns = b_slots[b];
-  dd s = dd_zero();
-  for (uint32_t i = tid; i < ns; i += 256) s = dd_add(s, weight2(uc[ub + i]));
-  for (int d = 32; d >= 1; d >>= 1) {
-    dd o;
-    o.hi = __shfl_down(s.hi, d, 64);
-    o.lo = __shfl_down(s.lo, d, 64);
-    if (lane < d) s = dd_add(s, o);
+// The buckets first, first + step, ... of one wave, with the next one's start
+// and length loaded while the current one is worked on.
+struct WaveBuckets {
+  const uint32_t *start, *len;
+  uint32_t b, step, nbk, ub, ns;
+  DEV WaveBuckets(const uint32_t* s, const uint32_t* l, uint32_t first, uint32_t st, uint32_t n)
+      : start(s), len(l), b(first), step(st), nbk(n), ub(0), ns(0) {
+    if (b < nbk) load();
   }
-  if (lane == 0) {
-    rh[wv] = s.hi;
-    rl[wv] = s.lo;
+  DEV void load() {
+    ub = start[b];
+    ns = len[b];
   }
-  __syncthreads();
-  if (tid == 0) {
-    dd t = {rh[0], rl[0]};
-    for (int w = 1; w < 4; w++) t = dd_add(t, dd{rh[w], rl[w]});
-    part[b] = make_double2(t.hi, t.lo);
+  DEV bool next(uint32_t& cb, uint32_t& cu, uint32_t& cn) {
+    if (b >= nbk) return false;
+    cb = b;
+    cu = ub;
+    cn = ns;
+    b += step;
+    if (b < nbk) load();
+    return true;
   }
-}
+};
 
-// k_norm_bucket for translation-symmetric operators: each merged unique
+// Lanczos: sum |c|^2 of the merged, untruncated O'_n in double-double, in a
+// fixed order: one wave per bucket, block partials (at most NORM_BLOCKS), and
+// the last block adds them into ctl->norm_hi, norm_lo.  TS: each merged string
 // weighted by its stabilizer count (the norm of sum_k T_k(A) over N).
-template <int W>
-__global__ __launch_bounds__(256) void k_norm_bucket_ts(const uint32_t* b_ubase,
-                                                        const uint32_t* b_slots, const void* uk_,
-                                                        const double2* uc, int N, double2* part) {
-  __shared__ double rh[4], rl[4];
+constexpr int NORM_BLOCKS = 1024;
+DEV dd dd_block_sum(dd s, double* rh, double* rl) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const uint32_t b = blockIdx.x;
-  const uint32_t ub = b_ubase[b], ns = b_slots[b];
-  const Key<W>* uk = reinterpret_cast<const Key<W>*>(uk_) + ub;
-  dd s = dd_zero();
-  for (uint32_t i = tid; i < ns; i += 256) {
-    const Key<W> raw = unmix_key<W>(uk[i]);
-    const int st = ts_stabilizers<W>(raw.w, raw.w + W, N);
-    const double w2 = weight2(uc[ub + i]);
-    for (int r = 0; r < st; r++) s = dd_add(s, w2);
-  }
   for (int d = 32; d >= 1; d >>= 1) {
     dd o;
     o.hi = __shfl_down(s.hi, d, 64);
@@ -1607,10 +1590,47 @@ __global__ __launch_bounds__(256) void k_norm_bucket_ts(const uint32_t* b_ubase,
     rl[wv] = s.lo;
   }
   __syncthreads();
+  dd t = {rh[0], rl[0]};
+  for (int w = 1; w < 4; w++) t = dd_add(t, dd{rh[w], rl[w]});
+  return t;
+}
+template <int W, bool TS>
+__global__ __launch_bounds__(256) void k_norm(const uint32_t* b_ubase, const uint32_t* b_slots,
+                                              const void* uk_, const double2* uc, int N, TsTop top,
+                                              uint32_t nbk, double2* part, Ctl* ctl) {
+  __shared__ double rh[4], rl[4];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const Key<W>* uk = reinterpret_cast<const Key<W>*>(uk_);
+  dd s = dd_zero();
+  WaveBuckets wb(b_ubase, b_slots, blockIdx.x * 4 + wv, gridDim.x * 4, nbk);
+  for (uint32_t b, ub, ns; wb.next(b, ub, ns);) {
+    for (uint32_t i0 = lane; i0 < ns; i0 += 256) {
+      double w2[4];
+#pragma unroll
+      for (int q = 0; q < 4; q++) w2[q] = i0 + 64 * q < ns ? weight2(uc[ub + i0 + 64 * q]) : 0.0;
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        int st = 1;
+        if constexpr (TS) {
+          if (i0 + 64 * q < ns) {
+            const Key<W> raw = unmix_key<W>(uk[ub + i0 + 64 * q]);
+            st = ts_stabilizers<W>(raw.w, raw.w + W, N, top);
+          }
+        }
+        for (int r = 0; r < st; r++) s = dd_add(s, w2[q]);
+      }
+    }
+  }
+  const dd t = dd_block_sum(s, rh, rl);
+  if (tid == 0) st_agent(&part[blockIdx.x], make_double2(t.hi, t.lo));
+  if (!last_block(&ctl->ticket[1])) return;
+  dd u = dd_zero();
+  for (uint32_t i = tid; i < gridDim.x; i += 256) u = dd_add(u, dd{part[i].x, part[i].y});
+  __syncthreads();  // rh, rl are reused
+  const dd v = dd_block_sum(u, rh, rl);
   if (tid == 0) {
-    dd t = {rh[0], rl[0]};
-    for (int w = 1; w < 4; w++) t = dd_add(t, dd{rh[w], rl[w]});
-    part[b] = make_double2(t.hi, t.lo);
+    ctl->norm_hi = v.hi;
+    ctl->norm_lo = v.lo;
   }
 }
 
@@ -1689,6 +1709,7 @@ struct ScaleArgs {
   const uint32_t* b_slots;
   uint32_t* b_surv;
   uint32_t* b_keep;
+  uint32_t nbk;
   void* uk;
   double2* uc;
   const double* norm2;  // ||O'_n||^2, written by the norm reduction
@@ -1703,60 +1724,68 @@ struct ScaleArgs {
   Ctl* ctl;
 };
 
+// One wave per bucket, SCALE_BLOCKS blocks at most, so that the 4096-bin
+// histogram in LDS is cleared and added to memory once per block and not once
+// per bucket: over 131072 buckets of 560 two-word strings 1.06 -> 0.50 ms (4.7
+// TB/s of values read and written).
+constexpr int SCALE_BLOCKS = 1024;
 template <int W>
-__global__ __launch_bounds__(256) void k_scale_filter(ScaleArgs a) {
+__global__ __launch_bounds__(512) void k_scale_filter(ScaleArgs a) {
   __shared__ uint32_t h0[SEL0_BINS];
-  __shared__ uint32_t rs[4], rk[4];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const uint32_t b = blockIdx.x;
-  for (int i = tid; i < SEL0_BINS; i += 256) h0[i] = 0u;
+  for (int i = tid; i < SEL0_BINS; i += 512) h0[i] = 0u;
   __syncthreads();
-  const uint32_t ub = a.b_ubase[b], ns = a.b_slots[b];
-  const Key<W>* uk = reinterpret_cast<const Key<W>*>(a.uk) + ub;
-  double2* uc = a.uc + ub;
   const Key<W>* keep = reinterpret_cast<const Key<W>*>(a.keep_mk);
   // b_n = sqrt(||O'_n||^2), correctly rounded as on the host, which reads the
   // same norm with the output size and reports the breakdown
   const double bn = sqrt(*a.norm2);
   const bool brk = !(bn > a.floor_b);
-  uint32_t surv = 0, kc = 0;
-  for (uint32_t i = tid; i < ns; i += 256) {
-    double2 v = uc[i];
-    v = make_double2(v.x / bn, v.y / bn);
-    // FP32 storage: a string whose stored value would be an exact zero is
-    // dropped; every other decision (cutoff, top-M) is taken on the FP64
-    // quotient, which the output write rounds to FP32
-    bool ok = !brk && (a.round32 ? !is_zero(make_double2(round_to_f32(v.x), round_to_f32(v.y)))
-                                 : !is_zero(v));
-    const Key<W> mk = uk[i];
-    if (ok && a.max_len > 0 && key_length<W>(unmix_key<W>(mk)) > a.max_len) ok = false;
-    if (ok && a.use_eps && !(weight2(v) >= a.eps2)) ok = false;
-    if (ok) {
-      surv++;
-      bool isk = a.n_keep ? keep_lookup<W>(keep, a.n_keep, mk) : false;
-      if (isk) kc++;
-      else atomicAdd(&h0[(uint32_t)((uint64_t)__double_as_longlong(weight2(v)) >> SEL0_SHIFT)], 1u);
-    } else {
-      v = make_double2(0.0, 0.0);
+  WaveBuckets wb(a.b_ubase, a.b_slots, blockIdx.x * 8 + wv, gridDim.x * 8, a.nbk);
+  for (uint32_t b, ub, ns; wb.next(b, ub, ns);) {
+    const Key<W>* uk = reinterpret_cast<const Key<W>*>(a.uk) + ub;
+    double2* uc = a.uc + ub;
+    uint32_t surv = 0, kc = 0;
+    for (uint32_t i0 = lane; i0 < ns; i0 += 256) {
+      double2 vv[4];
+#pragma unroll
+      for (int q = 0; q < 4; q++)
+        if (i0 + 64 * q < ns) vv[q] = uc[i0 + 64 * q];
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        const uint32_t i = i0 + 64 * q;
+        if (i >= ns) break;
+        double2 v = make_double2(vv[q].x / bn, vv[q].y / bn);
+        // FP32 storage: a string whose stored value would be an exact zero is
+        // dropped; every other decision (cutoff, top-M) is taken on the FP64
+        // quotient, which the output write rounds to FP32
+        bool ok = !brk && (a.round32 ? !is_zero(make_double2(round_to_f32(v.x), round_to_f32(v.y)))
+                                     : !is_zero(v));
+        if (ok && a.max_len > 0 && key_length<W>(unmix_key<W>(uk[i])) > a.max_len) ok = false;
+        if (ok && a.use_eps && !(weight2(v) >= a.eps2)) ok = false;
+        if (ok) {
+          surv++;
+          bool isk = a.n_keep ? keep_lookup<W>(keep, a.n_keep, uk[i]) : false;
+          if (isk) kc++;
+          else atomicAdd(&h0[(uint32_t)((uint64_t)__double_as_longlong(weight2(v)) >> SEL0_SHIFT)], 1u);
+        } else {
+          v = make_double2(0.0, 0.0);
+        }
+        uc[i] = v;
+      }
     }
-    uc[i] = v;
-  }
-  for (int d = 32; d >= 1; d >>= 1) {
-    surv += __shfl_down(surv, d, 64);
-    kc += __shfl_down(kc, d, 64);
-  }
-  if (lane == 0) {
-    rs[wv] = surv;
-    rk[wv] = kc;
+    for (int d = 32; d >= 1; d >>= 1) {
+      surv += __shfl_down(surv, d, 64);
+      kc += __shfl_down(kc, d, 64);
+    }
+    if (lane == 0) {
+      a.b_surv[b] = surv;
+      a.b_keep[b] = kc;
+    }
   }
   __syncthreads();
-  uint32_t* hrep = a.hist0 + (size_t)(b % HREP) * SEL0_BINS;
-  for (int i = tid; i < SEL0_BINS; i += 256)
+  uint32_t* hrep = a.hist0 + (size_t)(blockIdx.x % HREP) * SEL0_BINS;
+  for (int i = tid; i < SEL0_BINS; i += 512)
     if (h0[i]) atomicAdd(&hrep[i], h0[i]);
-  if (tid == 0) {
-    a.b_surv[b] = rs[0] + rs[1] + rs[2] + rs[3];
-    a.b_keep[b] = rk[0] + rk[1] + rk[2] + rk[3];
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2163,26 +2192,71 @@ __global__ __launch_bounds__(256) void k_write(WriteArgs a) {
 // ---------------------------------------------------------------------------
 // Small helpers
 // ---------------------------------------------------------------------------
-// H for the commutator emission (one block of 1024 threads, n <= 2047):
-// packed raw words [n][2W] in ascending order of lowest site, the index of
-// each entry in the caller's H, hstart[s] = first entry with lowest site >= s
-// (s = 0 .. 64W + 1; the empty string sorts as site 64W) and the largest
-// highest-minus-lowest site.  The order among entries of one lowest site is
-// not fixed: every entry carries its own index.
+// First kernel of an engine call, PREP_BLOCKS blocks of 1024 threads.  The
+// blocks after the first clear the level-0 |c|^2 histogram `hist0`; the first
+// clears the control block, takes the order keys of the keep set (n_keep <=
+// KEEP_PREP; a larger one is left to k_mix_keys) and, for a commutator (n > 0,
+// n <= 2047), lays out H: packed raw words [n][2W] in ascending order of lowest
+// site, the index of each entry in the caller's H, hstart[s] = first entry with
+// lowest site >= s (s = 0 .. 64W + 1; the empty string sorts as site 64W) and
+// the largest highest-minus-lowest site.  The order among entries of one lowest
+// site is not fixed: every entry carries its own index.
+constexpr int PREP_BLOCKS = 1 + HREP, KEEP_PREP = 1024;
+struct PrepArgs {
+  const uint64_t* x;
+  const uint64_t* z;
+  int64_t cap;
+  int n;
+  uint64_t* packed;
+  uint32_t* hidx;
+  uint32_t* hstart;
+  int* hspan;
+  const uint64_t* kx;
+  const uint64_t* kz;
+  int64_t kcap;
+  int n_keep;
+  void* keep_mk;
+  uint32_t* hist0;
+  uint32_t* cursor;  // append mode: n_cursor <= 1024 bucket cursors to clear
+  int n_cursor;
+  Ctl* ctl;
+};
 template <int W>
-__global__ __launch_bounds__(1024) void k_prep_h(const uint64_t* x, const uint64_t* z, int64_t cap,
-                                                 int n, uint64_t* packed, uint32_t* hidx,
-                                                 uint32_t* hstart, int* hspan, uint32_t* zero,
-                                                 uint32_t nzero) {
+__global__ __launch_bounds__(1024) void k_prep(PrepArgs a) {
   constexpr int SITES = 64 * W;
+  static_assert(SEL0_BINS == 4 * 1024, "one replica per block, 16 bytes per thread");
+  if (blockIdx.x > 0) {
+    uint4* z = reinterpret_cast<uint4*>(a.hist0 + (size_t)(blockIdx.x - 1) * SEL0_BINS);
+    z[threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
+    return;
+  }
+  const uint64_t* x = a.x;
+  const uint64_t* z = a.z;
+  const int64_t cap = a.cap;
+  const int n = a.n;
   __shared__ uint32_t cnt[SITES + 2];
   __shared__ int span;
   const int t = threadIdx.x;
-  // also clears `zero` (nzero words: the call's control block)
-  for (uint32_t q = t; q < nzero; q += 1024) zero[q] = 0u;
+  __shared__ int bad;
+  for (uint32_t q = t; q < sizeof(Ctl) / 4; q += 1024) reinterpret_cast<uint32_t*>(a.ctl)[q] = 0u;
   for (int q = t; q < SITES + 2; q += 1024) cnt[q] = 0u;
-  if (t == 0) span = 0;
+  if (t < a.n_cursor) a.cursor[t] = 0u;
+  if (t == 0) {
+    span = 0;
+    bad = 0;
+  }
   __syncthreads();
+  if (a.n_keep > 0) {
+    Key<W>* mk = reinterpret_cast<Key<W>*>(a.keep_mk);
+    if (t < a.n_keep) {
+      const Key<W> m = mix_key<W>(load_raw<W>(a.kx, a.kz, a.kcap, t));
+      mk[t] = m;
+      if (t > 0 && key_cmp<W>(mix_key<W>(load_raw<W>(a.kx, a.kz, a.kcap, t - 1)), m) >= 0) bad = 1;
+    }
+    __syncthreads();
+    if (t == 0 && bad) a.ctl->bad_keep = 1u;
+  }
+  if (n == 0) return;
   int lo[2], rk[2];
   for (int k = 0; k < 2; k++) {
     const int i = t + k * 1024;
@@ -2219,14 +2293,14 @@ __global__ __launch_bounds__(1024) void k_prep_h(const uint64_t* x, const uint64
       const int p = (int)cnt[lo[k]] + rk[k];
 #pragma unroll
       for (int w = 0; w < W; w++) {
-        packed[(size_t)p * 2 * W + w] = x[(size_t)w * cap + i];
-        packed[(size_t)p * 2 * W + W + w] = z[(size_t)w * cap + i];
+        a.packed[(size_t)p * 2 * W + w] = x[(size_t)w * cap + i];
+        a.packed[(size_t)p * 2 * W + W + w] = z[(size_t)w * cap + i];
       }
-      hidx[p] = (uint32_t)i;
+      a.hidx[p] = (uint32_t)i;
     }
   }
-  for (int q = t; q < SITES + 2; q += 1024) hstart[q] = cnt[q];
-  if (t == 0) *hspan = span;
+  for (int q = t; q < SITES + 2; q += 1024) a.hstart[q] = cnt[q];
+  if (t == 0) *a.hspan = span;
 }
 
 // Mixed keys of a canonical operator; flags a violation of ascending order.
@@ -2368,7 +2442,7 @@ __global__ __launch_bounds__(256) void k_ts_expand(const uint64_t* x, const uint
 template <int W, bool F32>
 __global__ __launch_bounds__(256) void k_norm_part_ts(const uint64_t* x, const uint64_t* z,
                                                       int64_t cap, const void* coef, int64_t n,
-                                                      int N, double2* part) {
+                                                      int N, TsTop top, double2* part) {
   __shared__ double rh[4], rl[4];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   dd s = dd_zero();
@@ -2386,7 +2460,7 @@ __global__ __launch_bounds__(256) void k_norm_part_ts(const uint64_t* x, const u
       vx[w] = x[(size_t)w * cap + i];
       vz[w] = z[(size_t)w * cap + i];
     }
-    const int st = ts_stabilizers<W>(vx, vz, N);
+    const int st = ts_stabilizers<W>(vx, vz, N, top);
     const double w2 = weight2(v);
     for (int r = 0; r < st; r++) s = dd_add(s, w2);
   }

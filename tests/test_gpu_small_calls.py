@@ -84,3 +84,60 @@ def test_training_without_transposed_weights(pk, n, batch):
     assert hist[0] == hist[1]
     assert torch.equal(nets[0].params, nets[1].params)
     assert hist[0][-1] < hist[0][0]
+
+
+# appended buckets of 2^F (bound of 2^(10 + F) records): filled to their room of 1408 one-word or
+# 1344 two-word records, one above it, and above it but within the merge's 1984; every pair of
+# the product with a single string is one record, half of the key range is left empty
+@pytest.mark.parametrize("n,count", [(40, 1408), (40, 1409), (40, 1700), (100, 1344), (100, 1345)])
+def test_appended_bucket_at_its_room(pk, n, count):
+    print(f"append n={n} count={count}", flush=True)
+    pool = wl.random_local_strings(n, 4 * count, 12, seed=count)
+    one = wl.from_terms(n, [(1.0, [("X", 3)])])
+    # strings whose product with X_3 has a key in the lower half
+    x = pool.x.copy()
+    x[:, 0] ^= np.uint64(4)
+    moved = pk.order_keys(pk.PauliOp.from_raw(n, x, pool.z, pool.coef))[:, 0].cpu().numpy()
+    pick = np.flatnonzero(moved >= 0)[:count]
+    assert len(pick) == count
+    O = wl.HostOp(n, pool.x[pick], pool.z[pick], pool.coef[pick])
+    ws = pk.Workspace(256 << 20)
+    got = pk.multiply(raw(pk, one), raw(pk, O), ws=ws).to_host()
+    same(got, oracle.product(one, O), "product")
+    room = 1408 if n <= 64 else 1344
+    assert (pk.last_stats()["host_syncs"] == 1) == (count <= room)
+
+
+# term runs found by one pass over the terms: no bucket bits (n <= 1033), empty buckets at both
+# ends, terms of one string, and unsorted input (redone by emission)
+@pytest.mark.parametrize("na,nb,shuffle", [(1, 1, False), (1, 1033, False), (700, 334, False),
+                                           (40000, 3, False), (5, 600000, False),
+                                           (3000, 2000, True)])
+def test_add_streamed_bounds(pk, na, nb, shuffle):
+    print(f"add na={na} nb={nb} shuffle={shuffle}", flush=True)
+    A = wl.random_local_strings(50, na, 12, seed=1)
+    B = wl.random_local_strings(50, nb, 12, seed=2)
+    ws = pk.Workspace(256 << 20)
+    dev = [raw(pk, h) if shuffle else pk.PauliOp.from_host(h, ws=ws) for h in (A, B)]
+    got = pk.add(dev[0], 2.0 - 0.5j, dev[1], 0.25, ws=ws).to_host()
+    same(got, oracle.add(A, 2.0 - 0.5j, B, 0.25), "add")
+
+
+# groups of equal |c| around the 64 that one wave ranks, the 2048 that one block takes, and more
+# (the multi-level select); the cut falls inside the group and is settled by the keys
+@pytest.mark.parametrize("n", [24, 100])
+@pytest.mark.parametrize("tied", [1, 64, 65, 1025, 2048, 2049])
+def test_threshold_among_ties(pk, n, tied):
+    print(f"ties n={n} tied={tied}", flush=True)
+    O = wl.random_local_strings(n, 6000, 12, seed=tied)
+    rng = np.random.default_rng(tied)
+    mag = np.where(np.arange(6000) < tied, 1.0, 2.0 ** rng.integers(1, 4, 6000))
+    mag[3000 + tied // 2:] = 2.0 ** -rng.integers(1, 9, 6000 - 3000 - tied // 2)
+    phase = np.array([1, 1j, -1, -1j])[rng.integers(0, 4, 6000)]
+    O = wl.HostOp(n, O.x, O.z, mag * phase)
+    above = int((mag > 1.0).sum())
+    ws = pk.Workspace(256 << 20)
+    for cut in sorted({above + 1, above + (tied + 1) // 2, above + tied}):
+        tr = dict(max_strings=cut)
+        got = pk.truncate(pk.PauliOp.from_host(O, ws=ws), pk.Trunc(**tr), ws=ws).to_host()
+        same(got, oracle.truncate(O, oracle.Trunc(**tr)), f"top {cut}")
