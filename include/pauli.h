@@ -12,12 +12,13 @@
  *   - Every pointer inside pauli_op and pauli_ws is a DEVICE pointer owned by
  *     the caller.  The library never allocates or frees device memory and
  *     keeps no pointer to caller memory after a call returns.  State kept
- *     between calls: a pinned host control block (under 1 KiB) per calling thread
+ *     between calls: a pinned host block (under 16 KiB) per calling thread
  *     (allocated with hipHostMalloc on the thread's first call, kept until the
  *     process ends), two events and a side stream of default priority per
  *     calling thread (created on its first call, on the device then current;
- *     the control block is copied to the host on the side stream while the
- *     call's own stream goes on), the per-thread diagnostics below and the
+ *     the block receives control data and partial sums from the device; an
+ *     early copy to it runs on the side stream while the call's own stream
+ *     goes on), the per-thread diagnostics below and the
  *     optional kernel-timing log (pauli_profile_*).
  *   - x and z are word-major: word w of string k is x[w * capacity + k].
  *     coef holds `capacity` interleaved (re, im) pairs: double for

@@ -12,6 +12,7 @@
 #include <stdint.h>
 
 #define DEV __device__ __forceinline__
+#define HOSTDEV __host__ __device__ inline
 
 namespace pauli {
 
@@ -426,13 +427,13 @@ DEV void kahan_add(float& s, float& comp, float t) {
 struct dd {
   double hi, lo;
 };
-DEV dd dd_zero() { return {0.0, 0.0}; }
-DEV void two_sum(double a, double b, double& s, double& e) {
+HOSTDEV dd dd_zero() { return {0.0, 0.0}; }
+HOSTDEV void two_sum(double a, double b, double& s, double& e) {
   s = a + b;
   double bb = s - a;
   e = (a - (s - bb)) + (b - bb);
 }
-DEV dd dd_add(dd a, double b) {
+HOSTDEV dd dd_add(dd a, double b) {
   double s, e;
   two_sum(a.hi, b, s, e);
   e = e + a.lo;
@@ -440,7 +441,7 @@ DEV dd dd_add(dd a, double b) {
   double lo = e - (hi - s);
   return {hi, lo};
 }
-DEV dd dd_add(dd a, dd b) {
+HOSTDEV dd dd_add(dd a, dd b) {
   double s, e;
   two_sum(a.hi, b.hi, s, e);
   e = e + (a.lo + b.lo);

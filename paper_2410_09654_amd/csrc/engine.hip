@@ -132,15 +132,40 @@ struct ProfScope {
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 inline int words_of(int n_qubits) { return (n_qubits + 63) / 64; }
 
-// pinned host copy of the control block (one per thread)
-thread_local Ctl* t_hctl = nullptr;
+// Pinned host memory of a thread, written by the device: the final control
+// block of an engine call, and the partials and results of the reductions.
+constexpr int RED_SUMS = 6;  // sums of one reduction call
+struct HostBlock {
+  Ctl ctl;
+  unsigned int bad;                          // an operand is not in canonical order
+  double2 part[RED_SUMS * RED_BLOCKS];
+};
+thread_local HostBlock* t_host = nullptr;
 thread_local hipEvent_t t_ctl_event = nullptr, t_scan_event = nullptr;
 thread_local hipStream_t t_side_stream = nullptr;  // on device t_side_dev
 thread_local int t_side_dev = -1;
-int host_ctl(Ctl** out) {
-  if (!t_hctl) HIP_TRY(hipHostMalloc((void**)&t_hctl, sizeof(Ctl), hipHostMallocDefault));
-  *out = t_hctl;
+int host_block(HostBlock** out) {
+  if (!t_host) HIP_TRY(hipHostMalloc((void**)&t_host, sizeof(HostBlock), hipHostMallocPortable));
+  *out = t_host;
   return PAULI_OK;
+}
+int host_ctl(Ctl** out) {
+  HostBlock* h = nullptr;
+  TRY(host_block(&h));
+  *out = &h->ctl;
+  return PAULI_OK;
+}
+// the sum of the first n partials of slot k, rounded once
+double host_sum(const HostBlock* h, int k, int n) {
+  dd s = {0.0, 0.0};
+  for (int i = 0; i < n; i++) {
+    const double2 p = h->part[k * RED_BLOCKS + i];
+    s = dd_add(s, dd{p.x, p.y});
+  }
+  return s.hi;
+}
+inline int red_blocks(int64_t n) {
+  return (int)std::min<int64_t>((n + RED_THREADS - 1) / RED_THREADS, RED_BLOCKS);
 }
 
 // ---------------------------------------------------------------------------
@@ -1701,6 +1726,44 @@ int static_scratch(void** out) {
 }
 }  // namespace
 
+namespace {
+// Launches of the reductions; their sums go to the slots of h->part.
+int launch_norm(hipStream_t stream, const pauli_op* A, HostBlock* h, int slot) {
+  const int blocks = red_blocks(A->size);
+  if (A->dtype == PAULI_C64K)
+    LAUNCH("k_norm_part", k_norm_part<true>, blocks, RED_THREADS, A->coef, A->size,
+           h->part + slot * RED_BLOCKS);
+  else
+    LAUNCH("k_norm_part", k_norm_part<false>, blocks, RED_THREADS, A->coef, A->size,
+           h->part + slot * RED_BLOCKS);
+  return PAULI_OK;
+}
+// <A, B> by lookups of A's strings in B, whose order keys go to bmk (slots
+// slot, slot + 1); h->bad = 1 when B is not in canonical order
+template <int W>
+int launch_inner(hipStream_t stream, const OpV& A, const pauli_op* B, void* bmk, HostBlock* h,
+                 int slot) {
+  LAUNCH("k_mix_keys", k_mix_keys<W>, (B->size + 255) / 256, 256, B->x, B->z, B->capacity, B->size,
+         (Key<W>*)bmk, &h->bad);
+  LAUNCH("k_inner_part", k_inner_part<W>, red_blocks(A.n), RED_THREADS, A.x, A.z, A.cap, A.n, A.c,
+         A.f32, (const Key<W>*)bmk, B->size, B->coef, B->dtype == PAULI_C64K ? 1 : 0,
+         h->part + slot * RED_BLOCKS, h->part + (slot + 1) * RED_BLOCKS);
+  return PAULI_OK;
+}
+int launch_inner(hipStream_t stream, const OpV& A, const pauli_op* B, void* bmk, HostBlock* h,
+                 int slot) {
+  return A.W == 1 ? launch_inner<1>(stream, A, B, bmk, h, slot)
+                  : launch_inner<2>(stream, A, B, bmk, h, slot);
+}
+// workspace of a reduction: `keys` bytes of order keys
+int red_room(pauli_ws* ws, size_t keys, void** out = nullptr) {
+  Arena ar = make_arena(ws);
+  void* p = ar.take(std::max<size_t>(keys, 16));
+  if (out) *out = p;
+  return ar.short_ ? ws_short(ar, ws) : PAULI_OK;
+}
+}  // namespace
+
 // ===========================================================================
 // C ABI
 // ===========================================================================
@@ -1893,61 +1956,55 @@ int pauli_canonicalize_ts1d(const pauli_op* in, pauli_op* out, pauli_ws* ws, voi
 int pauli_norm2_ts1d(const pauli_op* A, double* out, pauli_ws* ws, void* stream_) {
   if (!ws || !out || check_op(A, false)) return PAULI_EINVAL;
   hipStream_t stream = (hipStream_t)stream_;
-  Arena ar = make_arena(ws);
-  const int blocks = (int)std::min<int64_t>(std::max<int64_t>((A->size + 255) / 256, 1), 1024);
-  double2* part = (double2*)ar.take((size_t)blocks * 16);
-  double* res = (double*)ar.take(16);
-  if (ar.short_) return ws_short(ar, ws);
+  TRY(red_room(ws, 0));
   if (A->size == 0) {
     *out = 0.0;
     return PAULI_OK;
   }
+  HostBlock* h = nullptr;
+  TRY(host_block(&h));
+  const int blocks = red_blocks(A->size);
   const int W = words_of(A->n_qubits), N = A->n_qubits;
   const bool f32 = A->dtype == PAULI_C64K;
+#define NORM_TS(W, F)                                                                        \
+  LAUNCH("k_norm_part_ts", (k_norm_part_ts<W, F>), blocks, RED_THREADS, A->x, A->z,          \
+         A->capacity, A->coef, A->size, N, ts_top(N), h->part)
   if (W == 1) {
-    if (f32)
-      LAUNCH("k_norm_part_ts", (k_norm_part_ts<1, true>), blocks, 256, A->x, A->z, A->capacity,
-             A->coef, A->size, N, ts_top(N), part);
-    else
-      LAUNCH("k_norm_part_ts", (k_norm_part_ts<1, false>), blocks, 256, A->x, A->z, A->capacity,
-             A->coef, A->size, N, ts_top(N), part);
+    if (f32) NORM_TS(1, true);
+    else NORM_TS(1, false);
   } else {
-    if (f32)
-      LAUNCH("k_norm_part_ts", (k_norm_part_ts<2, true>), blocks, 256, A->x, A->z, A->capacity,
-             A->coef, A->size, N, ts_top(N), part);
-    else
-      LAUNCH("k_norm_part_ts", (k_norm_part_ts<2, false>), blocks, 256, A->x, A->z, A->capacity,
-             A->coef, A->size, N, ts_top(N), part);
+    if (f32) NORM_TS(2, true);
+    else NORM_TS(2, false);
   }
-  LAUNCH("k_reduce_dd", k_reduce_dd, 1, 1024, part, (uint32_t)blocks, res);
-  double h[2];
-  HIP_TRY(hipMemcpyAsync(h, res, 16, hipMemcpyDeviceToHost, stream));
+#undef NORM_TS
   HIP_TRY(hipStreamSynchronize(stream));
   g_prof.resolve();
-  *out = h[0];
+  *out = host_sum(h, 0, blocks);
   return PAULI_OK;
 }
 
 int pauli_trace(const pauli_op* A, double out[2], pauli_ws* ws, void* stream_) {
   if (!ws || !out || check_op(A, false)) return PAULI_EINVAL;
   hipStream_t stream = (hipStream_t)stream_;
-  Arena ar = make_arena(ws);
-  double* res = (double*)ar.take(16);
-  if (ar.short_) return ws_short(ar, ws);
+  TRY(red_room(ws, 0));
   out[0] = 0.0;
   out[1] = 0.0;
   if (A->size == 0) return PAULI_OK;
-  const int W = words_of(A->n_qubits);
-  LAUNCH("k_fill_u32", k_fill_u32, 1, 256, (uint32_t*)res, 0u, (size_t)4);
+  HostBlock* h = nullptr;
+  TRY(host_block(&h));
+  h->part[0] = make_double2(0.0, 0.0);
   const int blocks = (int)std::min<int64_t>((A->size + 255) / 256, 4096);
-  LAUNCH("k_trace", k_trace, blocks, 256, A->x, A->z, A->capacity, A->size, W,
-         A->coef, A->dtype == PAULI_C64K ? 1 : 0, res);
-  double h[2];
-  HIP_TRY(hipMemcpyAsync(h, res, 16, hipMemcpyDeviceToHost, stream));
+  const int f32 = A->dtype == PAULI_C64K ? 1 : 0;
+  if (words_of(A->n_qubits) == 1)
+    LAUNCH("k_trace", k_trace<1>, blocks, 256, A->x, A->z, A->capacity, A->size, A->coef, f32,
+           &h->part[0].x);
+  else
+    LAUNCH("k_trace", k_trace<2>, blocks, 256, A->x, A->z, A->capacity, A->size, A->coef, f32,
+           &h->part[0].x);
   HIP_TRY(hipStreamSynchronize(stream));
   g_prof.resolve();
-  out[0] = h[0];
-  out[1] = h[1];
+  out[0] = h->part[0].x;
+  out[1] = h->part[0].y;
   return PAULI_OK;
 }
 
@@ -2114,52 +2171,33 @@ static int lanczos_step_reorth(const pauli_op* H, const pauli_op* O_prev, const 
   const pauli_op* V[2] = {O_cur, has_prev ? O_prev : nullptr};
   if (Op.n > 0) {
     ar.bottom = 0;
-    unsigned int* bad = (unsigned int*)ar.take(16);
-    double* res = (double*)ar.take(6 * 16);
-    const int blocks = (int)std::min<int64_t>(std::max<int64_t>((Op.n + 255) / 256, 1), 1024);
-    double2* pr = (double2*)ar.take((size_t)1024 * 16);  // partials of up to 1024 blocks
-    double2* pi = (double2*)ar.take((size_t)1024 * 16);
     int64_t nk = 0;
     for (int k = 0; k < 2; k++)
       if (V[k]) nk = std::max<int64_t>(nk, V[k]->size);
     void* vmk = ar.take((size_t)std::max<int64_t>(nk, 1) * 16 * W);
     if (ar.short_) return ws_short(ar, ws);
-    LAUNCH("k_fill_u32", k_fill_u32, 1, 256, (uint32_t*)bad, 0u, (size_t)4);
+    HostBlock* hb = nullptr;
+    TRY(host_block(&hb));
+    hb->bad = 0;
     for (int k = 0; k < 2; k++) {
       const pauli_op* v = V[k];
       if (!v || v->size == 0) continue;
-      const int vb = (int)std::min<int64_t>((v->size + 255) / 256, 1024);
-      const int vf32 = v->dtype == PAULI_C64K;
-      // <O', V> = sum conj(o') v over common strings (V canonical: binary search)
-      if (W == 1) {
-        LAUNCH("k_mix_keys", k_mix_keys<1>, (v->size + 255) / 256, 256, v->x, v->z, v->capacity,
-               v->size, (Key<1>*)vmk, bad);
-        LAUNCH("k_inner_part", k_inner_part<1>, blocks, 256, Op.x, Op.z, Op.cap, Op.n, Op.c, 0,
-               (const Key<1>*)vmk, v->size, v->coef, vf32, pr, pi);
-      } else {
-        LAUNCH("k_mix_keys", k_mix_keys<2>, (v->size + 255) / 256, 256, v->x, v->z, v->capacity,
-               v->size, (Key<2>*)vmk, bad);
-        LAUNCH("k_inner_part", k_inner_part<2>, blocks, 256, Op.x, Op.z, Op.cap, Op.n, Op.c, 0,
-               (const Key<2>*)vmk, v->size, v->coef, vf32, pr, pi);
-      }
-      LAUNCH("k_reduce_dd", k_reduce_dd, 1, 1024, pr, (uint32_t)blocks, res + 6 * k);
-      LAUNCH("k_reduce_dd", k_reduce_dd, 1, 1024, pi, (uint32_t)blocks, res + 6 * k + 2);
-      // ||V||^2 (the partials reuse pr: same stream, after the reduction above)
-      if (vf32)
-        LAUNCH("k_norm_part", k_norm_part<true>, vb, 256, v->coef, v->size, pr);
-      else
-        LAUNCH("k_norm_part", k_norm_part<false>, vb, 256, v->coef, v->size, pr);
-      LAUNCH("k_reduce_dd", k_reduce_dd, 1, 1024, pr, (uint32_t)vb, res + 6 * k + 4);
+      // <O', V> = sum conj(o') v over common strings (V canonical), ||V||^2
+      TRY(launch_inner(stream, Op, v, vmk, hb, 3 * k));
+      TRY(launch_norm(stream, v, hb, 3 * k + 2));
     }
-    double h[12];
-    unsigned int hbad = 0;
-    HIP_TRY(hipMemcpyAsync(h, res, sizeof(h), hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipMemcpyAsync(&hbad, bad, 4, hipMemcpyDeviceToHost, stream));
     HIP_TRY(hipStreamSynchronize(stream));
     g_prof.resolve();
-    if (hbad) {
+    if (hb->bad) {
       g_last_error = "re-orthogonalisation needs canonical O_cur and O_prev";
       return PAULI_EINVAL;
+    }
+    double h[12] = {0.0};
+    for (int k = 0; k < 2; k++) {
+      if (!V[k] || V[k]->size == 0) continue;
+      h[6 * k] = host_sum(hb, 3 * k, red_blocks(Op.n));
+      h[6 * k + 2] = host_sum(hb, 3 * k + 1, red_blocks(Op.n));
+      h[6 * k + 4] = host_sum(hb, 3 * k + 2, red_blocks(V[k]->size));
     }
     for (int k = 0; k < 2; k++) {
       if (!V[k] || V[k]->size == 0) continue;
@@ -2333,27 +2371,26 @@ int pauli_coefficients(const pauli_op* A, const pauli_op* Q, double* out, pauli_
   if (Q->size == 0) return PAULI_OK;
   const int W = words_of(A->n_qubits);
   Arena ar = make_arena(ws);
-  void* keys = ar.take((size_t)std::max<int64_t>(A->size, 1) * 16 * W);
   double2* res = (double2*)ar.take((size_t)Q->size * 16);
   if (ar.short_) return ws_short(ar, ws);
-  const int64_t ba = (std::max<int64_t>(A->size, 1) + 255) / 256, bq = (Q->size + 255) / 256;
+  HostBlock* h = nullptr;
+  TRY(host_block(&h));
+  // few results go straight to pinned memory
+  const bool direct = Q->size <= RED_SUMS * RED_BLOCKS;
+  if (direct) res = h->part;
+  const int64_t bq = (Q->size + 63) / 64;
   const int af32 = A->dtype == PAULI_C64K ? 1 : 0;
-  if (W == 1) {
-    if (A->size)
-      LAUNCH("k_order_keys", k_order_keys<1>, ba, 256, A->x, A->z, A->capacity, A->size,
-             reinterpret_cast<Key<1>*>(keys));
-    LAUNCH("k_lookup", k_lookup<1>, bq, 256, reinterpret_cast<const Key<1>*>(keys), A->coef,
-           af32, A->size, Q->x, Q->z, Q->capacity, Q->size, res);
-  } else {
-    if (A->size)
-      LAUNCH("k_order_keys", k_order_keys<2>, ba, 256, A->x, A->z, A->capacity, A->size,
-             reinterpret_cast<Key<2>*>(keys));
-    LAUNCH("k_lookup", k_lookup<2>, bq, 256, reinterpret_cast<const Key<2>*>(keys), A->coef,
-           af32, A->size, Q->x, Q->z, Q->capacity, Q->size, res);
-  }
-  HIP_TRY(hipMemcpyAsync(out, res, (size_t)Q->size * 16, hipMemcpyDeviceToHost, stream));
+  if (W == 1)
+    LAUNCH("k_lookup", k_lookup<1>, bq, 64, A->x, A->z, A->capacity, A->coef, af32, A->size, Q->x,
+           Q->z, Q->capacity, Q->size, res);
+  else
+    LAUNCH("k_lookup", k_lookup<2>, bq, 64, A->x, A->z, A->capacity, A->coef, af32, A->size, Q->x,
+           Q->z, Q->capacity, Q->size, res);
+  if (!direct)
+    HIP_TRY(hipMemcpyAsync(out, res, (size_t)Q->size * 16, hipMemcpyDeviceToHost, stream));
   HIP_TRY(hipStreamSynchronize(stream));
   g_prof.resolve();
+  if (direct) memcpy(out, res, (size_t)Q->size * 16);
   return PAULI_OK;
 }
 
@@ -2400,40 +2437,45 @@ int pauli_workspace_query(int op, const pauli_op* A, const pauli_op* B, const pa
 }
 
 int pauli_correlator(const pauli_op* O0, const pauli_op* O, double out[2], pauli_ws* ws,
-                     void* stream) {
+                     void* stream_) {
   if (!out || check_op(O0, false) || check_op(O, false)) return PAULI_EINVAL;
-  double n0 = 0.0, ip[2] = {0.0, 0.0};
-  TRY(pauli_norm2(O0, &n0, ws, stream));
+  if (!ws || O0->n_qubits != O->n_qubits) return PAULI_EINVAL;
+  hipStream_t stream = (hipStream_t)stream_;
+  void* bmk = nullptr;
+  TRY(red_room(ws, (size_t)O0->size * 16 * words_of(O->n_qubits), &bmk));
+  if (O0->size == 0) return PAULI_EINVAL;  // <O0, O0> = 0
+  HostBlock* h = nullptr;
+  TRY(host_block(&h));
+  h->bad = 0;
+  TRY(launch_norm(stream, O0, h, 0));
   // <O, O0> looped over O with order-key lookups in O0, then conjugated
-  TRY(pauli_inner(O, O0, ip, ws, stream));
+  if (O->size) TRY(launch_inner(stream, view(O), O0, bmk, h, 1));
+  HIP_TRY(hipStreamSynchronize(stream));
+  g_prof.resolve();
+  if (h->bad) return PAULI_EINVAL;
+  const double n0 = host_sum(h, 0, red_blocks(O0->size));
   if (!(n0 > 0.0)) return PAULI_EINVAL;
-  out[0] = ip[0] / n0;
-  out[1] = -ip[1] / n0;
+  const double re = O->size ? host_sum(h, 1, red_blocks(O->size)) : 0.0;
+  const double im = O->size ? host_sum(h, 2, red_blocks(O->size)) : 0.0;
+  out[0] = re / n0;
+  out[1] = -im / n0;
   return PAULI_OK;
 }
 
 int pauli_norm2(const pauli_op* A, double* out, pauli_ws* ws, void* stream_) {
   if (!ws || !out || check_op(A, false)) return PAULI_EINVAL;
   hipStream_t stream = (hipStream_t)stream_;
-  Arena ar = make_arena(ws);
-  const int blocks = (int)std::min<int64_t>(std::max<int64_t>((A->size + 255) / 256, 1), 1024);
-  double2* part = (double2*)ar.take((size_t)blocks * 16);
-  double* res = (double*)ar.take(16);
-  if (ar.short_) return ws_short(ar, ws);
+  TRY(red_room(ws, 0));
   if (A->size == 0) {
     *out = 0.0;
     return PAULI_OK;
   }
-  if (A->dtype == PAULI_C64K)
-    LAUNCH("k_norm_part", k_norm_part<true>, blocks, 256, A->coef, A->size, part);
-  else
-    LAUNCH("k_norm_part", k_norm_part<false>, blocks, 256, A->coef, A->size, part);
-  LAUNCH("k_reduce_dd", k_reduce_dd, 1, 1024, part, (uint32_t)blocks, res);
-  double h[2];
-  HIP_TRY(hipMemcpyAsync(h, res, 16, hipMemcpyDeviceToHost, stream));
+  HostBlock* h = nullptr;
+  TRY(host_block(&h));
+  TRY(launch_norm(stream, A, h, 0));
   HIP_TRY(hipStreamSynchronize(stream));
   g_prof.resolve();
-  *out = h[0];
+  *out = host_sum(h, 0, red_blocks(A->size));
   return PAULI_OK;
 }
 
@@ -2442,45 +2484,19 @@ int pauli_inner(const pauli_op* A, const pauli_op* B, double out[2], pauli_ws* w
   if (!ws || !out || check_op(A, false) || check_op(B, false)) return PAULI_EINVAL;
   if (A->n_qubits != B->n_qubits) return PAULI_EINVAL;
   hipStream_t stream = (hipStream_t)stream_;
-  Arena ar = make_arena(ws);
-  const int W = words_of(A->n_qubits);
-  const int blocks = (int)std::min<int64_t>(std::max<int64_t>((A->size + 255) / 256, 1), 1024);
-  Ctl* dctl = (Ctl*)ar.take(sizeof(Ctl));
-  void* bmk = ar.take((size_t)std::max<int64_t>(B->size, 1) * 16 * W);
-  double2* pr = (double2*)ar.take((size_t)blocks * 16);
-  double2* pi = (double2*)ar.take((size_t)blocks * 16);
-  double* res = (double*)ar.take(32);
-  if (ar.short_) return ws_short(ar, ws);
+  void* bmk = nullptr;
+  TRY(red_room(ws, (size_t)B->size * 16 * words_of(A->n_qubits), &bmk));
   out[0] = out[1] = 0.0;
   if (A->size == 0 || B->size == 0) return PAULI_OK;
-  {
-    const size_t words = sizeof(Ctl) / 4;
-    LAUNCH("k_fill_u32", k_fill_u32, (words + 255) / 256, 256, (uint32_t*)dctl, 0u, words);
-  }
-  if (W == 1) {
-    LAUNCH("k_mix_keys", k_mix_keys<1>, (B->size + 255) / 256, 256, B->x, B->z, B->capacity,
-           B->size, (Key<1>*)bmk, &dctl->bad_keep);
-    LAUNCH("k_inner_part", k_inner_part<1>, blocks, 256, A->x, A->z, A->capacity, A->size,
-           A->coef, A->dtype == PAULI_C64K, (const Key<1>*)bmk, B->size, B->coef,
-           B->dtype == PAULI_C64K, pr, pi);
-  } else {
-    LAUNCH("k_mix_keys", k_mix_keys<2>, (B->size + 255) / 256, 256, B->x, B->z, B->capacity,
-           B->size, (Key<2>*)bmk, &dctl->bad_keep);
-    LAUNCH("k_inner_part", k_inner_part<2>, blocks, 256, A->x, A->z, A->capacity, A->size,
-           A->coef, A->dtype == PAULI_C64K, (const Key<2>*)bmk, B->size, B->coef,
-           B->dtype == PAULI_C64K, pr, pi);
-  }
-  LAUNCH("k_reduce_dd", k_reduce_dd, 1, 1024, pr, (uint32_t)blocks, res);
-  LAUNCH("k_reduce_dd", k_reduce_dd, 1, 1024, pi, (uint32_t)blocks, res + 2);
-  double h[4];
-  unsigned int bad = 0;
-  HIP_TRY(hipMemcpyAsync(h, res, 32, hipMemcpyDeviceToHost, stream));
-  HIP_TRY(hipMemcpyAsync(&bad, &dctl->bad_keep, 4, hipMemcpyDeviceToHost, stream));
+  HostBlock* h = nullptr;
+  TRY(host_block(&h));
+  h->bad = 0;
+  TRY(launch_inner(stream, view(A), B, bmk, h, 0));
   HIP_TRY(hipStreamSynchronize(stream));
   g_prof.resolve();
-  if (bad) return PAULI_EINVAL;
-  out[0] = h[0];
-  out[1] = h[2];
+  if (h->bad) return PAULI_EINVAL;
+  out[0] = host_sum(h, 0, red_blocks(A->size));
+  out[1] = host_sum(h, 1, red_blocks(A->size));
   return PAULI_OK;
 }
 

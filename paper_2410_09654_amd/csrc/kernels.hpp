@@ -1526,24 +1526,21 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
 }
 
 // Coefficient of the identity string (all mask words zero) of an operator
-// with distinct strings: Tr(A)/2^N.  `res` (two doubles) starts at zero; at
-// most one thread writes it.
+// with distinct strings: Tr(A)/2^N.  `res` (two doubles, pinned) starts at
+// zero; at most one thread writes it.
+template <int W>
 __global__ __launch_bounds__(256) void k_trace(const uint64_t* x, const uint64_t* z, int64_t cap,
-                                               int64_t n, int W, const void* coef, int f32,
-                                               double* res) {
+                                               int64_t n, const void* coef, int f32, double* res) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
     uint64_t s = 0;
+#pragma unroll
     for (int w = 0; w < W; w++) s |= x[(size_t)w * cap + i] | z[(size_t)w * cap + i];
     if (s == 0) {
-      if (f32) {
-        const float2 v = reinterpret_cast<const float2*>(coef)[i];
-        res[0] = (double)v.x;
-        res[1] = (double)v.y;
-      } else {
-        const double2 v = reinterpret_cast<const double2*>(coef)[i];
-        res[0] = v.x;
-        res[1] = v.y;
-      }
+      const double2 v = f32 ? make_double2((double)reinterpret_cast<const float2*>(coef)[i].x,
+                                           (double)reinterpret_cast<const float2*>(coef)[i].y)
+                            : reinterpret_cast<const double2*>(coef)[i];
+      res[0] = v.x;
+      res[1] = v.y;
     }
   }
 }
@@ -1664,40 +1661,6 @@ __global__ __launch_bounds__(1024) void k_bucket_totals(const uint32_t* b_slots,
     ctl->surv_total = tot[1];
     ctl->keep_total = tot[2];
     if (b_unique) ctl->u_unique = tot[3];
-  }
-}
-
-// Deterministic double-double sum of n partials (one block).
-__global__ __launch_bounds__(1024) void k_reduce_dd(const double2* part, uint32_t n, double* out) {
-  // four independent double-double chains per thread (partials i, i + 1024,
-  // i + 2048, i + 3072 of every 4096), combined in a fixed order
-  __shared__ double rh[16], rl[16];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  dd s[4] = {dd_zero(), dd_zero(), dd_zero(), dd_zero()};
-  for (uint32_t i0 = 0; i0 < n; i0 += 4096) {
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      const uint32_t i = i0 + q * 1024 + tid;
-      if (i < n) s[q] = dd_add(s[q], dd{part[i].x, part[i].y});
-    }
-  }
-  dd t = dd_add(dd_add(s[0], s[1]), dd_add(s[2], s[3]));
-  for (int d = 32; d >= 1; d >>= 1) {
-    dd o;
-    o.hi = __shfl_down(t.hi, d, 64);
-    o.lo = __shfl_down(t.lo, d, 64);
-    if (lane < d) t = dd_add(t, o);
-  }
-  if (lane == 0) {
-    rh[wv] = t.hi;
-    rl[wv] = t.lo;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    dd u = {rh[0], rl[0]};
-    for (int w = 1; w < 16; w++) u = dd_add(u, dd{rh[w], rl[w]});
-    out[0] = u.hi;
-    out[1] = u.lo;
   }
 }
 
@@ -2324,7 +2287,7 @@ __global__ void k_mix_keys(const uint64_t* x, const uint64_t* z, int64_t cap, in
       rp.w[w] = x[(size_t)w * cap + i - 1];
       rp.w[W + w] = z[(size_t)w * cap + i - 1];
     }
-    if (key_cmp<W>(mix_key<W>(rp), m) >= 0) atomicOr(bad, 1u);
+    if (key_cmp<W>(mix_key<W>(rp), m) >= 0) *bad = 1u;  // (may lie in host memory)
   }
 }
 
@@ -2369,40 +2332,57 @@ __global__ __launch_bounds__(256) void k_conj(void* coef, int64_t n, int f32) {
   }
 }
 
-// Coefficients in A (canonical: ascending order keys `ak`) of the strings of
-// Q: out[q] = A's coefficient of Q's string q, or 0 when A lacks it.
-template <int W>
-__global__ __launch_bounds__(256) void k_lookup(const Key<W>* ak, const void* acoef, int af32,
-                                                int64_t na, const uint64_t* qx,
-                                                const uint64_t* qz, int64_t qcap, int64_t nq,
-                                                double2* out) {
-  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (q >= nq) return;
-  Key<W> raw;
-#pragma unroll
-  for (int w = 0; w < W; w++) {
-    raw.w[w] = qx[(size_t)w * qcap + q];
-    raw.w[W + w] = qz[(size_t)w * qcap + q];
-  }
-  const Key<W> mk = mix_key<W>(raw);
-  int64_t lo = 0, hi = na;
-  double2 v = make_double2(0.0, 0.0);
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    const int c = key_cmp<W>(ak[mid], mk);
-    if (c == 0) {
-      if (af32) {
-        const float2 f = reinterpret_cast<const float2*>(acoef)[mid];
-        v = make_double2((double)f.x, (double)f.y);
-      } else {
-        v = reinterpret_cast<const double2*>(acoef)[mid];
-      }
-      break;
+// Position of the order key m among n strings in canonical order (key(i): the
+// order key of string i), or -1.  Order keys are spread evenly, so the
+// position is interpolated between the keys seen so far: about four dependent
+// reads where bisection takes log2(n); after eight, whatever the keys are,
+// bisection finishes.
+template <int W, typename F>
+DEV int64_t find_key(const Key<W>& m, int64_t n, F key) {
+  int64_t lo = 0, hi = n;
+  uint64_t klo = 0ull, khi = ~0ull;  // leading words below lo and from hi on
+  for (int step = 0; lo < hi; step++) {
+    int64_t mid = (lo + hi) >> 1;
+    if (step < 8 && khi > klo) {
+      const double f = fmin((double)(m.w[0] - klo) / (double)(khi - klo), 1.0);
+      mid = min(max(lo + (int64_t)(f * (double)(hi - lo)), lo), hi - 1);
     }
-    if (c < 0) lo = mid + 1;
-    else hi = mid;
+    const Key<W> k = key(mid);
+    const int c = key_cmp<W>(k, m);
+    if (c == 0) return mid;
+    if (c < 0) {
+      lo = mid + 1;
+      klo = k.w[0];
+    } else {
+      hi = mid;
+      khi = k.w[0];
+    }
   }
-  out[q] = v;
+  return -1;
+}
+
+DEV double2 load_coef(const void* c, int f32, int64_t i) {
+  if (f32) {
+    const float2 f = reinterpret_cast<const float2*>(c)[i];
+    return make_double2((double)f.x, (double)f.y);
+  }
+  return reinterpret_cast<const double2*>(c)[i];
+}
+
+// Coefficients in A (canonical) of the strings of Q: out[q] = A's coefficient
+// of Q's string q, or 0 when A lacks it.  A's keys are mixed where the search
+// reads them: mixing all of A first took 3 of 10 us at 2^18 strings.
+template <int W>
+__global__ __launch_bounds__(64) void k_lookup(const uint64_t* ax, const uint64_t* az,
+                                               int64_t acap, const void* acoef, int af32,
+                                               int64_t na, const uint64_t* qx, const uint64_t* qz,
+                                               int64_t qcap, int64_t nq, double2* out) {
+  const int64_t q = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  if (q >= nq) return;
+  const Key<W> mk = mix_key<W>(load_raw<W>(qx, qz, qcap, q));
+  const int64_t i = find_key<W>(
+      mk, na, [&](int64_t k) { return mix_key<W>(load_raw<W>(ax, az, acap, k)); });
+  out[q] = i >= 0 ? load_coef(acoef, af32, i) : make_double2(0.0, 0.0);
 }
 
 // H = sum_k T_k(H0) listed as T_0(h_0), T_1(h_0), ..., T_{N-1}(h_0), T_0(h_1), ...
@@ -2436,40 +2416,21 @@ __global__ __launch_bounds__(256) void k_ts_expand(const uint64_t* x, const uint
   oc[i] = c[h];
 }
 
-// Per-block double-double partials of sum_k stab(s_k) |c_k|^2: the norm of a
-// translation-symmetric operator held as representatives, over N (stab =
-// translations k in [0, N) that leave the string unchanged).
-template <int W, bool F32>
-__global__ __launch_bounds__(256) void k_norm_part_ts(const uint64_t* x, const uint64_t* z,
-                                                      int64_t cap, const void* coef, int64_t n,
-                                                      int N, TsTop top, double2* part) {
-  __shared__ double rh[4], rl[4];
+// Reductions over an operator's strings: at most RED_BLOCKS blocks of
+// RED_THREADS threads leave double-double partials in pinned host memory, which
+// the host adds up after its one wait (a second kernel and a copy of its result
+// took longer than the sum).
+constexpr int RED_BLOCKS = 128, RED_THREADS = 1024;
+DEV void red_part(dd s, double2* part) {
+  __shared__ double rh[RED_THREADS / 64], rl[RED_THREADS / 64];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  dd s = dd_zero();
-  for (int64_t i = (int64_t)blockIdx.x * 256 + tid; i < n; i += (int64_t)gridDim.x * 256) {
-    double2 v;
-    if (F32) {
-      const float2 f = reinterpret_cast<const float2*>(coef)[i];
-      v = make_double2(f.x, f.y);
-    } else {
-      v = reinterpret_cast<const double2*>(coef)[i];
-    }
-    uint64_t vx[W], vz[W];
-#pragma unroll
-    for (int w = 0; w < W; w++) {
-      vx[w] = x[(size_t)w * cap + i];
-      vz[w] = z[(size_t)w * cap + i];
-    }
-    const int st = ts_stabilizers<W>(vx, vz, N, top);
-    const double w2 = weight2(v);
-    for (int r = 0; r < st; r++) s = dd_add(s, w2);
-  }
   for (int d = 32; d >= 1; d >>= 1) {
     dd o;
     o.hi = __shfl_down(s.hi, d, 64);
     o.lo = __shfl_down(s.lo, d, 64);
     if (lane < d) s = dd_add(s, o);
   }
+  __syncthreads();  // rh, rl of an earlier sum have been read
   if (lane == 0) {
     rh[wv] = s.hi;
     rl[wv] = s.lo;
@@ -2477,9 +2438,29 @@ __global__ __launch_bounds__(256) void k_norm_part_ts(const uint64_t* x, const u
   __syncthreads();
   if (tid == 0) {
     dd t = {rh[0], rl[0]};
-    for (int w = 1; w < 4; w++) t = dd_add(t, dd{rh[w], rl[w]});
+    for (int w = 1; w < RED_THREADS / 64; w++) t = dd_add(t, dd{rh[w], rl[w]});
     part[blockIdx.x] = make_double2(t.hi, t.lo);
   }
+}
+
+// sum_k stab(s_k) |c_k|^2: the norm of a translation-symmetric operator held
+// as representatives, over N (stab = translations k in [0, N) that leave the
+// string unchanged).
+template <int W, bool F32>
+__global__ __launch_bounds__(RED_THREADS) void k_norm_part_ts(const uint64_t* x, const uint64_t* z,
+                                                              int64_t cap, const void* coef,
+                                                              int64_t n, int N, TsTop top,
+                                                              double2* part) {
+  dd s = dd_zero();
+  for (int64_t i = (int64_t)blockIdx.x * RED_THREADS + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * RED_THREADS) {
+    const double2 v = load_coef(coef, F32, i);
+    const Key<W> raw = load_raw<W>(x, z, cap, i);
+    const int st = ts_stabilizers<W>(raw.w, raw.w + W, N, top);
+    const double w2 = weight2(v);
+    for (int r = 0; r < st; r++) s = dd_add(s, w2);
+  }
+  red_part(s, part);
 }
 
 // Order keys of an operator's strings, and the strings of order keys.
@@ -2510,80 +2491,38 @@ __global__ void k_from_order_keys(const Key<W>* keys, int64_t n, uint64_t* x, ui
   }
 }
 
-// Partial double-double sums of |c|^2 per block.
+// sum |c|^2
 template <bool F32>
-__global__ __launch_bounds__(256) void k_norm_part(const void* coef, int64_t n, double2* part) {
-  __shared__ double rh[4], rl[4];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+__global__ __launch_bounds__(RED_THREADS) void k_norm_part(const void* coef, int64_t n,
+                                                           double2* part) {
   dd s = dd_zero();
-  for (int64_t i = (int64_t)blockIdx.x * 256 + tid; i < n; i += (int64_t)gridDim.x * 256) {
-    double2 v;
-    if (F32) {
-      const float2 f = reinterpret_cast<const float2*>(coef)[i];
-      v = make_double2(f.x, f.y);
-    } else {
-      v = reinterpret_cast<const double2*>(coef)[i];
-    }
-    s = dd_add(s, weight2(v));
+  const int64_t step = (int64_t)gridDim.x * RED_THREADS;
+  for (int64_t i0 = (int64_t)blockIdx.x * RED_THREADS + threadIdx.x; i0 < n; i0 += 4 * step) {
+    double w2[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++)
+      w2[u] = i0 + u * step < n ? weight2(load_coef(coef, F32, i0 + u * step)) : 0.0;
+#pragma unroll
+    for (int u = 0; u < 4; u++) s = dd_add(s, w2[u]);
   }
-  for (int d = 32; d >= 1; d >>= 1) {
-    dd o;
-    o.hi = __shfl_down(s.hi, d, 64);
-    o.lo = __shfl_down(s.lo, d, 64);
-    if (lane < d) s = dd_add(s, o);
-  }
-  if (lane == 0) {
-    rh[wv] = s.hi;
-    rl[wv] = s.lo;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    dd t = {rh[0], rl[0]};
-    for (int w = 1; w < 4; w++) t = dd_add(t, dd{rh[w], rl[w]});
-    part[blockIdx.x] = make_double2(t.hi, t.lo);
-  }
+  red_part(s, part);
 }
 
-// Inner product partials: every string of A is looked up in B's mixed keys.
+// Inner product: every string of A is looked up in B's order keys.
 template <int W>
-__global__ __launch_bounds__(256) void k_inner_part(const uint64_t* ax, const uint64_t* az,
-                                                    int64_t acap, int64_t na, const void* acoef,
-                                                    int af32, const Key<W>* bmk, int64_t nb,
-                                                    const void* bcoef, int bf32, double2* part_re,
-                                                    double2* part_im) {
-  __shared__ double rh[2][4], rl[2][4];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+__global__ __launch_bounds__(RED_THREADS) void k_inner_part(const uint64_t* ax, const uint64_t* az,
+                                                            int64_t acap, int64_t na,
+                                                            const void* acoef, int af32,
+                                                            const Key<W>* bmk, int64_t nb,
+                                                            const void* bcoef, int bf32,
+                                                            double2* part_re, double2* part_im) {
   dd sr = dd_zero(), si = dd_zero();
-  for (int64_t i = (int64_t)blockIdx.x * 256 + tid; i < na; i += (int64_t)gridDim.x * 256) {
-    Key<W> raw;
-#pragma unroll
-    for (int w = 0; w < W; w++) {
-      raw.w[w] = ax[(size_t)w * acap + i];
-      raw.w[W + w] = az[(size_t)w * acap + i];
-    }
-    const Key<W> m = mix_key<W>(raw);
-    int64_t lo = 0, hi = nb;
-    int64_t found = -1;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      const int c = key_cmp<W>(bmk[mid], m);
-      if (c == 0) {
-        found = mid;
-        break;
-      }
-      if (c < 0) lo = mid + 1;
-      else hi = mid;
-    }
+  for (int64_t i = (int64_t)blockIdx.x * RED_THREADS + threadIdx.x; i < na;
+       i += (int64_t)gridDim.x * RED_THREADS) {
+    const Key<W> m = mix_key<W>(load_raw<W>(ax, az, acap, i));
+    const int64_t found = find_key<W>(m, nb, [&](int64_t k) { return bmk[k]; });
     if (found >= 0) {
-      double2 av, bv;
-      if (af32) {
-        const float2 f = reinterpret_cast<const float2*>(acoef)[i];
-        av = make_double2(f.x, f.y);
-      } else av = reinterpret_cast<const double2*>(acoef)[i];
-      if (bf32) {
-        const float2 f = reinterpret_cast<const float2*>(bcoef)[found];
-        bv = make_double2(f.x, f.y);
-      } else bv = reinterpret_cast<const double2*>(bcoef)[found];
+      const double2 av = load_coef(acoef, af32, i), bv = load_coef(bcoef, bf32, found);
       const double p1 = av.x * bv.x, p2 = av.y * bv.y, p3 = av.x * bv.y, p4 = av.y * bv.x;
       sr = dd_add(sr, p1);
       sr = dd_add(sr, p2);
@@ -2591,31 +2530,8 @@ __global__ __launch_bounds__(256) void k_inner_part(const uint64_t* ax, const ui
       si = dd_add(si, -p4);
     }
   }
-  for (int d = 32; d >= 1; d >>= 1) {
-    dd o;
-    o.hi = __shfl_down(sr.hi, d, 64);
-    o.lo = __shfl_down(sr.lo, d, 64);
-    if (lane < d) sr = dd_add(sr, o);
-    o.hi = __shfl_down(si.hi, d, 64);
-    o.lo = __shfl_down(si.lo, d, 64);
-    if (lane < d) si = dd_add(si, o);
-  }
-  if (lane == 0) {
-    rh[0][wv] = sr.hi;
-    rl[0][wv] = sr.lo;
-    rh[1][wv] = si.hi;
-    rl[1][wv] = si.lo;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    dd t0 = {rh[0][0], rl[0][0]}, t1 = {rh[1][0], rl[1][0]};
-    for (int w = 1; w < 4; w++) {
-      t0 = dd_add(t0, dd{rh[0][w], rl[0][w]});
-      t1 = dd_add(t1, dd{rh[1][w], rl[1][w]});
-    }
-    part_re[blockIdx.x] = make_double2(t0.hi, t0.lo);
-    part_im[blockIdx.x] = make_double2(t1.hi, t1.lo);
-  }
+  red_part(sr, part_re);
+  red_part(si, part_im);
 }
 
 __global__ void k_fill_u32(uint32_t* p, uint32_t v, size_t n) {

@@ -141,3 +141,26 @@ def test_threshold_among_ties(pk, n, tied):
         tr = dict(max_strings=cut)
         got = pk.truncate(pk.PauliOp.from_host(O, ws=ws), pk.Trunc(**tr), ws=ws).to_host()
         same(got, oracle.truncate(O, oracle.Trunc(**tr)), f"top {cut}")
+
+
+# key search by interpolation: operators of 1 to 3 strings and more, members and others; 768
+# results fit the pinned block, 769 do not; 131072 strings fill one round of the reductions
+@pytest.mark.parametrize("n", [30, 90])
+@pytest.mark.parametrize("na,nq", [(1, 3), (2, 5), (3, 768), (5000, 769), (131073, 2000)])
+def test_lookups_and_reductions(pk, n, na, nq):
+    print(f"lookups n={n} na={na} nq={nq}", flush=True)
+    A = wl.random_local_strings(n, na, 12, seed=na)
+    B = wl.random_local_strings(n, nq, 12, seed=nq + 1)
+    k = min(na, nq // 2)  # half of Q's strings are A's
+    Q = wl.HostOp(n, np.concatenate([A.x[:k], B.x[k:]]), np.concatenate([A.z[:k], B.z[k:]]),
+                  B.coef)
+    ws = pk.Workspace(64 << 20)
+    dA = pk.PauliOp.from_host(A, ws=ws)
+    assert np.array_equal(pk.coefficients(dA, raw(pk, Q), ws=ws), oracle.coefficients(A, Q))
+    assert pk.norm2(dA, ws=ws) == oracle.norm2(A)
+    dB = pk.PauliOp.from_host(oracle.canonicalize(Q), ws=ws)
+    want = oracle.inner(A, oracle.canonicalize(Q))
+    got = pk.inner(dA, dB, ws=ws)
+    assert got == want
+    s = pk.correlator(dA, dA, ws=ws)
+    assert s == 1.0
