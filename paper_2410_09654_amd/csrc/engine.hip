@@ -121,7 +121,7 @@ struct ProfScope {
 // both scans of a count matrix over 2^nbl bins
 #define SCAN(nbl, counts, rows, spec_cap, mcap)                                    \
   LAUNCH("k_scan", k_scan<nbl>, (1 << nbl) / SC_COLS, SC_COLS * SC_NSEG, counts,   \
-         rows, bin_total, bin_base, dctl, spec_cap, mcap)
+         rows, bin_total, bin_base, dctl, look, spec_cap, mcap)
 
 #define TRY(expr)                    \
   do {                               \
@@ -369,6 +369,7 @@ struct Bufs1 {
   uint32_t *hsum = nullptr, *h0sum = nullptr;
   unsigned long long* psum = nullptr;
   uint32_t* defer = nullptr;  // buckets left to the full-size merge (per pass)
+  unsigned long long* look = nullptr;  // look-back states of a pass's buckets
 };
 template <int W>
 void take_bufs1(Arena& ar, bool comm, int64_t nH, int64_t n_keep, int rows, Bufs1<W>& b) {
@@ -389,7 +390,9 @@ void take_bufs1(Arena& ar, bool comm, int64_t nH, int64_t n_keep, int rows, Bufs
   b.hsum = (uint32_t*)ar.take(SEL_BINS * 4);
   b.h0sum = (uint32_t*)ar.take(SEL0_BINS * 4);
   b.psum = (unsigned long long*)ar.take(PLAN_PARTS * 4 * 8);
-  b.defer = (uint32_t*)ar.take(NBINS_MP * 4);
+  // (a merge defers buckets or looks back, never both)
+  b.look = (unsigned long long*)ar.take(NBINS_MP * 8);
+  b.defer = (uint32_t*)b.look;
 }
 
 // scratch taken after the count pass: records (and their partitions),
@@ -579,6 +582,7 @@ int Engine::run(Call& c) {
   uint32_t* hsum = b1.hsum;
   uint32_t* h0sum = b1.h0sum;
   unsigned long long* psum = b1.psum;
+  unsigned long long* look = b1.look;
   if (ar->short_) return PAULI_EWORKSPACE;
   if (!hctl) {
     TRY(host_ctl(&hctl));
@@ -629,6 +633,8 @@ int Engine::run(Call& c) {
       pr.cursor = bin_base;
       pr.n_cursor = 1 << append_F;
     }
+    pr.look = look;
+    pr.n_look = MERGE_ONE_WAVE;
     pr.ctl = dctl;
     LAUNCH("k_prep", (k_prep<W>), PREP_BLOCKS, 1024, pr);
   }
@@ -648,6 +654,56 @@ int Engine::run(Call& c) {
   unsigned long long pe_all = 0;
   bool scattered = false;  // one pass over 2^14 bins scattered before the count was read
   MergeArgs ma;
+  WriteArgs wa;
+  memset(&wa, 0, sizeof(wa));
+  wa.keep_mk = keep_mk;
+  wa.n_keep = (int)n_keep;
+  wa.ctl = dctl;
+  wa.out_f32 = c.out.f32;
+  // where the output goes: the caller's operator, or the top of the workspace
+  // (it never exceeds the records emitted, nor max(M, |keep|) when a top-M cut
+  // is asked for)
+  auto place_output = [&](unsigned long long records) -> int {
+    if (c.out.to_arena) {
+      unsigned long long bound = records;
+      if (want_select)
+        bound = std::min<unsigned long long>(
+            bound, (unsigned long long)std::max<long long>((long long)tr->max_strings, n_keep));
+      const size_t n = (size_t)std::max<unsigned long long>(bound, 1);
+      uint64_t* ox = (uint64_t*)ar->take_top(n * 8 * W);
+      uint64_t* oz = (uint64_t*)ar->take_top(n * 8 * W);
+      void* oc = ar->take_top(n * (c.out.f32 ? 8 : 16));
+      if (ar->short_) return PAULI_EWORKSPACE;
+      c.out.arena_op.W = W;
+      c.out.arena_op.f32 = c.out.f32;
+      c.out.arena_op.canon = 1;
+      c.out.arena_op.n = 0;
+      c.out.arena_op.cap = (int64_t)n;
+      c.out.arena_op.x = ox;
+      c.out.arena_op.z = oz;
+      c.out.arena_op.c = oc;
+      wa.ox = ox;
+      wa.oz = oz;
+      wa.oc = oc;
+      wa.ocap = (int64_t)n;
+    } else {
+      pauli_op* o = c.out.user;
+      wa.ox = o->x;
+      wa.oz = o->z;
+      wa.oc = o->coef;
+      wa.ocap = o->capacity;
+    }
+    ma.ox = wa.ox;
+    ma.oz = wa.oz;
+    ma.oc = wa.oc;
+    ma.ocap = wa.ocap;
+    ma.out_f32 = wa.out_f32;
+    return PAULI_OK;
+  };
+  // Nothing is selected after a plain merge without a top-M cut: it writes the
+  // output itself (k_merge's OUT).  Direct merges of more buckets than run at
+  // once keep the small variant with its deferral list.
+  bool final_merge = !want_select && c.mode == M_PLAIN;
   uint32_t nbk = 0;  // buckets written so far
   int npass = 1;
   auto merge_common = [&]() {
@@ -718,7 +774,14 @@ int Engine::run(Call& c) {
     ma.tv = tv;
     ma.nbins_log = F;
     ma.digit_shift = F;
-    if (nb <= MERGE_ONE_WAVE) {
+    final_merge = final_merge && nb <= MERGE_ONE_WAVE;
+    if (final_merge) {
+      TRY(place_output((unsigned long long)nterm_rec));
+      ma.look = look;
+      ma.hctl = pinned ? hctl : nullptr;
+      LAUNCH("k_merge", (k_merge<W, F32, MERGE_THREADS, merge_cap<W>(), MERGE_GRID, true, true>),
+             nb, MERGE_THREADS, ma);
+    } else if (nb <= MERGE_ONE_WAVE) {
       // every bucket has a CU: the full-size variant takes them all at once
       LAUNCH("k_merge", (k_merge<W, F32, MERGE_THREADS, merge_cap<W>(), MERGE_GRID, true>), nb,
              MERGE_THREADS, ma);
@@ -796,9 +859,17 @@ int Engine::run(Call& c) {
       ma.nbins_log = append_F;
       ma.digit_shift = append_F;
       nbk = 1u << append_F;
-      LAUNCH("k_merge", (k_merge<W, F32, MERGE_THREADS, merge_cap<W>(), MERGE_GRID>), nbk,
-             MERGE_THREADS, ma);
       pe_all = rec_bound;
+      if (final_merge) {
+        TRY(place_output(pe_all));
+        ma.look = look;
+        ma.hctl = pinned ? hctl : nullptr;
+        LAUNCH("k_merge", (k_merge<W, F32, MERGE_THREADS, merge_cap<W>(), MERGE_GRID, false, true>),
+               nbk, MERGE_THREADS, ma);
+      } else {
+        LAUNCH("k_merge", (k_merge<W, F32, MERGE_THREADS, merge_cap<W>(), MERGE_GRID>), nbk,
+               MERGE_THREADS, ma);
+      }
     } else {
     // 2^nbl hash bins per pass: NBINS_LOG while the call fits one pass,
     // NBINS_LOG_MP (twice the records per pass) when it needs several, and
@@ -948,6 +1019,7 @@ int Engine::run(Call& c) {
     uint32_t* const* ccnt = b2.ccnt;
 
     merge_common();
+    if (final_merge) TRY(place_output(pe_all));
     ma.bin_base = bin_base;
     ma.recs = recs;
     ma.rsrc_wide = rsrc_wide;
@@ -1047,7 +1119,9 @@ int Engine::run(Call& c) {
           }
           pass_bits++;
           done = false;
-          TRY(zero_u32(hist0, (size_t)HREP * SEL0_BINS));  // the earlier passes' merges filled it
+          // the earlier passes' merges filled the histogram and wrote rows
+          TRY(zero_u32(hist0, (size_t)HREP * SEL0_BINS));
+          TRY(zero_u32(&dctl->out_total, 2));
           break;
         }
         int g_log = 4;
@@ -1079,6 +1153,21 @@ int Engine::run(Call& c) {
         // takes every bucket.
         constexpr int SCAP = small_merge_cap<W, F32>();
         const unsigned int big = hctl->maxg[g_log];
+        if (final_merge) {
+          ma.look = look;
+          ma.hctl = pinned && npass == 1 ? hctl : nullptr;
+          if (big <= (unsigned int)SCAP)
+            LAUNCH("k_merge_small",
+                   (k_merge<W, F32, MERGE_SMALL_THREADS, SCAP, MERGE_SMALL, false, true>), nb_pass,
+                   MERGE_SMALL_THREADS, ma);
+          else
+            LAUNCH("k_merge",
+                   (k_merge<W, F32, MERGE_THREADS, merge_cap<W>(), MERGE_GRID, false, true>),
+                   nb_pass, MERGE_THREADS, ma);
+          nbk += nb_pass;
+          u_off += pe;
+          continue;
+        }
         ma.defer = b1.defer;
         if (big <= (unsigned int)SCAP) {
           LAUNCH("k_merge_small", (k_merge<W, F32, MERGE_SMALL_THREADS, SCAP, MERGE_SMALL>),
@@ -1131,8 +1220,12 @@ int Engine::run(Call& c) {
     return write_empty();
   }
 
-  // ----- Lanczos: b_n from the untruncated sum, then divide and filter -------
+  const int nchunk = (int)((nbk + SEL_CHUNK - 1) / SEL_CHUNK);
   const double lanczos_floor_b = 1e-13 * (c.b_prev > 1.0 ? c.b_prev : 1.0);
+  if (final_merge) {
+    TRY(ma.hctl ? wait_ctl() : read_ctl());
+  } else {
+  // ----- Lanczos: b_n from the untruncated sum, then divide and filter -------
   if (c.mode == M_LANCZOS) {
     const int nblk = (int)std::min<uint32_t>((nbk + 3) / 4, NORM_BLOCKS);
     if (c.ts)
@@ -1168,7 +1261,6 @@ int Engine::run(Call& c) {
   }
 
   // ----- top-M threshold, output offsets and write, decided on the device ---
-  const int nchunk = (int)((nbk + SEL_CHUNK - 1) / SEL_CHUNK);
   Sel2Args s2;
   memset(&s2, 0, sizeof(s2));
   s2.b_ubase = b_ubase;
@@ -1216,50 +1308,15 @@ int Engine::run(Call& c) {
     LAUNCH("k_sel_narrow", (k_sel_narrow<W>), nsel, 1024, s2);
   }
 
-  WriteArgs wa;
-  memset(&wa, 0, sizeof(wa));
   wa.b_ubase = b_ubase;
   wa.b_slots = b_slots;
   wa.b_obase = b_obase;
   wa.uk = uk;
   wa.uc = uc;
-  wa.keep_mk = keep_mk;
-  wa.n_keep = (int)n_keep;
-  wa.ctl = dctl;
-  wa.out_f32 = c.out.f32;
-  if (c.out.to_arena) {
-    // the output never exceeds the records emitted, nor max(M, |keep|) when
-    // a top-M cut is asked for
-    unsigned long long bound = pe_all;
-    if (want_select)
-      bound = std::min<unsigned long long>(
-          bound, (unsigned long long)std::max<long long>((long long)tr->max_strings, n_keep));
-    const size_t n = (size_t)std::max<unsigned long long>(bound, 1);
-    uint64_t* ox = (uint64_t*)ar->take_top(n * 8 * W);
-    uint64_t* oz = (uint64_t*)ar->take_top(n * 8 * W);
-    void* oc = ar->take_top(n * (c.out.f32 ? 8 : 16));
-    if (ar->short_) return PAULI_EWORKSPACE;
-    c.out.arena_op.W = W;
-    c.out.arena_op.f32 = c.out.f32;
-    c.out.arena_op.canon = 1;
-    c.out.arena_op.n = 0;
-    c.out.arena_op.cap = (int64_t)n;
-    c.out.arena_op.x = ox;
-    c.out.arena_op.z = oz;
-    c.out.arena_op.c = oc;
-    wa.ox = ox;
-    wa.oz = oz;
-    wa.oc = oc;
-    wa.ocap = (int64_t)n;
-  } else {
-    pauli_op* o = c.out.user;
-    wa.ox = o->x;
-    wa.oz = o->z;
-    wa.oc = o->coef;
-    wa.ocap = o->capacity;
-  }
+  TRY(place_output(pe_all));
   LAUNCH("k_write_out", (k_write_out<W>), nchunk, 256, wa, nbk);
   TRY(pinned ? wait_ctl() : read_ctl());
+  }
   if (direct && (hctl->unsorted || hctl->overflow)) {
     // a term out of canonical order (the buckets were left empty), or strings
     // crowded into one bucket beyond the merge's capacity: redo by emission,

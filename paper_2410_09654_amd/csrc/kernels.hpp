@@ -672,12 +672,15 @@ __global__ __launch_bounds__(SC_COLS * SC_NSEG) void k_scan_cols(uint32_t* count
 template <int NBL>
 __global__ __launch_bounds__(1024) void k_scan(uint32_t* counts, int rows, uint32_t* bin_total,
                                                uint32_t* bin_base, Ctl* ctl,
+                                               unsigned long long* look,
                                                unsigned long long spec_cap,
                                                unsigned int merge_cap) {
   static_assert(SC_COLS * SC_NSEG == 1024, "one block size for both parts");
   constexpr int NB = 1 << NBL;
   constexpr int BPT = NB / 1024;
   static_assert(BPT * 1024 == NB, "every thread owns whole bins");
+  // clears a look-back state per bin, for merges that follow (nullable)
+  if (look && threadIdx.x < SC_COLS) look[blockIdx.x * SC_COLS + threadIdx.x] = 0ull;
   scan_cols(counts, rows, bin_total, ctl, NB);
   if (!last_block(&ctl->ticket[0])) return;
   __shared__ unsigned long long tmp[17];
@@ -903,7 +906,68 @@ struct MergeArgs {
   uint32_t* defer;  // buckets above the small variant's capacity (nullptr: none deferred)
   Ctl* ctl;
   TermView tv;      // direct merges: the canonical terms and their bucket runs
+  // final merges (nothing to select): the output operator, the look-back
+  // states of this launch's buckets (zero at the start), and the host's copy of
+  // the control block, written by the last launch of the call
+  unsigned long long* look;
+  uint64_t* ox;
+  uint64_t* oz;
+  void* oc;
+  int64_t ocap;
+  int out_f32;
+  Ctl* hctl;
 };
+
+// Look-back: the number of output rows before bucket j of a launch, from the
+// states of the buckets below it.  A state is 0 until the bucket has counted
+// its rows, then LB_SUM | rows, and LB_TOTAL | (rows up to and including the
+// bucket) once its own look-back is done; bucket 0 starts from `base`.  Buckets
+// are numbered in the order in which their blocks draw them, so every bucket
+// waited for belongs to a block that is already running, and no block waits
+// before it has published its own count: the lowest unfinished bucket waits
+// for nothing, and every wait ends.  Called by one whole wave.
+constexpr unsigned long long LB_SUM = 1ull << 62, LB_TOTAL = 2ull << 62, LB_VALUE = LB_SUM - 1ull;
+DEV unsigned long long look_back(unsigned long long* look, uint32_t j, uint32_t rows,
+                                 unsigned long long base) {
+  const int lane = threadIdx.x & 63;
+  if (j == 0) {
+    if (lane == 0) st_agent(&look[0], LB_TOTAL | (base + rows));
+    return base;
+  }
+  if (lane == 0) st_agent(&look[j], LB_SUM | (unsigned long long)rows);
+  unsigned long long before = 0;
+  for (int64_t hi = (int64_t)j - 1;; hi -= 64) {
+    const int64_t i = hi - lane;
+    unsigned long long w = LB_TOTAL;  // (below bucket 0)
+    uint64_t m;
+    for (;;) {
+      if (i >= 0) w = __hip_atomic_load(&look[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint64_t none = __ballot(w == 0ull);
+      m = __ballot((w & LB_TOTAL) != 0ull);
+      // every bucket down to the nearest total has published
+      if (!(none & (m ? (m & (~m + 1ull)) - 1ull : ~0ull))) break;
+      __builtin_amdgcn_s_sleep(1);
+    }
+    const int last = m ? __builtin_ctzll(m) : 63;
+    unsigned long long v = lane <= last ? (w & LB_VALUE) : 0ull;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+    before += v;
+    if (m) break;
+  }
+  if (lane == 0) st_agent(&look[j], LB_TOTAL | (before + rows));
+  return before;
+}
+// The control block to the host's pinned copy: the host reads it after it has
+// waited for the stream, with no copy of its own.  Called by a whole block, all
+// of whose writes to the block lie before it.
+DEV void publish(const Ctl* ctl, Ctl* hctl) {
+  __syncthreads();
+  if (!hctl) return;
+  const uint32_t* src = reinterpret_cast<const uint32_t*>(ctl);
+  uint32_t* dst = reinterpret_cast<uint32_t*>(hctl);
+  for (uint32_t i = threadIdx.x; i < sizeof(Ctl) / 4; i += blockDim.x) dst[i] = src[i];
+}
 
 template <int W>
 DEV bool keep_lookup(const Key<W>* keep, int n, const Key<W>& mk) {
@@ -998,7 +1062,12 @@ DEV void merge_full_rank(Key<W>* mk, uint32_t* sx, RecV<F32>* sv, uint32_t n, in
 enum MergeKind : int { MERGE_GRID = 0, MERGE_SMALL = 1, MERGE_LIST = 2 };
 // DIRECT: the records of bucket j are the j-th runs of the canonical terms
 // of a.tv (g_log = 0, no pass bits), read in place; source id = term group.
-template <int W, bool F32, int THREADS, int CAP, int MODE, bool DIRECT = false>
+// OUT: nothing is selected afterwards, so every survivor is an output row and
+// the block writes its strings to the output itself, at the row that the
+// look-back over the earlier buckets gives (no merged copy, no second pass to
+// move it: OUT_US).  Not with MERGE_LIST, and MERGE_SMALL only where every
+// bucket fits.
+template <int W, bool F32, int THREADS, int CAP, int MODE, bool DIRECT = false, bool OUT = false>
 __global__ __launch_bounds__(THREADS)
 __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(MergeArgs a) {
   constexpr bool SMALL = MODE == MERGE_SMALL;
@@ -1032,6 +1101,33 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
   __shared__ uint64_t hmask[NHW];  // bit p: sorted position p starts a run of equal keys
 
   const int tid = threadIdx.x;
+  // OUT: the first output row of bucket j with `rows` rows; the last bucket's
+  // block also writes the total and, when asked, the host's control block
+  __shared__ unsigned long long s_row;
+  auto finish = [&](const uint32_t j, const uint32_t rows) -> unsigned long long {
+    if constexpr (OUT) {
+      if (tid < 64) {
+        const unsigned long long r = look_back(a.look, j, rows, a.ctl->out_total);
+        if (tid == 0) {
+          s_row = r;
+          if (j == gridDim.x - 1) {
+            a.ctl->out_total = r + rows;
+            a.ctl->surv_total = r + rows;
+            if (!a.use_eps) a.ctl->u_unique = r + rows;
+            a.ctl->sel_mode = 0;  // S_ALL
+            st_agent(&a.ctl->ticket[2], 0u);
+          }
+        }
+      }
+      __syncthreads();
+      if (j == gridDim.x - 1) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        publish(a.ctl, a.hctl);
+      }
+      return s_row;
+    }
+    return 0ull;
+  };
   auto bucket = [&](const uint32_t j) {
   const uint32_t gb = a.bucket_off + j;
   uint32_t b0, b1;
@@ -1099,6 +1195,14 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
     }
     return v;
   };
+  if constexpr (OUT) {
+    if (n > (uint32_t)CAP) {
+      if (tid == 0) atomicOr(&a.ctl->overflow, 1u);
+      __builtin_amdgcn_s_waitcnt(0);
+      finish(j, 0u);
+      return;
+    }
+  }
   if (n > (uint32_t)CAP) {
     if (SMALL) {  // left to the full-size variant
       if (tid == 0) a.defer[atomicAdd(&a.ctl->ndefer, 1u)] = j;
@@ -1264,7 +1368,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
   __syncthreads();
   // keys, sources and values in sorted order; the digit counts become the
   // level-0 |c|^2 histogram (16-bit counters, two per word)
-  if (a.mode == M_PLAIN)
+  if (!OUT && a.mode == M_PLAIN)
     for (int i = tid; i < NDIGITS; i += THREADS) h0[i] = 0u;
 #pragma unroll
   for (int k = 0; k < PER; k++) {
@@ -1459,7 +1563,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
         if (a.mode != M_LANCZOS) {
           // the length cap was applied when the records were emitted
           if (a.use_eps && !(weight2(v) >= a.eps2)) surv = false;
-          if (surv) {
+          if (!OUT && surv) {
             const bool isk = a.n_keep ? keep_lookup<W>(keep, a.n_keep, mk[p]) : false;
             if (isk) kc++;
             else {
@@ -1486,6 +1590,30 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
   uint32_t tot_cnt;
   {
     uint32_t o = block_exclusive_scan((uint32_t)__popc(smask), scan_tmp, &tot_cnt);
+    if constexpr (OUT) {
+      if (tid == 0 && a.use_eps && (s_pk & 0xFFFFu))
+        atomicAdd(&a.ctl->u_unique, (unsigned long long)(s_pk & 0xFFFFu));
+      __builtin_amdgcn_s_waitcnt(0);
+      const unsigned long long row = finish(j, tot_cnt);
+      if (row + tot_cnt > (unsigned long long)a.ocap) return;  // the host reports the size
+#pragma unroll
+      for (int k = 0; k < PER; k++)
+        if ((smask >> k) & 1u) {
+          const size_t r = (size_t)row + o;
+          const Key<W> raw = unmix_key<W>(mk[tid * per + k]);
+#pragma unroll
+          for (int w = 0; w < W; w++) {
+            a.ox[(size_t)w * a.ocap + r] = raw.w[w];
+            a.oz[(size_t)w * a.ocap + r] = raw.w[W + w];
+          }
+          if (a.out_f32)
+            reinterpret_cast<float2*>(a.oc)[r] = make_float2((float)fv[k].x, (float)fv[k].y);
+          else
+            reinterpret_cast<double2*>(a.oc)[r] = fv[k];
+          o++;
+        }
+      return;
+    }
     // U keeps order keys; raw strings are restored where needed
 #pragma unroll
     for (int k = 0; k < PER; k++)
@@ -1514,7 +1642,14 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
     a.b_unique[gb] = tot_nzu;
   }
   };
-  if constexpr (MODE != MERGE_LIST) {
+  if constexpr (OUT) {
+    static_assert(MODE != MERGE_LIST, "buckets are numbered as they are drawn");
+    __shared__ uint32_t s_j;
+    if (tid == 0)
+      s_j = __hip_atomic_fetch_add(&a.ctl->ticket[2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    bucket(s_j);
+  } else if constexpr (MODE != MERGE_LIST) {
     bucket(blockIdx.x);
   } else {
     const uint32_t nd = *reinterpret_cast<volatile unsigned int*>(&a.ctl->ndefer);
@@ -2182,6 +2317,8 @@ struct PrepArgs {
   uint32_t* hist0;
   uint32_t* cursor;  // append mode: n_cursor <= 1024 bucket cursors to clear
   int n_cursor;
+  unsigned long long* look;  // n_look <= 1024 look-back states to clear
+  int n_look;
   Ctl* ctl;
 };
 template <int W>
@@ -2204,6 +2341,7 @@ __global__ __launch_bounds__(1024) void k_prep(PrepArgs a) {
   for (uint32_t q = t; q < sizeof(Ctl) / 4; q += 1024) reinterpret_cast<uint32_t*>(a.ctl)[q] = 0u;
   for (int q = t; q < SITES + 2; q += 1024) cnt[q] = 0u;
   if (t < a.n_cursor) a.cursor[t] = 0u;
+  if (t < a.n_look) a.look[t] = 0ull;
   if (t == 0) {
     span = 0;
     bad = 0;

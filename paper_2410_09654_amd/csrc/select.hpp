@@ -102,17 +102,6 @@ struct PlanArgs {
   Ctl* hctl;                 // the host's copy (nullable: the host reads ctl itself)
 };
 
-// The control block to the host's pinned copy (one block of 1024 threads, all
-// of whose writes to it lie before a barrier): the host reads it after it has
-// waited for the stream, with no copy of its own.
-DEV void publish(const Ctl* ctl, Ctl* hctl) {
-  __syncthreads();
-  if (!hctl) return;
-  const uint32_t* src = reinterpret_cast<const uint32_t*>(ctl);
-  uint32_t* dst = reinterpret_cast<uint32_t*>(hctl);
-  for (uint32_t i = threadIdx.x; i < sizeof(Ctl) / 4; i += 1024) dst[i] = src[i];
-}
-
 // Eight consecutive words p[b0 .. b0 + 8) (zero past nb), as two 16-byte
 // loads when the eight lie inside the array (b0 is a multiple of 8 and the
 // arena aligns the tables to 256 bytes).
