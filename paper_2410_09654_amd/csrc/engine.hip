@@ -1172,7 +1172,7 @@ int Engine::run(Call& c) {
         if (big <= (unsigned int)SCAP) {
           LAUNCH("k_merge_small", (k_merge<W, F32, MERGE_SMALL_THREADS, SCAP, MERGE_SMALL>),
                  nb_pass, MERGE_SMALL_THREADS, ma);
-        } else if (pe <= (unsigned long long)nb_pass * (SCAP * 7 / 8)) {
+        } else if (pe <= (unsigned long long)nb_pass * (SCAP * 9 / 10)) {
           LAUNCH("k_merge_small", (k_merge<W, F32, MERGE_SMALL_THREADS, SCAP, MERGE_SMALL>),
                  nb_pass, MERGE_SMALL_THREADS, ma);
           LAUNCH("k_merge_deferred", (k_merge<W, F32, MERGE_THREADS, merge_cap<W>(), MERGE_LIST>),
@@ -1308,6 +1308,7 @@ int Engine::run(Call& c) {
     LAUNCH("k_sel_narrow", (k_sel_narrow<W>), nsel, 1024, s2);
   }
 
+  wa.b_keep = b_keep;
   wa.b_ubase = b_ubase;
   wa.b_slots = b_slots;
   wa.b_obase = b_obase;

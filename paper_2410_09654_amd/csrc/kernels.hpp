@@ -920,7 +920,7 @@ struct MergeArgs {
 
 // Look-back: the number of output rows before bucket j of a launch, from the
 // states of the buckets below it.  A state is 0 until the bucket has counted
-// its rows, then LB_SUM | rows, and LB_TOTAL | (rows up to and including the
+// its rows, then LB_SUM | rows (set by the caller), and LB_TOTAL | (rows up to and including the
 // bucket) once its own look-back is done; bucket 0 starts from `base`.  Buckets
 // are numbered in the order in which their blocks draw them, so every bucket
 // waited for belongs to a block that is already running, and no block waits
@@ -930,23 +930,18 @@ constexpr unsigned long long LB_SUM = 1ull << 62, LB_TOTAL = 2ull << 62, LB_VALU
 DEV unsigned long long look_back(unsigned long long* look, uint32_t j, uint32_t rows,
                                  unsigned long long base) {
   const int lane = threadIdx.x & 63;
-  if (j == 0) {
-    if (lane == 0) st_agent(&look[0], LB_TOTAL | (base + rows));
-    return base;
-  }
-  if (lane == 0) st_agent(&look[j], LB_SUM | (unsigned long long)rows);
-  unsigned long long before = 0;
-  for (int64_t hi = (int64_t)j - 1;; hi -= 64) {
+  unsigned long long before = j == 0 ? base : 0ull;
+  for (int64_t hi = (int64_t)j - 1; hi >= 0; hi -= 64) {
     const int64_t i = hi - lane;
-    unsigned long long w = LB_TOTAL;  // (below bucket 0)
+    unsigned long long w = i >= 0 ? 0ull : LB_TOTAL;  // (below bucket 0)
     uint64_t m;
     for (;;) {
-      if (i >= 0) w = __hip_atomic_load(&look[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (w == 0ull) w = __hip_atomic_load(&look[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const uint64_t none = __ballot(w == 0ull);
       m = __ballot((w & LB_TOTAL) != 0ull);
       // every bucket down to the nearest total has published
       if (!(none & (m ? (m & (~m + 1ull)) - 1ull : ~0ull))) break;
-      __builtin_amdgcn_s_sleep(1);
+      __builtin_amdgcn_s_sleep(8);
     }
     const int last = m ? __builtin_ctzll(m) : 63;
     unsigned long long v = lane <= last ? (w & LB_VALUE) : 0ull;
@@ -1001,14 +996,14 @@ DEV uint64_t key_window(const Key<W>& m, int shift) {
 
 // Rank of every record of the block inside its digit group by full
 // (mixed key, source id) comparison, used when two distinct keys of a group
-// share their 32 sort bits.  On entry mk/sx/sv hold the n records grouped by
-// digit (ascending); on return they are in (key, source id) order.
-template <int W, bool F32, int THREADS, int CAP>
-DEV void merge_full_rank(Key<W>* mk, uint32_t* sx, RecV<F32>* sv, uint32_t n, int shift) {
+// share their 32 sort bits.  On entry mk/sx hold the n records grouped by
+// digit (ascending) and id their source ids; on return mk/sx are in (key,
+// source id) order.
+template <int W, int THREADS, int CAP>
+DEV void merge_full_rank(Key<W>* mk, uint32_t* sx, const uint32_t* id, uint32_t n, int shift) {
   constexpr int PER = (CAP + THREADS - 1) / THREADS;
   Key<W> k[PER];
   uint32_t x[PER], pos[PER];
-  typename std::conditional<F32, float, double>::type vx[PER], vy[PER];
 #pragma unroll
   for (int q = 0; q < PER; q++) {
     const uint32_t p = threadIdx.x + q * THREADS;
@@ -1016,8 +1011,7 @@ DEV void merge_full_rank(Key<W>* mk, uint32_t* sx, RecV<F32>* sv, uint32_t n, in
     if (p < n) {
       k[q] = mk[p];
       x[q] = sx[p];
-      vx[q] = sv[p].x;
-      vy[q] = sv[p].y;
+      const uint32_t me = id[p];
       const uint32_t d = (uint32_t)(key_window<W>(k[q], shift) >> 32);
       // digit group [s0, s1): binary searches on the (ascending) digits
       uint32_t lo = 0, hi = p;
@@ -1036,7 +1030,7 @@ DEV void merge_full_rank(Key<W>* mk, uint32_t* sx, RecV<F32>* sv, uint32_t n, in
       }
       const uint32_t s1 = lo;
       uint32_t rank = 0;
-      for (uint32_t r = s0; r < s1; r++) rank += key_src_less<W>(mk[r], sx[r], k[q], x[q]) ? 1u : 0u;
+      for (uint32_t r = s0; r < s1; r++) rank += key_src_less<W>(mk[r], id[r], k[q], me) ? 1u : 0u;
       pos[q] = s0 + rank;
     }
   }
@@ -1047,8 +1041,6 @@ DEV void merge_full_rank(Key<W>* mk, uint32_t* sx, RecV<F32>* sv, uint32_t n, in
     if (p < n) {
       mk[pos[q]] = k[q];
       sx[pos[q]] = x[q];
-      sv[pos[q]].x = vx[q];
-      sv[pos[q]].y = vy[q];
     }
   }
   __syncthreads();
@@ -1065,7 +1057,7 @@ enum MergeKind : int { MERGE_GRID = 0, MERGE_SMALL = 1, MERGE_LIST = 2 };
 // OUT: nothing is selected afterwards, so every survivor is an output row and
 // the block writes its strings to the output itself, at the row that the
 // look-back over the earlier buckets gives (no merged copy, no second pass to
-// move it: OUT_US).  Not with MERGE_LIST, and MERGE_SMALL only where every
+// move it: 19 M records into 13 M strings 386 + 278 -> 504 us). Not with MERGE_LIST, and MERGE_SMALL only where every
 // bucket fits.
 template <int W, bool F32, int THREADS, int CAP, int MODE, bool DIRECT = false, bool OUT = false>
 __global__ __launch_bounds__(THREADS)
@@ -1074,20 +1066,29 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
   using V = RecV<F32>;
   constexpr int PER = (CAP + THREADS - 1) / THREADS;
   constexpr int DPT = NDIGITS / THREADS;
+  static_assert(CAP <= NDIGITS, "the source ids of a bucket fit the digit table");
   static_assert(SEL0_BINS == 2 * NDIGITS,
                 "digit counts and the |c|^2 histogram (16-bit counters, two per word) share LDS");
   // Sort: a counting sort on the DIGIT_BITS key bits after the bucket bits,
   // then the rank of every record inside its digit group by a 64-bit sort
   // word (the next 32 key bits, then the source id), read from `swd` (which
-  // aliases sv until the values are written).  mk / sx / sv then hold the
-  // records in sorted order; dh holds the digit counts and starts, then the
+  // aliases mk until the keys are written).  mk / sx then hold the keys and
+  // SX words (group, position in the bucket) in sorted order; the values stay
+  // in sv where their records lie in the bucket, so each record is read from
+  // memory once, key and value together.  (Values written in sorted order were
+  // read a second time for it: 7 us of a block's 33 us, and in direct merges,
+  // whose values lie in arrays of their own, from memory: 4.82 -> 3.59 ms for
+  // 137 M term strings, with the terms' pointers in LDS.)  dh holds the digit counts and starts, then the
   // level-0 histogram of |c|^2.  Two distinct keys of one digit group with
   // equal sort bits show up as adjacent entries with equal windows but
   // different keys; the block then ranks by full keys (merge_full_rank).
   __shared__ Key<W> mk[CAP];
   __shared__ __align__(16) V sv[CAP];
-  static_assert(sizeof(V) >= sizeof(uint64_t), "sort words alias the values");
-  uint64_t* const swd = reinterpret_cast<uint64_t*>(sv);
+  static_assert(sizeof(Key<W>) >= sizeof(uint64_t), "sort words alias the keys");
+  uint64_t* const swd = reinterpret_cast<uint64_t*>(mk);
+  // SX word: source group on top, a flag for strings above the length cap
+  // (direct merges), the record's position in the bucket
+  constexpr uint32_t SX_LONG = 1u << (GROUP_SHIFT - 1), SX_POS = SX_LONG - 1u;
   __shared__ uint32_t sx[CAP];
   __shared__ int s_collide;
   __shared__ uint32_t s_pk;
@@ -1097,10 +1098,32 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
   __shared__ int s_gk[MAX_GROUPS], s_ak[MAX_GROUPS];
   __shared__ double2 s_al[MAX_GROUPS];
   __shared__ uint32_t sbb[17];
+  __shared__ int s_kr[2];
   constexpr int NHW = (CAP + 63) / 64;
   __shared__ uint64_t hmask[NHW];  // bit p: sorted position p starts a run of equal keys
 
   const int tid = threadIdx.x;
+  struct TermDesc {
+    const uint64_t *x, *z;
+    const void* c;
+    int64_t cap;
+    uint32_t group;
+    int f32;
+  };
+  __shared__ TermDesc s_term[DIRECT ? MAX_TERMS : 1];
+  if constexpr (DIRECT) {
+    if (tid < a.tv.n_terms) {
+      TermDesc d;
+      d.x = a.tv.tx[tid];
+      d.z = a.tv.tz[tid];
+      d.c = a.tv.tc[tid];
+      d.cap = a.tv.tcap[tid];
+      d.group = a.tv.tgroup[tid];
+      d.f32 = a.tv.tf32[tid];
+      s_term[tid] = d;
+    }
+    __syncthreads();
+  }
   // OUT: the first output row of bucket j with `rows` rows; the last bucket's
   // block also writes the total and, when asked, the host's control block
   __shared__ unsigned long long s_row;
@@ -1135,7 +1158,16 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
   // first position in the bucket (tpre, ascending over the terms)
   uint32_t tst[DIRECT ? MAX_TERMS : 1], tpre[DIRECT ? MAX_TERMS : 1];
   if constexpr (DIRECT) {
+    // (all bounds loaded before any is used: a load per term and branch made a
+    // chain of up to six reads)
     const uint32_t stride = (1u << a.tv.F) + 1u;
+    uint32_t s0[MAX_TERMS], s1[MAX_TERMS];
+#pragma unroll
+    for (int t = 0; t < MAX_TERMS; t++) {
+      const uint32_t* bt = a.tv.bounds + (size_t)min(t, a.tv.n_terms - 1) * stride + j;
+      s0[t] = bt[0];
+      s1[t] = bt[1];
+    }
     b0 = 0u;
     b1 = 0u;
 #pragma unroll
@@ -1143,11 +1175,10 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
       tst[t] = 0u;
       tpre[t] = 0xFFFFFFFFu;
       if (t < a.tv.n_terms) {
-        const uint32_t s0 = a.tv.bounds[t * stride + j], s1 = a.tv.bounds[t * stride + j + 1];
-        tst[t] = s0;
+        tst[t] = s0[t];
         tpre[t] = b1 - b0;
-        b0 += s0;
-        b1 += s1;
+        b0 += s0[t];
+        b1 += s1[t];
       }
     }
     if (a.ctl->unsorted) b0 = b1 = 0u;  // the call is redone by emission
@@ -1163,33 +1194,45 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
   }
   const uint32_t n = b1 - b0;
   const unsigned long long ub = a.u_off + b0;
-  // direct merges: term, group and index of bucket position i (the last
-  // term whose run starts at or before i; empty runs are passed over)
+  // direct merges: where the string at bucket position i lies (in the last
+  // term whose run starts at or before i; empty runs are passed over), from the
+  // terms' copies in LDS (indexed by lane, the kernel arguments would be read
+  // from memory before the string)
   struct TermPos {
-    int t;
-    int64_t e;
+    const uint64_t *x, *z;
+    const void* c;
+    int64_t cap, e;
+    uint32_t group;
+    int f32;
   };
   auto term_pos = [&](uint32_t i) -> TermPos {
-    TermPos r{0, 0};
+    int t = 0;
+    int64_t e = 0;
 #pragma unroll
-    for (int t = 0; t < (DIRECT ? MAX_TERMS : 1); t++)
-      if (i >= tpre[t]) {
-        r.t = t;
-        r.e = (int64_t)tst[t] + (int64_t)(i - tpre[t]);
+    for (int u = 0; u < (DIRECT ? MAX_TERMS : 1); u++)
+      if (i >= tpre[u]) {
+        t = u;
+        e = (int64_t)tst[u] + (int64_t)(i - tpre[u]);
       }
-    return r;
+    const TermDesc& d = s_term[t];
+    return TermPos{d.x, d.z, d.c, d.cap, e, d.group, d.f32};
   };
-  auto term_key = [&](const TermPos& q) -> Key<W> {
-    return mix_key<W>(load_raw<W>(a.tv.tx[q.t], a.tv.tz[q.t], a.tv.tcap[q.t], q.e));
+  // direct merges apply the length cap here (emission applies it to records
+  // before they reach a bucket)
+  const int cap_len = DIRECT && a.mode == M_PLAIN ? a.max_len : 0;
+  auto term_src = [&](uint32_t group, const Key<W>& raw) -> uint32_t {
+    const uint32_t g = group << GROUP_SHIFT;
+    return cap_len > 0 && key_length<W>(raw) > cap_len ? g | SX_LONG : g;
   };
+  auto term_raw = [&](const TermPos& q) -> Key<W> { return load_raw<W>(q.x, q.z, q.cap, q.e); };
   auto term_val = [&](const TermPos& q) -> V {
     V v;
-    if (a.tv.tf32[q.t]) {
-      const float2 f = reinterpret_cast<const float2*>(a.tv.tc[q.t])[q.e];
+    if (F32 || q.f32) {
+      const float2 f = reinterpret_cast<const float2*>(q.c)[q.e];
       v.x = f.x;
       v.y = f.y;
     } else {
-      const double2 d = reinterpret_cast<const double2*>(a.tv.tc[q.t])[q.e];
+      const double2 d = reinterpret_cast<const double2*>(q.c)[q.e];
       v.x = d.x;
       v.y = d.y;
     }
@@ -1197,8 +1240,11 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
   };
   if constexpr (OUT) {
     if (n > (uint32_t)CAP) {
-      if (tid == 0) atomicOr(&a.ctl->overflow, 1u);
-      __builtin_amdgcn_s_waitcnt(0);
+      if (tid == 0) {
+        atomicOr(&a.ctl->overflow, 1u);
+        __builtin_amdgcn_s_waitcnt(0);
+        if (j > 0) st_agent(&a.look[j], LB_SUM);
+      }
       finish(j, 0u);
       return;
     }
@@ -1222,12 +1268,14 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
   const int F = a.nbins_log + a.pass_bits;
   const uint32_t ibits = (uint32_t)(F - 3);
   // Per record the digit, its rank among the digit's records, the source id
-  // and the 32 sort bits stay in registers, and at W = 1 the order key; the
-  // value (and a wider key) is read a second time, from cache, for the
-  // sorted write, which keeps the kernel spill-free at 8 waves per SIMD.
+  // and the 32 sort bits stay in registers, and at W = 1 the order key; a
+  // wider key is read a second time, from cache, for the sorted write, which
+  // keeps the kernel spill-free at 8 waves per SIMD.
   constexpr bool HOLD_KEY = W == 1;
   uint32_t dig[PER], rnk[PER], rsx[PER], swl[PER];
   uint64_t rkw[HOLD_KEY ? 2 * W : 1][PER];
+  typename std::conditional<F32, float, double>::type rvx[HOLD_KEY ? PER : 1],
+      rvy[HOLD_KEY ? PER : 1];
   // one-word keys: the record loads are issued before the shared-memory
   // set-up, so that their latency overlaps it
   if constexpr (HOLD_KEY) {
@@ -1239,10 +1287,16 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
         Key<W> m;
         if constexpr (DIRECT) {
           const TermPos q = term_pos(i);
-          m = term_key(q);
-          rsx[k] = a.tv.tgroup[q.t] << GROUP_SHIFT;
+          m = term_raw(q);  // (mixed below, when it has arrived)
+          rsx[k] = q.group;
+          const V v = term_val(q);
+          rvx[k] = v.x;
+          rvy[k] = v.y;
         } else {
           m = recs[b0 + i].k;
+          const V v = recs[b0 + i].v;
+          rvx[k] = v.x;
+          rvy[k] = v.y;
           if (a.wide) rsx[k] = a.rsrc_wide[b0 + i];
         }
 #pragma unroll
@@ -1261,6 +1315,20 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
   if (tid == 0) {
     s_collide = 0;
     s_pk = 0u;
+  }
+  // the keep keys of this bucket: [s_kr[0], s_kr[1]) of the sorted keep set
+  // (mostly none, and then no string looks its key up)
+  if (!OUT && tid < 2 && a.n_keep) {
+    const Key<W>* keep = reinterpret_cast<const Key<W>*>(a.keep_mk);
+    const uint64_t first = ((uint64_t)a.pass_id << a.nbins_log) | ((uint64_t)j << a.g_log);
+    const uint64_t bound = first + (tid ? (1ull << a.g_log) : 0ull);
+    int lo = 0, hi = a.n_keep;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if ((F ? keep[mid].w[0] >> (64 - F) : 0ull) < bound) lo = mid + 1;
+      else hi = mid;
+    }
+    s_kr[tid] = lo;
   }
   __syncthreads();
 
@@ -1288,12 +1356,23 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
       if constexpr (HOLD_KEY) {
 #pragma unroll
         for (int q = 0; q < 2 * W; q++) m.w[q] = rkw[q][k];
+        sv[i].x = rvx[k];
+        sv[i].y = rvy[k];
+        if constexpr (DIRECT) {
+          rsx[k] = term_src(rsx[k], m);
+          m = mix_key<W>(m);
+#pragma unroll
+          for (int q = 0; q < 2 * W; q++) rkw[q][k] = m.w[q];
+        }
       } else if constexpr (DIRECT) {
         const TermPos q = term_pos(i);
-        m = term_key(q);
-        rsx[k] = a.tv.tgroup[q.t] << GROUP_SHIFT;
+        sv[i] = term_val(q);
+        m = term_raw(q);
+        rsx[k] = term_src(q.group, m);
+        m = mix_key<W>(m);
       } else {
         m = recs[pos].k;
+        sv[i] = recs[pos].v;
         if (a.wide) rsx[k] = a.rsrc_wide[pos];
       }
       if constexpr (!DIRECT) {
@@ -1366,7 +1445,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
     }
   }
   __syncthreads();
-  // keys, sources and values in sorted order; the digit counts become the
+  // keys and SX words in sorted order; the digit counts become the
   // level-0 |c|^2 histogram (16-bit counters, two per word)
   if (!OUT && a.mode == M_PLAIN)
     for (int i = tid; i < NDIGITS; i += THREADS) h0[i] = 0u;
@@ -1379,35 +1458,45 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
 #pragma unroll
         for (int q = 0; q < 2 * W; q++) m.w[q] = rkw[q][k];
         mk[fpos[k]] = m;
-        if constexpr (DIRECT) sv[fpos[k]] = term_val(term_pos(i));
-        else sv[fpos[k]] = recs[b0 + i].v;  // second read (cache)
       } else if constexpr (DIRECT) {
-        const TermPos q = term_pos(i);  // second read (cache)
-        mk[fpos[k]] = term_key(q);
-        sv[fpos[k]] = term_val(q);
+        mk[fpos[k]] = mix_key<W>(term_raw(term_pos(i)));  // second read (cache)
       } else {
-        const Rec<W, F32> r = recs[b0 + i];  // second read (cache)
-        mk[fpos[k]] = order_key(b0 + i, r.k);
-        sv[fpos[k]] = r.v;
+        mk[fpos[k]] = order_key(b0 + i, recs[b0 + i].k);  // second read (cache)
       }
-      sx[fpos[k]] = rsx[k];
+      sx[fpos[k]] = (rsx[k] & ~SX_POS & ~(DIRECT ? 0u : SX_LONG)) | i;
     }
   }
   __syncthreads();
 
   const Key<W>* keep = reinterpret_cast<const Key<W>*>(a.keep_mk);
+  const int kr0 = !OUT && a.n_keep ? s_kr[0] : 0, kr1 = !OUT && a.n_keep ? s_kr[1] : 0;
   // Fold the run [p, q) of equal keys: groups in ascending id, a SUM group
   // adds its contributions in ascending source index, then
   // acc = g0, acc = fl(acc + g1), ... after scaling each group by its alpha.
+  auto val = [&](uint32_t r) -> V { return sv[sx[r] & SX_POS]; };
   auto fold = [&](uint32_t p, uint32_t q, double2& out) -> bool {
+    if constexpr (DIRECT) {
+      // every entry of the run is a group of its own
+      double2 acc = make_double2(0.0, 0.0);
+      for (uint32_t r = p; r < q; r++) {
+        const uint32_t x = sx[r];
+        const int g = (int)(x >> GROUP_SHIFT);
+        const V v = sv[x & SX_POS];
+        const double2 gv = apply_alpha(s_ak[g], s_al[g], make_double2((double)v.x, (double)v.y));
+        acc = r == p ? gv : make_double2(acc.x + gv.x, acc.y + gv.y);
+      }
+      if (a.round32) acc = make_double2(round_to_f32(acc.x), round_to_f32(acc.y));
+      out = acc;
+      return !is_zero(acc);
+    }
     if (a.single) {
       // one group: the sequential sum of the run, then the group's alpha
       const int g = (int)(sx[p] >> GROUP_SHIFT);
-      const V v0 = sv[p];
+      const V v0 = val(p);
       double sr = (double)v0.x, si = (double)v0.y;
       uint32_t r = p + 1;
       for (; r + 4 <= q; r += 4) {
-        const V v1 = sv[r], v2 = sv[r + 1], v3 = sv[r + 2], v4 = sv[r + 3];
+        const V v1 = val(r), v2 = val(r + 1), v3 = val(r + 2), v4 = val(r + 3);
         sr = sr + (double)v1.x;
         si = si + (double)v1.y;
         sr = sr + (double)v2.x;
@@ -1418,7 +1507,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
         si = si + (double)v4.y;
       }
       for (; r < q; r++) {
-        const V v1 = sv[r];
+        const V v1 = val(r);
         sr = sr + (double)v1.x;
         si = si + (double)v1.y;
       }
@@ -1451,7 +1540,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
      for (int u = 0; u < FU; u++)
        if (r0 + u < q) {
          gx[u] = sx[r0 + u];
-         vv[u] = sv[r0 + u];
+         vv[u] = sv[gx[u] & SX_POS];
        }
 #pragma unroll
      for (int u = 0; u < FU; u++) {
@@ -1515,7 +1604,23 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
   __syncthreads();
   if (s_collide) {
     // rare: distinct keys with equal sort bits; rank again by full keys
-    merge_full_rank<W, F32, THREADS, CAP>(mk, sx, sv, n, a.digit_shift);
+    // (their source ids, from the records, in dh for the time being)
+    for (uint32_t p = tid; p < n; p += THREADS) {
+      const uint32_t i = sx[p] & SX_POS;
+      uint32_t id = sx[p] & ~SX_POS;
+      if constexpr (!DIRECT) {
+        if (a.wide) {
+          id = a.rsrc_wide[b0 + i];
+        } else {
+          const uint32_t small = (uint32_t)(recs[b0 + i].k.w[0] >> (64 - F));
+          id = ((small >> ibits) << GROUP_SHIFT) | (small & ((1u << ibits) - 1u));
+        }
+      }
+      dh[p] = id;
+    }
+    __syncthreads();
+    merge_full_rank<W, THREADS, CAP>(mk, sx, dh, n, a.digit_shift);
+    for (int i = tid; i < NDIGITS; i += THREADS) dh[i] = 0u;
     for (uint32_t r = 0; r < nround; r++) {
       const uint32_t p = r * THREADS + tid;
       const bool head = p < n && (p == 0 || !key_eq<W>(mk[p - 1], mk[p]));
@@ -1553,10 +1658,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
       }
       if (q > n) q = n;
       double2 v;
-      // direct merges apply the length cap here (emission applies it to
-      // records before they reach a bucket)
-      const bool too_long = DIRECT && a.mode == M_PLAIN && a.max_len > 0 &&
-                            key_length<W>(unmix_key<W>(mk[p])) > a.max_len;
+      const bool too_long = DIRECT && (sx[p] & SX_LONG);
       if (!too_long && fold(p, q, v)) {
         nzu++;
         bool surv = true;
@@ -1564,7 +1666,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
           // the length cap was applied when the records were emitted
           if (a.use_eps && !(weight2(v) >= a.eps2)) surv = false;
           if (!OUT && surv) {
-            const bool isk = a.n_keep ? keep_lookup<W>(keep, a.n_keep, mk[p]) : false;
+            const bool isk = kr1 > kr0 && keep_lookup<W>(keep + kr0, kr1 - kr0, mk[p]);
             if (isk) kc++;
             else {
               // 16-bit counters (a bucket holds < 2^16 records), two per word
@@ -1590,38 +1692,63 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
   uint32_t tot_cnt;
   {
     uint32_t o = block_exclusive_scan((uint32_t)__popc(smask), scan_tmp, &tot_cnt);
+    // OUT, FP64: the survivors' values and sorted positions go to LDS in output
+    // order (sv and sx have been read), so that neighbouring threads write
+    // neighbouring strings: 612 -> 579 us for 13 M strings (merged copies,
+    // written as whole records, gain nothing by it)
+    constexpr bool STAGE = OUT && !F32;
     if constexpr (OUT) {
-      if (tid == 0 && a.use_eps && (s_pk & 0xFFFFu))
-        atomicAdd(&a.ctl->u_unique, (unsigned long long)(s_pk & 0xFFFFu));
-      __builtin_amdgcn_s_waitcnt(0);
-      const unsigned long long row = finish(j, tot_cnt);
-      if (row + tot_cnt > (unsigned long long)a.ocap) return;  // the host reports the size
+      if (tid == 0) {
+        if (a.use_eps && (s_pk & 0xFFFFu))
+          atomicAdd(&a.ctl->u_unique, (unsigned long long)(s_pk & 0xFFFFu));
+        __builtin_amdgcn_s_waitcnt(0);  // counted before the bucket is known to be
+        if (j > 0) st_agent(&a.look[j], LB_SUM | (unsigned long long)tot_cnt);
+      }
+    }
+    if constexpr (STAGE) {
 #pragma unroll
       for (int k = 0; k < PER; k++)
         if ((smask >> k) & 1u) {
-          const size_t r = (size_t)row + o;
-          const Key<W> raw = unmix_key<W>(mk[tid * per + k]);
-#pragma unroll
-          for (int w = 0; w < W; w++) {
-            a.ox[(size_t)w * a.ocap + r] = raw.w[w];
-            a.oz[(size_t)w * a.ocap + r] = raw.w[W + w];
-          }
-          if (a.out_f32)
-            reinterpret_cast<float2*>(a.oc)[r] = make_float2((float)fv[k].x, (float)fv[k].y);
-          else
-            reinterpret_cast<double2*>(a.oc)[r] = fv[k];
+          sv[o].x = fv[k].x;
+          sv[o].y = fv[k].y;
+          sx[o] = tid * per + k;
           o++;
         }
+    }
+    auto each = [&](auto&& put) {
+      if constexpr (STAGE) {
+        __syncthreads();
+        for (uint32_t r = tid; r < tot_cnt; r += THREADS)
+          put(r, mk[sx[r]], make_double2((double)sv[r].x, (double)sv[r].y));
+      } else {
+#pragma unroll
+        for (int k = 0; k < PER; k++)
+          if ((smask >> k) & 1u) put(o++, mk[tid * per + k], fv[k]);
+      }
+    };
+    if constexpr (OUT) {
+      const unsigned long long row = finish(j, tot_cnt);
+      if (row + tot_cnt > (unsigned long long)a.ocap) return;  // the host reports the size
+      each([&](uint32_t q, const Key<W>& k, double2 v) {
+        const size_t r = (size_t)row + q;
+        const Key<W> raw = unmix_key<W>(k);
+#pragma unroll
+        for (int w = 0; w < W; w++) {
+          a.ox[(size_t)w * a.ocap + r] = raw.w[w];
+          a.oz[(size_t)w * a.ocap + r] = raw.w[W + w];
+        }
+        if (a.out_f32)
+          reinterpret_cast<float2*>(a.oc)[r] = make_float2((float)v.x, (float)v.y);
+        else
+          reinterpret_cast<double2*>(a.oc)[r] = v;
+      });
       return;
     }
     // U keeps order keys; raw strings are restored where needed
-#pragma unroll
-    for (int k = 0; k < PER; k++)
-      if ((smask >> k) & 1u) {
-        uk[o] = mk[tid * per + k];
-        uc[o] = fv[k];
-        o++;
-      }
+    each([&](uint32_t q, const Key<W>& k, double2 v) {
+      uk[q] = k;
+      uc[q] = v;
+    });
   }
   // the scan's barriers have ordered every histogram and s_pk update
   const uint32_t tot_kc = s_pk >> 16, tot_nzu = s_pk & 0xFFFFu;
@@ -2218,6 +2345,7 @@ __global__ __launch_bounds__(1024) void k_scan_buckets(const uint32_t* b_surv,
 }
 
 struct WriteArgs {
+  const uint32_t* b_keep;
   const uint32_t* b_ubase;
   const uint32_t* b_slots;
   const uint32_t* b_obase;

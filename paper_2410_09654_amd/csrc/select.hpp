@@ -365,6 +365,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
   WaveBuckets wb(a.b_ubase, a.b_slots, blockIdx.x * 16 + wv, gridDim.x * 16, a.nbk);
   for (uint32_t b, ub, ns; wb.next(b, ub, ns);) {
     uint32_t abv = 0, nc = 0;
+    // keys are read only in buckets that hold a string of the keep set
+    const int n_keep = a.n_keep && a.b_keep[b] ? a.n_keep : 0;
     // SB loads in flight per lane
     constexpr int SB = 4;
     for (uint32_t i00 = 0; i00 < ns; i00 += 64 * SB) {
@@ -381,7 +383,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
         bool cand = false;
         if (!is_zero(v)) {
           bool isk = false;
-          if (a.n_keep) isk = keep_lookup<W>(keep, a.n_keep, ukb[ub + i]);
+          if (n_keep) isk = keep_lookup<W>(keep, n_keep, ukb[ub + i]);
           if (!isk) {
             const uint32_t d0 = (uint32_t)((uint64_t)__double_as_longlong(weight2(v)) >> SEL0_SHIFT);
             if (d0 > D0) {
@@ -607,6 +609,7 @@ __global__ __launch_bounds__(256) void k_write_out(WriteArgs a, uint32_t nbk) {
   const uint32_t b = blockIdx.x * SEL_CHUNK + wv;
   if (b >= nbk) return;
   const uint32_t ub = a.b_ubase[b], ns = a.b_slots[b];
+  const int n_keep = a.n_keep && a.b_keep[b] ? a.n_keep : 0;
   uint32_t obase = a.b_obase[b];
   for (uint32_t i0 = lane; i0 < ns + lane; i0 += 64 * WB) {
     // WB values, then the keys of those that are kept, in flight per lane
@@ -616,7 +619,7 @@ __global__ __launch_bounds__(256) void k_write_out(WriteArgs a, uint32_t nbk) {
 #pragma unroll
     for (int u = 0; u < WB; u++)
       v[u] = i0 + 64 * u < ns ? a.uc[ub + i0 + 64 * u] : make_double2(0.0, 0.0);
-    if (mode == S_ALL && !a.n_keep) {
+    if (mode == S_ALL) {
 #pragma unroll
       for (int u = 0; u < WB; u++) {
         s[u] = !is_zero(v[u]);
@@ -628,9 +631,7 @@ __global__ __launch_bounds__(256) void k_write_out(WriteArgs a, uint32_t nbk) {
         const uint32_t i = i0 + 64 * u;
         s[u] = false;
         if (!is_zero(v[u])) {
-          if (mode == S_ALL) {
-            s[u] = true;
-          } else if (a.n_keep && keep_lookup<W>(keep, a.n_keep, ukb[ub + i])) {
+          if (n_keep && keep_lookup<W>(keep, n_keep, ukb[ub + i])) {
             s[u] = true;
           } else if (mode == S_THRESHOLD) {
             // |c|^2 bits decide unless they equal the threshold's
