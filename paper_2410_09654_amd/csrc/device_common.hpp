@@ -24,6 +24,8 @@ constexpr int NBL_APPEND = 6;           // NBL of its emission kernel (which bin
 constexpr int NBINS_LOG_MID = 12;       // hash bins of a call of at most 2^22 records
 constexpr int NBINS_LOG_MP = 15;        // hash bins per pass of a call that needs
 constexpr int NBINS_MP = 1 << NBINS_LOG_MP;  // several (twice the records per pass)
+constexpr int NBINS_LOG_WIDE = 17;      // hash bins of a large call that one pass over them holds
+constexpr int NBINS_WIDE = 1 << NBINS_LOG_WIDE;  // (counted per workgroup in bytes)
 constexpr int MERGE_CAP = 1984;         // max records of one merge bucket (LDS: two
                                         // merge blocks per CU at W = 1)
 // The bucket capacity per key width: two merge blocks per CU in LDS at

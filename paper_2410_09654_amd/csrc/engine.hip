@@ -306,6 +306,10 @@ static_assert(COMM_ROWS_MAX + TERM_ROWS_MAX <= SC_ROWS_MAX, "k_scan_cols covers 
 // pruned to each wave's window (2 to 3 times fewer pairs tested); below, the
 // pair tests take about a microsecond and the sort's loads and barriers more.
 constexpr int EMIT_WINDOW_TILES = 32;
+// One-pass calls over 2^17 bins: strings whose pairs are counted for the
+// estimate, and rows of O tiles (one workgroup to a CU by LDS, two rounds)
+constexpr int64_t WIDE_SAMPLE = 64 * EMIT_THREADS, WIDE_TILE_ROWS = 512;
+static_assert(WIDE_TILE_ROWS + TERM_ROWS_MAX <= SW_ROWS_MAX, "k_scan_wide covers every row");
 constexpr int MAX_PASS_BITS = 12;
 constexpr int DIRECT_MAX_F = 22;  // at most 2^22 buckets in a direct merge
 constexpr int64_t STREAM_MAX = 1 << 20;  // canonical terms up to here are streamed for their bounds
@@ -833,6 +837,7 @@ int Engine::run(Call& c) {
     }
     for (int t = 0; t <= c.n_terms; t++) ea.tstart[t] = tstart[t];
     ea.counts = counts;
+    ea.ctl = dctl;
     ea.bin_base = bin_base;
     ea.max_len = (c.mode == M_PLAIN && tr) ? tr->max_len : 0;
 
@@ -872,10 +877,17 @@ int Engine::run(Call& c) {
       }
     } else {
     // 2^nbl hash bins per pass: NBINS_LOG while the call fits one pass,
-    // NBINS_LOG_MP (twice the records per pass) when it needs several, and
+    // NBINS_LOG_WIDE while it fits one pass over those, else NBINS_LOG_MP (twice the records per pass) when it needs several, and
     // NBINS_LOG_MID for calls of at most 2^22 records even if every pair emits
     // one (the per-call bin tables then cost a quarter)
     int nbl = NBINS_LOG;
+    // wide bins: emission rows (0: not used), row prefixes, tables
+    int wtiles = 0, wrows = 0;
+    bool counted_mp = false;  // the count read was taken over NBINS_LOG_MP bins
+    uint16_t* pre16 = nullptr;
+    uint32_t *wtotal = nullptr, *wbase = nullptr;
+    unsigned long long* wlook = nullptr;
+    uint32_t* defer = b1.defer;
     if (rec_bound <= (1ull << (NBINS_LOG_MID + 10)) && (!comm || c.H.n < (1 << (NBINS_LOG_MID - 3))))
       nbl = NBINS_LOG_MID;
     auto count_pass = [&](int pass_bits, uint32_t pass_id, bool read = true,
@@ -959,7 +971,88 @@ int Engine::run(Call& c) {
         }
       }
     } else {
-      TRY(count_pass(0, 0));
+      // A call of more possible records than that: the number is estimated
+      // from the pairs of the first WIDE_SAMPLE strings (45 us, host included),
+      // and the bins chosen by it.
+      //  - One pass over 2^15 bins: counted over those at once (a count over
+      //    2^14 bins first took 0.21 of 2.43 ms for 23 M two-word FP32 records).
+      //  - More, up to one pass over 2^17: counted over those, in bytes (which
+      //    is what LDS holds of them), and scattered straight to the buckets,
+      //    where the partitions below write and read every record twice: 96 M
+      //    two-word records 6.8 -> 5.0 ms with the binning, the step 11.9 ->
+      //    10.3 ms.  Not below 2^15 bins' worth: the open lines of 2^15 bins
+      //    fit an L2, those of 2^17 do not (23 M records 0.80 -> 1.19 ms).
+      //  - Otherwise, and when a count does not fit after all: the count over
+      //    2^14 bins, and partitions.
+      const int64_t tiles = (c.O.n + EMIT_THREADS - 1) / EMIT_THREADS;
+      if (comm && rec_bound > 7ull * (1ull << NBINS_LOG) * (unsigned long long)merge_cap<W>() &&
+          c.O.n > WIDE_SAMPLE) {
+        const double room = 0.85 * merge_cap<W>();
+        EmitArgs se = ea;
+        se.nO = WIDE_SAMPLE;
+        se.n_terms = 0;
+        se.hseg = (int)std::max<int64_t>(
+            1, std::min<int64_t>(HSEG_ROWS * EMIT_THREADS / WIDE_SAMPLE, c.H.n / HSEG_MIN));
+        se.comm_rows = (int)(WIDE_SAMPLE / EMIT_THREADS) * se.hseg;
+        {
+          const EmitArgs& ea = se;
+          const int rows = se.comm_rows;
+          EMIT("k_emit_sample", false, NBINS_LOG_MID);
+          SCAN(NBINS_LOG_MID, counts, rows, 0ull, 0u);
+        }
+        TRY(read_ctl());
+        const double est = 1.05 * (double)hctl->pe_total * ((double)c.O.n / (double)WIDE_SAMPLE) +
+                           (double)nterm_rec;
+        if (est > room * NBINS && est <= room * NBINS_MP) {
+          nbl = NBINS_LOG_MP;
+        } else if (est > room * NBINS && est <= room * NBINS_WIDE) {
+          wtiles = (int)std::min<int64_t>(tiles, WIDE_TILE_ROWS);
+          wrows = wtiles * hseg + term_rows;
+        }
+      }
+      const size_t mark_bottom = ar->bottom, mark_need = ar->need;
+      if (wrows) {
+        pre16 = (uint16_t*)ar->take((size_t)wrows * NBINS_WIDE * 2);
+        wtotal = (uint32_t*)ar->take(NBINS_WIDE * 4);
+        wbase = (uint32_t*)ar->take((NBINS_WIDE + 1) * 4);
+        wlook = (unsigned long long*)ar->take(NBINS_WIDE * 8);
+        if (ar->short_) wrows = 0;
+      }
+      if (wrows) {
+        ea.comm_rows = wtiles * hseg;
+        ea.counts8 = (uint8_t*)counts;
+        ea.pre16 = pre16;
+        {
+          const int rows = wrows;
+          EMIT("k_emit_count", false, NBINS_LOG_WIDE);
+        }
+        LAUNCH("k_scan_wide", k_scan_wide, NBINS_WIDE / 128, 1024, (const uint8_t*)counts, wrows,
+               pre16, wtotal, wbase, dctl, wlook);
+        TRY(read_ctl());
+        if ((hctl->overflow & 4u) || hctl->maxg[0] > (unsigned int)merge_cap<W>()) {
+          wrows = 0;
+          ea.comm_rows = comm_rows;
+          TRY(zero_u32(&dctl->overflow, 1));
+        }
+      }
+      if (wrows) {
+        nbl = NBINS_LOG_WIDE;
+        bin_base = wbase;
+        look = wlook;
+        defer = (uint32_t*)wlook;
+        ea.bin_base = wbase;
+      } else {
+        ar->bottom = mark_bottom;
+        ar->need = mark_need;
+        ar->short_ = false;
+        TRY(count_pass(0, 0));
+        counted_mp = nbl == NBINS_LOG_MP;
+        if (counted_mp && hctl->maxg[0] > (unsigned int)merge_cap<W>()) {
+          counted_mp = false;
+          nbl = NBINS_LOG;
+          TRY(count_pass(0, 0));
+        }
+      }
     }
     if (nbl < NBINS_LOG && hctl->maxg[0] > (unsigned int)merge_cap<W>()) {
       // records that crowd one bin of 2^12: count again over 2^14 bins
@@ -977,7 +1070,7 @@ int Engine::run(Call& c) {
     // of one string share a bin), so a pass that still overflows restarts the
     // loop with one more pass bit
     // the count pass measured every bin exactly
-    int pass_bits = nbl < NBINS_LOG ? 0 : plan_pass_bits<W>(hctl->maxg[0], &nbl);
+    int pass_bits = nbl < NBINS_LOG || wrows || counted_mp ? 0 : plan_pass_bits<W>(hctl->maxg[0], &nbl);
     // Several passes bin each partition over 2^14 instead of 2^15 bins when
     // the 2^14 bins are expected to stay within 0.8 of the merge's capacity
     // (the merge then takes single bins where it would take pairs of 2^15
@@ -987,7 +1080,7 @@ int Engine::run(Call& c) {
     if (nbl == NBINS_LOG_MP && pass_bits > 0 &&
         (double)hctl->maxg[0] <= std::ldexp(0.8 * merge_cap<W>(), pass_bits))
       pnbl = NBINS_LOG;
-    const int table_bits = std::min(pass_bits + 2, MAX_PASS_BITS);
+    const int table_bits = wrows ? 0 : std::min(pass_bits + 2, MAX_PASS_BITS);
     const size_t ptot = (size_t)std::max<unsigned long long>(pe_all, 1);
     const uint32_t max_buckets = (uint32_t)(1u << nbl) << table_bits;
     // ----- records, U, bucket tables, candidate lists -------------------------
@@ -1032,7 +1125,7 @@ int Engine::run(Call& c) {
     npass = 1 << pass_bits;
     // the first count pass's prefixes (in `counts`) and bin totals (in
     // bin_total) serve the first partitioning only
-    bool first_counts = pe_all < 0xFFFFFFFFull;
+    bool first_counts = pe_all < 0xFFFFFFFFull && !counted_mp;
     for (bool done = false; !done;) {
       done = true;
       nbk = 0;
@@ -1093,7 +1186,7 @@ int Engine::run(Call& c) {
             SCAN(NBINS_LOG_MP, scounts, SPLIT_ROWS, 0ull, 0u);
           }
           TRY(read_ctl());
-        } else if (nbl == NBINS_LOG_MP) {
+        } else if (nbl == NBINS_LOG_MP && !counted_mp) {
           // one pass at NBINS_LOG_MP bins: count again at that bin count; this
           // overwrites the first count pass's NBINS_LOG-bin prefixes and totals
           TRY(count_pass(pass_bits, (uint32_t)p));
@@ -1118,6 +1211,7 @@ int Engine::run(Call& c) {
             return PAULI_EINTERNAL;
           }
           pass_bits++;
+          counted_mp = false;
           done = false;
           // the earlier passes' merges filled the histogram and wrote rows
           TRY(zero_u32(hist0, (size_t)HREP * SEL0_BINS));
@@ -1133,7 +1227,10 @@ int Engine::run(Call& c) {
           LAUNCH("k_split_scatter", (k_split<W, F32, true, NBINS_LOG_MP>), SPLIT_ROWS, 1024, sp);
         else if (scattered)
           ;  // launched before the count was read
-        else if (nbl == NBINS_LOG_MID)
+        else if (nbl == NBINS_LOG_WIDE) {
+          const int rows = wrows;
+          EMIT("k_emit_scatter", true, NBINS_LOG_WIDE);
+        } else if (nbl == NBINS_LOG_MID)
           EMIT("k_emit_scatter", true, NBINS_LOG_MID);
         else if (nbl == NBINS_LOG)
           EMIT("k_emit_scatter", true, NBINS_LOG);
@@ -1168,7 +1265,7 @@ int Engine::run(Call& c) {
           u_off += pe;
           continue;
         }
-        ma.defer = b1.defer;
+        ma.defer = defer;
         if (big <= (unsigned int)SCAP) {
           LAUNCH("k_merge_small", (k_merge<W, F32, MERGE_SMALL_THREADS, SCAP, MERGE_SMALL>),
                  nb_pass, MERGE_SMALL_THREADS, ma);

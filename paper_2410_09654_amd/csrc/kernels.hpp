@@ -125,6 +125,11 @@ struct EmitArgs {
   uint32_t* cursor;
   int append_F;
   uint32_t append_cap;
+  // wide bins: counts as bytes [rows][2^17], and the row prefixes k_scan_wide
+  // makes of them
+  uint8_t* counts8;
+  const uint16_t* pre16;
+  Ctl* ctl;
 };
 
 template <bool F32>
@@ -183,8 +188,13 @@ template <int W, bool F32, bool SCATTER, int NBL, bool TS>
 __global__ __launch_bounds__(EMIT_THREADS)
 __attribute__((amdgpu_waves_per_eu(W == 1 && NBL <= 14 ? 8 : 4))) void k_emit(EmitArgs a) {
   constexpr int NB = 1 << NBL;  // hash bins of this call
+  // wide bins: one byte per bin (a workgroup rarely puts more than a few
+  // records into one of 2^17; more than 255 send the call to the partitions).
+  // The scatter takes a record's place from the bin's start, the row's prefix
+  // in the bin (both from memory) and the byte.
+  constexpr bool BYTES = NBL == NBINS_LOG_WIDE;
   using V = RecV<F32>;
-  __shared__ uint32_t hist[NB];
+  __shared__ uint32_t hist[BYTES ? NB / 4 : NB];
   __shared__ uint32_t queue[EMIT_THREADS / 64][128];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wv = tid >> 6;
@@ -192,7 +202,9 @@ __attribute__((amdgpu_waves_per_eu(W == 1 && NBL <= 14 ? 8 : 4))) void k_emit(Em
   const uint32_t lrow = layout_row(blockIdx.x, gridDim.x);
   if (SCATTER && a.skip && *a.skip) return;
   constexpr bool append = SCATTER && NBL == NBL_APPEND;
-  if (SCATTER) {
+  if (BYTES) {
+    for (int i = tid; i < NB / 4; i += EMIT_THREADS) hist[i] = 0u;
+  } else if (SCATTER) {
     if (!append) {
       const uint32_t* crow = a.counts + (size_t)lrow * NB;
       for (int i = tid; i < NB; i += EMIT_THREADS) hist[i] = a.bin_base[i] + crow[i];
@@ -238,7 +250,18 @@ __attribute__((amdgpu_waves_per_eu(W == 1 && NBL <= 14 ? 8 : 4))) void k_emit(Em
       top <<= a.pass_bits;
     }
     const uint32_t bin = (uint32_t)(top >> (64 - NBL));
-    const uint32_t pos = atomicAdd(&hist[bin], 1u);
+    uint32_t pos;
+    if constexpr (BYTES) {
+      const uint32_t sh = (bin & 3u) * 8u;
+      const uint32_t old = (atomicAdd(&hist[bin >> 2], 1u << sh) >> sh) & 255u;
+      if constexpr (SCATTER) {
+        pos = a.bin_base[bin] + a.pre16[(size_t)lrow * NB + bin] + old;
+      } else if (old == 255u) {
+        atomicOr(&a.ctl->overflow, 4u);
+      }
+    } else {
+      pos = atomicAdd(&hist[bin], 1u);
+    }
     if (SCATTER) {
       const uint64_t small = a.wide ? 0ull : (((uint64_t)group << (F - 3)) | index);
       mk.w[0] = (small << (64 - F)) | (mk.w[0] & (~0ull >> F));
@@ -471,8 +494,9 @@ __attribute__((amdgpu_waves_per_eu(W == 1 && NBL <= 14 ? 8 : 4))) void k_emit(Em
   }
   __syncthreads();
   if (!SCATTER) {
-    uint32_t* crow = a.counts + (size_t)lrow * NB;
-    for (int i = tid; i < NB; i += EMIT_THREADS) crow[i] = hist[i];
+    uint32_t* crow = BYTES ? reinterpret_cast<uint32_t*>(a.counts8 + (size_t)lrow * NB)
+                           : a.counts + (size_t)lrow * NB;
+    for (int i = tid; i < (BYTES ? NB / 4 : NB); i += EMIT_THREADS) crow[i] = hist[i];
   }
 }
 
@@ -771,6 +795,143 @@ __global__ __launch_bounds__(1024) void k_scan(uint32_t* counts, int rows, uint3
     // a scatter already launched for a single pass laid out for spec_cap
     // records stands down unless the records fit and every bin fits a bucket
     if (spec_cap) ctl->spec_fail = (total > spec_cap || gmax[0] > merge_cap) ? 1u : 0u;
+  }
+}
+
+// The scans of a wide count: row prefixes (16 bits; a bin whose total exceeds
+// merge_cap sends the call to the partitions, so no prefix that is used wraps)
+// from the byte counts, four bins per thread and row, and the bin totals; the
+// last block scans those into bin bases, 16384 bins at a time, as k_scan does.
+constexpr int SW_SEG = 20, SW_ROWS_MAX = SW_SEG * 32;
+__global__ __launch_bounds__(1024) void k_scan_wide(const uint8_t* counts8, int rows,
+                                                    uint16_t* pre16, uint32_t* bin_total,
+                                                    uint32_t* bin_base, Ctl* ctl,
+                                                    unsigned long long* look) {
+  constexpr int NB = NBINS_WIDE;
+  __shared__ uint4 ssum[32][32];
+  const int t = threadIdx.x, col = t & 31, seg = t >> 5, lane = t & 63, wv = t >> 6;
+  const int word = blockIdx.x * 32 + col;  // bins 4 word .. 4 word + 3
+  if (t < 128) look[blockIdx.x * 128 + t] = 0ull;
+  {
+    const int r0 = seg * SW_SEG;
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(counts8) + word;
+    uint32_t c[SW_SEG];
+#pragma unroll
+    for (int q = 0; q < SW_SEG; q++) c[q] = r0 + q < rows ? src[(size_t)(r0 + q) * (NB / 4)] : 0u;
+    uint4 s = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+    for (int q = 0; q < SW_SEG; q++) {
+      s.x += c[q] & 255u;
+      s.y += (c[q] >> 8) & 255u;
+      s.z += (c[q] >> 16) & 255u;
+      s.w += c[q] >> 24;
+    }
+    ssum[seg][col] = s;
+    __syncthreads();
+    const int last = (rows - 1) / SW_SEG;
+    uint4 run = make_uint4(0u, 0u, 0u, 0u);
+    if (seg <= last)
+      for (int g = 0; g < seg; g++) {
+        const uint4 o = ssum[g][col];
+        run.x += o.x;
+        run.y += o.y;
+        run.z += o.z;
+        run.w += o.w;
+      }
+    uint2* dst = reinterpret_cast<uint2*>(pre16) + word;
+#pragma unroll
+    for (int q = 0; q < SW_SEG; q++) {
+      if (r0 + q < rows)
+        dst[(size_t)(r0 + q) * (NB / 4)] =
+            make_uint2((run.x & 0xFFFFu) | (run.y << 16), (run.z & 0xFFFFu) | (run.w << 16));
+      run.x += c[q] & 255u;
+      run.y += (c[q] >> 8) & 255u;
+      run.z += (c[q] >> 16) & 255u;
+      run.w += c[q] >> 24;
+    }
+    if (seg == last) {
+      st_agent(&bin_total[4 * word], run.x);
+      st_agent(&bin_total[4 * word + 1], run.y);
+      st_agent(&bin_total[4 * word + 2], run.z);
+      st_agent(&bin_total[4 * word + 3], run.w);
+    }
+  }
+  if (!last_block(&ctl->ticket[0])) return;
+  __shared__ unsigned long long tmp[17];
+  __shared__ unsigned int gmax[5];
+  if (t < 5) gmax[t] = 0u;
+  unsigned long long carry = 0;
+  unsigned int best[5] = {0u, 0u, 0u, 0u, 0u};
+  for (int b0 = 0; b0 < NB; b0 += 16 * 1024) {
+    const uint4* src = reinterpret_cast<const uint4*>(bin_total + b0) + 4 * t;
+    uint32_t v[16];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const uint4 c = src[q];
+      v[4 * q] = c.x;
+      v[4 * q + 1] = c.y;
+      v[4 * q + 2] = c.z;
+      v[4 * q + 3] = c.w;
+    }
+    unsigned long long s = 0;
+#pragma unroll
+    for (int k = 0; k < 16; k++) s += v[k];
+#pragma unroll
+    for (int lg = 0; lg < 5; lg++)
+#pragma unroll
+      for (int k = 0; k < 16; k += 1 << lg) {
+        unsigned int acc = 0;  // (at most 16 x 640 x 255)
+#pragma unroll
+        for (int q = 0; q < (1 << lg); q++) acc += v[k + q];
+        best[lg] = max(best[lg], acc);
+      }
+    unsigned long long x = s;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const unsigned long long y = __shfl_up(x, d, 64);
+      if (lane >= d) x += y;
+    }
+    if (lane == 63) tmp[wv] = x;
+    __syncthreads();
+    unsigned long long w = lane < 16 ? tmp[lane] : 0ull;
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) {
+      const unsigned long long y = __shfl_up(w, d, 64);
+      if (lane >= d) w += y;
+    }
+    const unsigned long long before = wv > 0 ? __shfl(w, wv - 1, 64) : 0ull;
+    unsigned long long pre = carry + before + x - s;
+    carry += __shfl(w, 15, 64);
+    uint4* dst = reinterpret_cast<uint4*>(bin_base + b0) + 4 * t;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      uint4 o;
+      o.x = (uint32_t)pre;
+      pre += v[4 * q];
+      o.y = (uint32_t)pre;
+      pre += v[4 * q + 1];
+      o.z = (uint32_t)pre;
+      pre += v[4 * q + 2];
+      o.w = (uint32_t)pre;
+      pre += v[4 * q + 3];
+      dst[q] = o;
+    }
+    __syncthreads();  // tmp is rewritten by the next bins
+  }
+#pragma unroll
+  for (int lg = 0; lg < 5; lg++) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1)
+      best[lg] = max(best[lg], (unsigned int)__shfl_xor((int)best[lg], d, 64));
+    if (lane == 0) atomicMax(&gmax[lg], best[lg]);
+  }
+  __syncthreads();
+  if (t == 0) {
+    bin_base[NB] = (uint32_t)carry;
+    ctl->pe_total = carry;
+    ctl->ndefer = 0u;
+    if (carry > 0xFFFFFFFFull) ctl->overflow |= 2u;
+    for (int lg = 0; lg < 5; lg++) ctl->maxg[lg] = gmax[lg];
   }
 }
 

@@ -164,3 +164,53 @@ def test_lookups_and_reductions(pk, n, na, nq):
     assert got == want
     s = pk.correlator(dA, dA, ws=ws)
     assert s == 1.0
+
+
+def dyadic(h, seed):
+    """The strings of h with small integer coefficients: every sum of products is exact, so any
+    order of summation gives the same bits."""
+    rng = np.random.default_rng(seed)
+    c = rng.integers(1, 9, h.n) * rng.choice([1.0, -1.0], h.n) + 1j * rng.integers(-8, 9, h.n)
+    return wl.HostOp(h.n_qubits, h.x, h.z, c)
+
+
+# calls too large for one pass over 2^14 bins, binned over 2^15 or (more than 55 M one-word or
+# 37 M two-word records expected) 2^17 at once, against the sum of the same call on quarters of O
+# (each within 2^14 bins); the last case puts 400 records of one string into one workgroup's bin,
+# more than a byte counts, and goes back to the partitions
+@pytest.mark.parametrize("n,chain,count,dtype,crowd", [(64, "ising", 2500003, 0, 0),
+                                                       (64, "ising", 3700003, 0, 0),
+                                                       (100, "xxz", 1200001, 1, 0),
+                                                       (100, "xxz", 1900001, 0, 0),
+                                                       (100, "xxz", 1900001, 1, 0),
+                                                       (48, "random", 640000, 0, 400)])
+def test_one_pass_over_wide_bins(pk, n, chain, count, dtype, crowd):
+    print(f"wide bins n={n} {chain} count={count} dtype={dtype} crowd={crowd}", flush=True)
+    O = wl.random_local_strings(n, count, 13, seed=count)
+    if crowd:
+        H, P = wl.same_key_runs(n, np.ones(crowd))
+        keep = ~np.isin(O.x[:, 0] ^ (O.z[:, 0] << np.uint64(1)), P.x[:, 0] ^ (P.z[:, 0] << np.uint64(1)))
+        O = wl.HostOp(n, np.concatenate([P.x, O.x[keep]]), np.concatenate([P.z, O.z[keep]]),
+                      np.concatenate([P.coef, O.coef[keep]]))
+    else:
+        H = wl.ising_chain(n, 0.5, 2.0) if chain == "ising" else wl.xxz_random_field(n, 0.5, 0.0)[0]
+        H = wl.HostOp(n, H.x[H.coef != 0], H.z[H.coef != 0], H.coef[H.coef != 0])
+    H = wl.HostOp(n, H.x, H.z, np.where(np.arange(H.n) % 3, 0.5, 2.0))
+    O = dyadic(O, 7)
+    assert H.n * O.n > 7 * (1 << 14) * (1984 if n <= 64 else 1344)
+    ws = pk.Workspace(1 << 30)
+    dH = raw(pk, H)
+    got = pk.commutator(dH, raw(pk, O, dtype), ws=ws)
+    stats = pk.last_stats()
+    assert stats["passes"] == 1 or crowd
+    q = -(-O.n // 4)
+    total = None
+    for k in range(4):
+        part = wl.HostOp(n, O.x[k * q:(k + 1) * q], O.z[k * q:(k + 1) * q], O.coef[k * q:(k + 1) * q])
+        c = pk.commutator(dH, raw(pk, part, dtype), ws=ws)
+        total = c if total is None else pk.add(total, 1.0, c, 1.0, ws=ws)
+    m = got.size
+    assert m == total.size
+    import torch
+    assert torch.equal(got.x[:, :m], total.x[:, :m]) and torch.equal(got.z[:, :m], total.z[:, :m])
+    assert torch.equal(got.coef[:m], total.coef[:m])
