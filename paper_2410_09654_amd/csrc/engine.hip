@@ -1247,13 +1247,15 @@ int Engine::run(Call& c) {
         // Buckets up to the small variant's capacity run three to a CU: all
         // of them when the largest bucket fits; when most do, the full-size
         // merge takes the others from a deferral list; else the full-size merge
-        // takes every bucket.
+        // takes every bucket, and also when there are so few that all run at
+        // once (its 1024 threads finish a bucket of 1000 records in 17 us, 512
+        // take 26).
         constexpr int SCAP = small_merge_cap<W, F32>();
         const unsigned int big = hctl->maxg[g_log];
         if (final_merge) {
           ma.look = look;
           ma.hctl = pinned && npass == 1 ? hctl : nullptr;
-          if (big <= (unsigned int)SCAP)
+          if (big <= (unsigned int)SCAP && nb_pass > MERGE_ONE_WAVE)
             LAUNCH("k_merge_small",
                    (k_merge<W, F32, MERGE_SMALL_THREADS, SCAP, MERGE_SMALL, false, true>), nb_pass,
                    MERGE_SMALL_THREADS, ma);
@@ -1266,7 +1268,10 @@ int Engine::run(Call& c) {
           continue;
         }
         ma.defer = defer;
-        if (big <= (unsigned int)SCAP) {
+        if (nb_pass <= MERGE_ONE_WAVE) {
+          LAUNCH("k_merge", (k_merge<W, F32, MERGE_THREADS, merge_cap<W>(), MERGE_GRID>), nb_pass,
+                 MERGE_THREADS, ma);
+        } else if (big <= (unsigned int)SCAP) {
           LAUNCH("k_merge_small", (k_merge<W, F32, MERGE_SMALL_THREADS, SCAP, MERGE_SMALL>),
                  nb_pass, MERGE_SMALL_THREADS, ma);
         } else if (pe <= (unsigned long long)nb_pass * (SCAP * 9 / 10)) {
@@ -2853,10 +2858,12 @@ int pauli_mlp_train(const pauli_mlp* net, const float* x, const float* t, const 
       batch > 4096 || t0 < 0 || !net->grads || !net->adam_m || !net->adam_v)
     return PAULI_EINVAL;
   Arena ar = make_arena(ws);
+  // a minibatch's activations, in the room of one gradient share per SR rows
   const int nblk_max = (batch + SR - 1) / SR;
-  float* part = (float*)ar.take((size_t)nblk_max * NPARAM * 4);
-  double* lpart = (double*)ar.take((size_t)nblk_max * 16);
+  char* part = (char*)ar.take((size_t)nblk_max * NPARAM * 4);
+  ar.take((size_t)nblk_max * 16);
   if (ar.short_) return ws_short(ar, ws);
+  static_assert(step_out_bytes(SR) + 16 * 256 <= NPARAM * 4, "the activations fit their room");
   // W2 transposed for the backward product, where the workspace has room for it
   uint16_t* w2t = (uint16_t*)ar.take((size_t)NHID * NHID * 2);
   if (w2t) LAUNCH("k_w2_transpose", k_w2_transpose, NHID * NHID / 256, 256, net->params_bf16, w2t);
@@ -2867,6 +2874,23 @@ int pauli_mlp_train(const pauli_mlp* net, const float* x, const float* t, const 
       const int64_t s0 = k * batch;
       const int rows = (int)std::min<int64_t>(batch, n - s0);
       const int nblk = (rows + SR - 1) / SR;
+      StepOut so;
+      so.Bp = nblk * SR;
+      Arena room;
+      room.base = part;
+      room.cap = (size_t)nblk_max * NPARAM * 4;
+      const size_t Bp = (size_t)so.Bp;
+      so.x = (uint16_t*)room.take(Bp * NIN * 2);
+      so.y1 = (uint16_t*)room.take(Bp * NHID * 2);
+      so.y2 = (uint16_t*)room.take(Bp * NHID * 2);
+      so.dz1 = (uint16_t*)room.take(Bp * NHID * 2);
+      so.dz2 = (uint16_t*)room.take(Bp * NHID * 2);
+      so.dy = (uint16_t*)room.take(Bp * NOUT * 2);
+      so.fz1 = (float*)room.take(Bp * NHID * 4);
+      so.fz2 = (float*)room.take(Bp * NHID * 4);
+      so.fy = (float*)room.take(Bp * NOUT * 4);
+      so.err = (double*)room.take(Bp * NOUT * 8);
+      so.cnt = (double*)room.take(8);
       StepArgs sa;
       sa.params = net->params;
       sa.pb = net->params_bf16;
@@ -2876,16 +2900,27 @@ int pauli_mlp_train(const pauli_mlp* net, const float* x, const float* t, const 
       sa.Mk = mask;
       sa.order = order + e * n + s0;
       sa.rows = rows;
-      sa.part = part;
-      sa.lpart = lpart;
-      LAUNCH("k_mlp_step", k_mlp_step, nblk, STEP_THREADS, sa);
+      sa.o = so;
+      LAUNCH("k_mlp_step", k_mlp_step, so.Bp / SB, STEP_THREADS, sa);
       step++;
-      const float c1 = (float)(1.0 - std::pow(b1, (double)step));
-      const float c2 = (float)(1.0 - std::pow(b2, (double)step));
-      LAUNCH("k_mlp_reduce_adam", k_mlp_reduce_adam, (NPARAM + 255) / 256, 256, part, nblk,
-             net->grads, net->params, net->adam_m, net->adam_v, net->params_bf16, (float)lr,
-             (float)b1, (float)(1.0 - b1), (float)b2, (float)(1.0 - b2), (float)eps, c1, c2,
-             lpart, losses + e * spe + k, w2t);
+      GradArgs ga;
+      ga.o = so;
+      ga.grads = net->grads;
+      ga.p = net->params;
+      ga.m = net->adam_m;
+      ga.v = net->adam_v;
+      ga.pb = net->params_bf16;
+      ga.w2t = w2t;
+      ga.lr = (float)lr;
+      ga.b1 = (float)b1;
+      ga.omb1 = (float)(1.0 - b1);
+      ga.b2 = (float)b2;
+      ga.omb2 = (float)(1.0 - b2);
+      ga.eps = (float)eps;
+      ga.c1 = (float)(1.0 - std::pow(b1, (double)step));
+      ga.c2 = (float)(1.0 - std::pow(b2, (double)step));
+      ga.loss = losses + e * spe + k;
+      LAUNCH("k_mlp_grad_adam", k_mlp_grad_adam, GRAD_BLOCKS, 64, ga);
     }
   }
   HIP_TRY(hipStreamSynchronize(stream));

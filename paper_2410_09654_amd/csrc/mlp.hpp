@@ -192,28 +192,44 @@ __global__ void k_adam(float* p, const float* g, float* m, float* v, uint16_t* p
 }
 
 // ---------------------------------------------------------------------------
-// Fused training step.  One block of 1024 threads (sixteen waves, wave w on
-// hidden columns 16 w .. 16 w + 15) takes SR rows of the minibatch (row i of
-// the minibatch is row order[i] of the training set): forward, masked MSE and
-// backward with every activation in LDS and every matrix product on the
-// matrix cores (the same BF16 operands, FP32 accumulation and epilogues as the
-// layer-by-layer kernels above), then writes its rows' share of every
-// parameter gradient to part[block][NPARAM] and of the loss to lpart[block]
-// (sum mask (y - t)^2 and the minibatch's sum of mask).  k_mlp_reduce_adam
-// sums the shares in block order and takes the Adam step.  Rows beyond the
-// minibatch are zero with zero mask, so they contribute nothing.
+// Fused training step, two kernels per minibatch (row i of the minibatch is row
+// order[i] of the training set; the operands, FP32 accumulation and epilogues
+// are those of the layer-by-layer kernels above).
 //
-// Bound: the chain of eight dependent products with a barrier after each, on
-// as many CUs as the minibatch has SR-row blocks.  Four waves that walked
-// the tiles in turn and read the transposed operands as single 16-bit words
-// took 50.7 us for 256 rows; sixteen waves, activations held in both orders
-// (row-major for the next layer, column-major for the weight gradients, so
-// every operand is one 16-byte LDS read), weights loaded ahead of the product
-// that needs them and Z in registers: 22.7 us (a run of
-// 256-row minibatches 58.8 -> 31.6 us a minibatch).
+// k_mlp_step: one block of 1024 threads (sixteen waves, wave w on hidden columns
+// 16 w .. 16 w + 15) takes SB rows through forward, masked MSE and backward
+// with the activations in LDS and every product on the matrix cores, and
+// leaves what the weight gradients need in memory (StepOut; rows beyond the
+// minibatch are zero with zero mask, so they contribute nothing).
+// k_mlp_grad_adam: one wave per 16 x 16 tile of a weight gradient (K = the
+// minibatch, in shares of SR rows that are added in order) or per eight bias
+// columns takes the gradient and the Adam step at once.
+//
+// Bound: the chain of six dependent products with a barrier after each, on as
+// many CUs as the minibatch has SB-row blocks.  Four waves that walked the tiles of 32 rows
+// in turn, with operands read as single 16-bit words, took 50.7 us for 256 rows
+// and 4.9 us for the sum of the blocks' gradient shares and Adam; sixteen waves
+// with 16-byte operand reads 22.7 us; 16-row blocks that leave the weight
+// gradients to the second kernel (no gradient shares are written or read) 15.1
+// and 6.2 us. (240 such minibatches: 14.4 -> 6.2 ms with the launches.)
 // ---------------------------------------------------------------------------
-constexpr int SR = 32;  // minibatch rows per block
+constexpr int SR = 32;  // rows of a gradient share
+constexpr int SB = 16;  // rows of a block of k_mlp_step
 constexpr int STEP_THREADS = 1024;
+
+// Activations of a minibatch padded to Bp rows (a multiple of SR): by columns
+// [column][Bp] in bf16, the operands of the weight gradients, and by rows in
+// FP32, for the bias gradients; and the squared errors.
+struct StepOut {
+  uint16_t *x, *y1, *y2, *dz1, *dz2, *dy;
+  float *fz1, *fz2, *fy;
+  double* err;  // [Bp][16]
+  double* cnt;  // sum of the mask
+  int Bp;
+};
+constexpr size_t step_out_bytes(size_t Bp) {
+  return Bp * (2 * (NIN + 4 * NHID + NOUT) + 4 * (2 * NHID + NOUT) + 8 * NOUT) + 8;
+}
 
 struct StepArgs {
   const float* params;   // fp32 master weights (biases)
@@ -224,8 +240,7 @@ struct StepArgs {
   const float* Mk;       // [n][16] target mask
   const int32_t* order;  // the minibatch's rows, `rows` entries
   int rows;
-  float* part;           // [gridDim.x][NPARAM]
-  double* lpart;         // [gridDim.x][2]
+  StepOut o;
 };
 
 __device__ __forceinline__ bf16x8 bf8_lds(const uint16_t* p) {
@@ -266,38 +281,36 @@ __device__ __forceinline__ void tree256(double* d, int tid) {
 }
 
 __global__ __launch_bounds__(STEP_THREADS) void k_mlp_step(StepArgs a) {
-  constexpr int RS = NHID + 8;  // row-major row (16-bit words; 16-byte aligned, off the bank stride)
-  constexpr int CS = SR + 8;    // column-major row
-  constexpr int ZS = NHID + 4;
-  static_assert(NHID == 16 * (STEP_THREADS / 64) && SR == 32, "one column tile per wave, two row tiles");
-  __shared__ __align__(16) uint16_t xb[SR][NIN];
-  __shared__ __align__(16) uint16_t xT[NIN][CS];
-  __shared__ __align__(16) uint16_t y1b[SR][RS];   // bf16 GELU(Z1)
-  __shared__ __align__(16) uint16_t y1T[NHID][CS]; // the same by columns, then bf16 dZ1
-  __shared__ __align__(16) uint16_t y2b[SR][RS];   // bf16 GELU(Z2), then bf16 dZ2
-  __shared__ __align__(16) uint16_t y2T[NHID][CS];
-  __shared__ float zf[SR][ZS];                     // dZ2, then dZ1 (bias gradients)
-  __shared__ float yv[SR][NOUT];                   // Y, then dY
-  __shared__ __align__(16) uint16_t dyb[SR][NOUT];
-  __shared__ __align__(16) uint16_t dyT[NOUT][CS];
+  constexpr int RS = NHID + 8;  // row of a tile (16-bit words; 16-byte aligned, off the bank stride)
+  static_assert(NHID == 16 * (STEP_THREADS / 64) && SB == 16, "one column tile per wave, one row tile");
+  __shared__ __align__(16) uint16_t xb[SB][NIN];
+  __shared__ __align__(16) uint16_t y1b[SB][RS];   // bf16 GELU(Z1)
+  __shared__ __align__(16) uint16_t y2b[SB][RS];   // bf16 GELU(Z2), then bf16 dZ2
+  __shared__ float yv[SB][NOUT];
+  __shared__ __align__(16) uint16_t dyb[SB][NOUT];
   __shared__ double dred[256];
   __shared__ float mk[4096];                       // mask values, 256 rows at a time
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int r = lane & 15, kq = (lane >> 4) * 8, rq = (lane >> 4) * 4;
-  const int row0 = blockIdx.x * SR;
+  const int row0 = blockIdx.x * SB;
+  const StepOut& o = a.o;
+  const size_t Bp = (size_t)o.Bp;
   const uint16_t* W1 = a.pb + OFF_W1;
   const uint16_t* W2 = a.pb + OFF_W2;
   const uint16_t* W3 = a.pb + OFF_W3;
-  float* G = a.part + (size_t)blockIdx.x * NPARAM;
   const int n = wv * 16 + r;  // this lane's hidden column
+  // this lane's four rows of column c of a tile, by columns and by rows
+  auto put = [&](uint16_t* by_col, int c, ushort4 t) {
+    *reinterpret_cast<ushort4*>(by_col + (size_t)c * Bp + row0 + rq) = t;
+  };
 
   // Loads in two rounds: the rows of this block and of the minibatch's mask
   // (every index clamped, so that no branch comes between loads) with the
   // forward weights of this wave's columns, then what those rows hold.
-  // Thread t of the first half takes input and output t % 16 of row t / 16.
-  static_assert(NIN == NOUT && SR * NIN == STEP_THREADS / 2, "one input and one output per thread");
-  const int xr = (tid & 511) / NIN, xj = tid % NIN;
-  const bool have = tid < SR * NIN && row0 + xr < a.rows;
+  // Thread t of the first quarter takes input and output t % 16 of row t / 16.
+  static_assert(NIN == NOUT && SB * NIN == STEP_THREADS / 4, "one input and one output per thread");
+  const int xr = (tid & 255) / NIN, xj = tid % NIN;
+  const bool have = tid < SB * NIN && row0 + xr < a.rows;
   const int id = a.order[min(row0 + xr, a.rows - 1)];
   const int nmask = a.rows * NOUT;
   int mid[4];
@@ -305,7 +318,7 @@ __global__ __launch_bounds__(STEP_THREADS) void k_mlp_step(StepArgs a) {
   for (int q = 0; q < 4; q++) mid[q] = a.order[min(q * STEP_THREADS + tid, nmask - 1) / NOUT];
   const bf16x8 w1 = kq < NIN ? *reinterpret_cast<const bf16x8*>(W1 + n * NIN + kq) : bf8_zero();
   const float bias1 = a.params[OFF_B1 + n], bias2 = a.params[OFF_B2 + n];
-  bf16x8 w2[NHID / 32];
+  bf16x8 w2[NHID / 32], w2c[NHID / 32];
 #pragma unroll
   for (int k = 0; k < NHID / 32; k++)
     w2[k] = *reinterpret_cast<const bf16x8*>(W2 + n * NHID + k * 32 + kq);
@@ -316,66 +329,64 @@ __global__ __launch_bounds__(STEP_THREADS) void k_mlp_step(StepArgs a) {
   float mv[4];
 #pragma unroll
   for (int q = 0; q < 4; q++) mv[q] = a.Mk[(size_t)mid[q] * NOUT + tid % NOUT];
-  if (tid < SR * NIN) {
+  if (tid < SB * NIN) {
     const uint16_t v = have ? f2bf(tx) : (uint16_t)0;
     xb[xr][xj] = v;
-    xT[xj][xr] = v;
+    o.x[(size_t)xj * Bp + row0 + xr] = v;
   }
   lds_barrier();
 
   // Z1 = Xb W1^T + b1 (K = 16: lanes of k >= 16 supply zeros), Y1 = GELU(Z1)
-  float z1[2][4], z2[2][4];
-#pragma unroll
-  for (int mt = 0; mt < 2; mt++) {
-    const bf16x8 av = kq < NIN ? bf8_lds(&xb[mt * 16 + r][kq]) : bf8_zero();
+  float z1[4], z2[4];
+  {
+    const bf16x8 av = kq < NIN ? bf8_lds(&xb[r][kq]) : bf8_zero();
     const floatx4 acc = mfma(av, w1, floatx4{0.f, 0.f, 0.f, 0.f});
     ushort4 t;
     uint16_t* tv = reinterpret_cast<uint16_t*>(&t);
 #pragma unroll
     for (int q = 0; q < 4; q++) {
-      z1[mt][q] = acc[q] + bias1;
-      tv[q] = f2bf(gelu(z1[mt][q]));
-      y1b[mt * 16 + rq + q][n] = tv[q];
+      z1[q] = acc[q] + bias1;
+      tv[q] = f2bf(gelu(z1[q]));
+      y1b[rq + q][n] = tv[q];
     }
-    *reinterpret_cast<ushort4*>(&y1T[n][mt * 16 + rq]) = t;
+    put(o.y1, n, t);
   }
+  // the backward weights: W2 and W3 by columns
+#pragma unroll
+  for (int k = 0; k < NHID / 32; k++)
+    w2c[k] = a.w2t ? *reinterpret_cast<const bf16x8*>(a.w2t + n * NHID + k * 32 + kq)
+                   : bf8_strided(W2 + (size_t)(k * 32 + kq) * NHID + n, NHID);
+  const bf16x8 w3 = kq < NOUT ? bf8_strided(W3 + (size_t)kq * NHID + n, NHID) : bf8_zero();
   lds_barrier();
   // Z2 = Y1b W2^T + b2, Y2 = GELU(Z2)
-#pragma unroll
-  for (int mt = 0; mt < 2; mt++) {
+  {
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int k = 0; k < NHID / 32; k++) acc = mfma(bf8_lds(&y1b[mt * 16 + r][k * 32 + kq]), w2[k], acc);
+    for (int k = 0; k < NHID / 32; k++) acc = mfma(bf8_lds(&y1b[r][k * 32 + kq]), w2[k], acc);
     ushort4 t;
     uint16_t* tv = reinterpret_cast<uint16_t*>(&t);
 #pragma unroll
     for (int q = 0; q < 4; q++) {
-      z2[mt][q] = acc[q] + bias2;
-      tv[q] = f2bf(gelu(z2[mt][q]));
-      y2b[mt * 16 + rq + q][n] = tv[q];
+      z2[q] = acc[q] + bias2;
+      tv[q] = f2bf(gelu(z2[q]));
+      y2b[rq + q][n] = tv[q];
     }
-    *reinterpret_cast<ushort4*>(&y2T[n][mt * 16 + rq]) = t;
+    put(o.y2, n, t);
   }
-  // the backward weights: W2 by columns (over the forward ones), W3 by columns
-#pragma unroll
-  for (int k = 0; k < NHID / 32; k++)
-    w2[k] = a.w2t ? *reinterpret_cast<const bf16x8*>(a.w2t + n * NHID + k * 32 + kq)
-                  : bf8_strided(W2 + (size_t)(k * 32 + kq) * NHID + n, NHID);
-  const bf16x8 w3 = kq < NOUT ? bf8_strided(W3 + (size_t)kq * NHID + n, NHID) : bf8_zero();
 #pragma unroll
   for (int q = 0; q < 4; q++)
     mk[q * STEP_THREADS + tid] = q * STEP_THREADS + tid < nmask ? mv[q] : 0.f;
   lds_barrier();
   // Y = Y2b W3^T + b3
-  if (wv < 2) {
+  if (wv == 0) {
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int k0 = 0; k0 < NHID; k0 += 32)
-      acc = mfma(bf8_lds(&y2b[wv * 16 + r][k0 + kq]),
+      acc = mfma(bf8_lds(&y2b[r][k0 + kq]),
                  *reinterpret_cast<const bf16x8*>(W3 + r * NHID + k0 + kq), acc);
     const float bias3 = a.params[OFF_B3 + r];
 #pragma unroll
-    for (int q = 0; q < 4; q++) yv[wv * 16 + rq + q][r] = acc[q] + bias3;
+    for (int q = 0; q < 4; q++) yv[rq + q][r] = acc[q] + bias3;
   }
   // the minibatch's mask count: thread t < 256 adds entries t, t + 256, ...
   double c = 0.0;
@@ -389,17 +400,15 @@ __global__ __launch_bounds__(STEP_THREADS) void k_mlp_step(StepArgs a) {
       }
       lds_barrier();
     }
-    if (tid >= 768)  // (not the waves of the product above)
+    if (tid >= 768)  // (not the wave of the product above)
 #pragma unroll
       for (int q = 0; q < 16; q++) c += (double)mk[q * 256 + tid - 768];
   }
   if (tid >= 768) dred[tid - 768] = c;
   tree256(dred, tid);
   const double cnt = dred[0];
-  lds_barrier();  // dred is reused below
-  // masked MSE share and dY = 2 mask (y - t) / sum(mask)
-  __shared__ double derr[SR * NOUT];
-  if (tid < SR * NOUT) {
+  // squared errors and dY = 2 mask (y - t) / sum(mask)
+  if (tid < SB * NOUT) {
     double err = 0.0;
     float g = 0.f;
     if (have) {
@@ -408,143 +417,171 @@ __global__ __launch_bounds__(STEP_THREADS) void k_mlp_step(StepArgs a) {
       err = m * d * d;
       g = cnt > 0 ? (float)(2.0 * m * d / cnt) : 0.f;
     }
-    derr[tid] = err;
-    yv[xr][xj] = g;
-    dyb[xr][xj] = f2bf(g);
-    dyT[xj][xr] = f2bf(g);
+    const uint16_t gb = f2bf(g);
+    dyb[xr][xj] = gb;
+    o.err[(size_t)(row0 + xr) * NOUT + xj] = err;
+    o.fy[(size_t)(row0 + xr) * NOUT + xj] = g;
+    o.dy[(size_t)xj * Bp + row0 + xr] = gb;
   }
+  if (blockIdx.x == 0 && tid == 0) *o.cnt = cnt;
   lds_barrier();
-  if (tid < 256) dred[tid] = derr[tid] + derr[tid + 256];
-  // db3 (fixed row order) and dW3 = dYb^T Y2b (M = 16, N = 256, K = SR)
-  if (tid < NOUT) {
-    float sm = 0.f;
-    for (int rr = 0; rr < SR; rr++) sm += yv[rr][tid];
-    G[OFF_B3 + tid] = sm;
-  }
+  // dY2 = dYb W3 (K = 16), dZ2 = dY2 GELU'(Z2); its bf16 copy replaces Y2
+  // (y2b was read before the last barriers)
   {
-    const floatx4 acc = mfma(bf8_lds(&dyT[r][kq]), bf8_lds(&y2T[n][kq]), floatx4{0.f, 0.f, 0.f, 0.f});
-#pragma unroll
-    for (int q = 0; q < 4; q++) G[OFF_W3 + (size_t)(rq + q) * NHID + n] = acc[q];
-  }
-  wave_sync();  // y2T is rewritten by the wave that has just read it
-  // dY2 = dYb W3 (K = 16), dZ2 = dY2 GELU'(Z2); its bf16 copies replace Y2
-  // (each wave read only its own columns of y2T; y2b was read before the barrier)
-#pragma unroll
-  for (int mt = 0; mt < 2; mt++) {
-    const bf16x8 av = kq < NOUT ? bf8_lds(&dyb[mt * 16 + r][kq]) : bf8_zero();
+    const bf16x8 av = kq < NOUT ? bf8_lds(&dyb[r][kq]) : bf8_zero();
     const floatx4 acc = mfma(av, w3, floatx4{0.f, 0.f, 0.f, 0.f});
     ushort4 t;
     uint16_t* tv = reinterpret_cast<uint16_t*>(&t);
 #pragma unroll
     for (int q = 0; q < 4; q++) {
-      const int rr = mt * 16 + rq + q;
-      const float g = acc[q] * gelu_grad(z2[mt][q]);
+      const float g = acc[q] * gelu_grad(z2[q]);
       tv[q] = f2bf(g);
-      zf[rr][n] = g;
-      y2b[rr][n] = tv[q];
+      y2b[rq + q][n] = tv[q];
+      o.fz2[(size_t)(row0 + rq + q) * NHID + n] = g;
     }
-    *reinterpret_cast<ushort4*>(&y2T[n][mt * 16 + rq]) = t;
+    put(o.dz2, n, t);
   }
-  tree256(dred, tid);
-  if (tid == 0) {
-    a.lpart[2 * blockIdx.x] = dred[0];
-    a.lpart[2 * blockIdx.x + 1] = cnt;
-  }
-  // db2 and dW2 = dZ2b^T Y1b (M = N = 256, K = SR): this wave's 16 rows
-  if (tid < NHID) {
-    float sm = 0.f;
-#pragma unroll
-    for (int rr = 0; rr < SR; rr++) sm += zf[rr][tid];
-    G[OFF_B2 + tid] = sm;
-  }
+  lds_barrier();
+  // dY1 = dZ2b W2, dZ1 = dY1 GELU'(Z1)
   {
-    const bf16x8 av = bf8_lds(&y2T[n][kq]);
-#pragma unroll 4
-    for (int nt = 0; nt < NHID / 16; nt++) {
-      const floatx4 acc = mfma(av, bf8_lds(&y1T[nt * 16 + r][kq]), floatx4{0.f, 0.f, 0.f, 0.f});
-#pragma unroll
-      for (int q = 0; q < 4; q++) G[OFF_W2 + (size_t)(wv * 16 + rq + q) * NHID + nt * 16 + r] = acc[q];
-    }
-  }
-  // dY1 = dZ2b W2, dZ1 = dY1 GELU'(Z1); its bf16 copy replaces Y1
-  float g1[2][4];
-#pragma unroll
-  for (int mt = 0; mt < 2; mt++) {
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int k = 0; k < NHID / 32; k++) acc = mfma(bf8_lds(&y2b[mt * 16 + r][k * 32 + kq]), w2[k], acc);
-#pragma unroll
-    for (int q = 0; q < 4; q++) g1[mt][q] = acc[q] * gelu_grad(z1[mt][q]);
-  }
-  lds_barrier();  // every wave has read y1T and the bias sums zf
-#pragma unroll
-  for (int mt = 0; mt < 2; mt++) {
+    for (int k = 0; k < NHID / 32; k++) acc = mfma(bf8_lds(&y2b[r][k * 32 + kq]), w2c[k], acc);
     ushort4 t;
     uint16_t* tv = reinterpret_cast<uint16_t*>(&t);
 #pragma unroll
     for (int q = 0; q < 4; q++) {
-      tv[q] = f2bf(g1[mt][q]);
-      zf[mt * 16 + rq + q][n] = g1[mt][q];
+      const float g = acc[q] * gelu_grad(z1[q]);
+      tv[q] = f2bf(g);
+      o.fz1[(size_t)(row0 + rq + q) * NHID + n] = g;
     }
-    *reinterpret_cast<ushort4*>(&y1T[n][mt * 16 + rq]) = t;
-  }
-  lds_barrier();
-  // db1 and dW1 = dZ1b^T Xb (M = 256, N = 16, K = SR)
-  if (tid < NHID) {
-    float sm = 0.f;
-#pragma unroll
-    for (int rr = 0; rr < SR; rr++) sm += zf[rr][tid];
-    G[OFF_B1 + tid] = sm;
-  }
-  {
-    const floatx4 acc = mfma(bf8_lds(&y1T[n][kq]), bf8_lds(&xT[r][kq]), floatx4{0.f, 0.f, 0.f, 0.f});
-#pragma unroll
-    for (int q = 0; q < 4; q++) G[OFF_W1 + (size_t)(wv * 16 + rq + q) * NIN + r] = acc[q];
+    put(o.dz1, n, t);
   }
 }
 
-// bf16 W2, transposed (see StepArgs::w2t; k_mlp_reduce_adam keeps it current).
+// bf16 W2, transposed (see StepArgs::w2t; k_mlp_grad_adam keeps it current).
 __global__ void k_w2_transpose(const uint16_t* pb, uint16_t* w2t) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;  // over W2, row-major
   if (i < NHID * NHID) w2t[(i % NHID) * NHID + i / NHID] = pb[OFF_W2 + i];
 }
 
-// Gradient = the blocks' shares summed in block order; Adam step; the
-// minibatch loss (sum of the shares over the mask count) into *loss.
-__global__ void k_mlp_reduce_adam(const float* part, int nblk, float* grads, float* p, float* m,
-                                  float* v, uint16_t* pb, float lr, float b1, float omb1, float b2,
-                                  float omb2, float eps, float c1, float c2, const double* lpart,
-                                  double* loss, uint16_t* w2t) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) {
+struct GradArgs {
+  StepOut o;
+  float *grads, *p, *m, *v;
+  uint16_t* pb;
+  uint16_t* w2t;
+  float lr, b1, omb1, b2, omb2, eps, c1, c2;
+  double* loss;
+};
+// the Adam step of parameter i with gradient g; returns the bf16 copy
+__device__ __forceinline__ uint16_t adam_step(const GradArgs& a, int64_t i, float g) {
+  a.grads[i] = g;
+  const float mi = a.b1 * a.m[i] + a.omb1 * g;
+  const float vi = a.b2 * a.v[i] + a.omb2 * g * g;
+  a.m[i] = mi;
+  a.v[i] = vi;
+  const float mh = mi / a.c1, vh = vi / a.c2;
+  const float pi = a.p[i] - a.lr * mh / (sqrtf(vh) + a.eps);
+  a.p[i] = pi;
+  const uint16_t b = f2bf(pi);
+  a.pb[i] = b;
+  return b;
+}
+
+// Gradient = the SR-row shares summed in order, then the Adam step; the
+// minibatch loss (the shares' squared errors over the mask count) into *loss.
+// Blocks of one wave: W2_TILES + 32 weight tiles, BIAS_BLOCKS bias blocks, one
+// for the loss.
+constexpr int HT = NHID / 16, W2_TILES = HT * HT, BIAS_BLOCKS = (2 * NHID + NOUT) / 8;
+constexpr int GRAD_BLOCKS = W2_TILES + 2 * HT + BIAS_BLOCKS + 1;
+__global__ __launch_bounds__(64) void k_mlp_grad_adam(GradArgs a) {
+  const int lane = threadIdx.x, r = lane & 15, kq = (lane >> 4) * 8, rq = (lane >> 4) * 4;
+  const int blk = blockIdx.x;
+  const size_t Bp = (size_t)a.o.Bp;
+  const int nsh = a.o.Bp / SR;
+  if (blk < W2_TILES + 2 * HT) {
+    // rows of the tile: columns m0 of A; columns of the tile: columns n0 of B
+    const uint16_t *A, *B;
+    int m0, n0, ld;
+    int64_t off;
+    bool is_w2 = false;
+    if (blk < W2_TILES) {
+      A = a.o.dz2, B = a.o.y1, m0 = blk / HT * 16, n0 = blk % HT * 16, ld = NHID, off = OFF_W2;
+      is_w2 = true;
+    } else if (blk < W2_TILES + HT) {
+      A = a.o.dz1, B = a.o.x, m0 = (blk - W2_TILES) * 16, n0 = 0, ld = NIN, off = OFF_W1;
+    } else {
+      A = a.o.dy, B = a.o.y2, m0 = 0, n0 = (blk - W2_TILES - HT) * 16, ld = NHID, off = OFF_W3;
+    }
+    const uint16_t* pa = A + (size_t)(m0 + r) * Bp + kq;
+    const uint16_t* pbv = B + (size_t)(n0 + r) * Bp + kq;
+    floatx4 g = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < nsh; s0 += 8) {
+      bf16x8 av[8], bv[8];
+#pragma unroll
+      for (int u = 0; u < 8; u++) {
+        const int s = min(s0 + u, nsh - 1);
+        av[u] = *reinterpret_cast<const bf16x8*>(pa + s * SR);
+        bv[u] = *reinterpret_cast<const bf16x8*>(pbv + s * SR);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; u++)
+        if (s0 + u < nsh) {
+          const floatx4 d = mfma(av[u], bv[u], floatx4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+          for (int q = 0; q < 4; q++) g[q] += d[q];
+        }
+    }
+    ushort4 t;
+    uint16_t* tv = reinterpret_cast<uint16_t*>(&t);
+#pragma unroll
+    for (int q = 0; q < 4; q++) tv[q] = adam_step(a, off + (int64_t)(m0 + rq + q) * ld + n0 + r, g[q]);
+    if (is_w2 && a.w2t)
+      *reinterpret_cast<ushort4*>(a.w2t + (size_t)(n0 + r) * NHID + m0 + rq) = t;
+  } else if (blk < W2_TILES + 2 * HT + BIAS_BLOCKS) {
+    // eight columns, one share per lane of a column at a time
+    const int col = (blk - W2_TILES - 2 * HT) * 8 + (lane & 7), sl = lane >> 3;
+    const float* src;
+    int ld;
+    int64_t i;
+    if (col < NHID) {
+      src = a.o.fz1 + col, ld = NHID, i = OFF_B1 + col;
+    } else if (col < 2 * NHID) {
+      src = a.o.fz2 + col - NHID, ld = NHID, i = OFF_B2 + col - NHID;
+    } else {
+      src = a.o.fy + col - 2 * NHID, ld = NOUT, i = OFF_B3 + col - 2 * NHID;
+    }
+    float g = 0.f;
+    for (int s0 = 0; s0 < nsh; s0 += 8) {
+      const int s = min(s0 + sl, nsh - 1);
+      float e[SR];
+#pragma unroll
+      for (int k = 0; k < SR; k++) e[k] = src[(size_t)(s * SR + k) * ld];
+      float sm = 0.f;
+#pragma unroll
+      for (int k = 0; k < SR; k++) sm += e[k];
+#pragma unroll
+      for (int u = 0; u < 8; u++) {
+        const float x = __shfl(sm, u * 8 + (lane & 7), 64);
+        if (s0 + u < nsh) g += x;
+      }
+    }
+    if (sl == 0) adam_step(a, i, g);
+  } else {
     double e = 0.0;
-    for (int b = 0; b < nblk; b++) e += lpart[2 * b];
-    const double cnt = lpart[1];
-    *loss = cnt > 0 ? e / cnt : 0.0;
-  }
-  if (i >= NPARAM) return;
-  const float m0 = m[i], v0 = v[i], p0 = p[i];
-  // shares loaded eight at a time, added in block order
-  float gi = 0.f;
-  for (int b0 = 0; b0 < nblk; b0 += 8) {
-    float g8[8];
+    for (int s = 0; s < nsh; s++) {
+      const double* d = a.o.err + (size_t)s * SR * NOUT;
+      double q[4];
 #pragma unroll
-    for (int q = 0; q < 8; q++) g8[q] = b0 + q < nblk ? part[(size_t)(b0 + q) * NPARAM + i] : 0.f;
+      for (int u = 0; u < 4; u++) q[u] = d[lane + 64 * u] + d[lane + 64 * u + 256];
+      double v = (q[0] + q[2]) + (q[1] + q[3]);
 #pragma unroll
-    for (int q = 0; q < 8; q++)
-      if (b0 + q < nblk) gi += g8[q];
+      for (int h = 32; h > 0; h >>= 1) v += __shfl_down(v, h, 64);
+      e += v;
+    }
+    const double cnt = *a.o.cnt;
+    if (lane == 0) *a.loss = cnt > 0 ? e / cnt : 0.0;
   }
-  grads[i] = gi;
-  const float mi = b1 * m0 + omb1 * gi;
-  const float vi = b2 * v0 + omb2 * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  const float mh = mi / c1, vh = vi / c2;
-  const float pi = p0 - lr * mh / (sqrtf(vh) + eps);
-  p[i] = pi;
-  pb[i] = f2bf(pi);
-  const int64_t w = i - OFF_W2;
-  if (w2t && w >= 0 && w < NHID * NHID) w2t[(w % NHID) * NHID + w / NHID] = f2bf(pi);
 }
 
 }  // namespace mlp
