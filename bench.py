@@ -692,8 +692,8 @@ def main():
         # emission stage is H preparation, the count pass, its two scans and
         # the scatter), from the per-kernel pass
         np_steps = min(args.steps, 10)
-        emission = ("k_prep_h", "k_mix_keys", "k_fill_u32", "k_emit_count", "k_scan_cols",
-                    "k_scan_bins", "k_emit_scatter")
+        emission = ("k_prep", "k_mix_keys", "k_fill_u32", "k_emit_count", "k_scan",
+                    "k_emit_scatter")
         mt_ms = sum(per_kernel[k]["total_ms"] for k in per_kernel
                     if k not in emission) / np_steps
         mt_bytes = (pe + 2 * u + m_out) * R_BYTES

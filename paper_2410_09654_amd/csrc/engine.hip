@@ -877,7 +877,8 @@ int Engine::run(Call& c) {
       }
     } else {
     // 2^nbl hash bins per pass: NBINS_LOG while the call fits one pass,
-    // NBINS_LOG_WIDE while it fits one pass over those, else NBINS_LOG_MP (twice the records per pass) when it needs several, and
+    // NBINS_LOG_WIDE while it fits one pass over those, else NBINS_LOG_MP
+    // (twice the records per pass) when it needs several, and
     // NBINS_LOG_MID for calls of at most 2^22 records even if every pair emits
     // one (the per-call bin tables then cost a quarter)
     int nbl = NBINS_LOG;
@@ -981,7 +982,10 @@ int Engine::run(Call& c) {
       //    where the partitions below write and read every record twice: 96 M
       //    two-word records 6.8 -> 5.0 ms with the binning, the step 11.9 ->
       //    10.3 ms.  Not below 2^15 bins' worth: the open lines of 2^15 bins
-      //    fit an L2, those of 2^17 do not (23 M records 0.80 -> 1.19 ms).
+      //    fit an L2, those of 2^17 do not (23 M records 0.80 -> 1.19 ms).  Nor
+      //    translation-symmetric calls, whose binning runs beside the search
+      //    for the representatives on one workgroup per CU: a step of 102 M
+      //    one-word records 11.9 ms by partitions, 13.2 ms so.
       //  - Otherwise, and when a count does not fit after all: the count over
       //    2^14 bins, and partitions.
       const int64_t tiles = (c.O.n + EMIT_THREADS - 1) / EMIT_THREADS;
@@ -1005,7 +1009,7 @@ int Engine::run(Call& c) {
                            (double)nterm_rec;
         if (est > room * NBINS && est <= room * NBINS_MP) {
           nbl = NBINS_LOG_MP;
-        } else if (est > room * NBINS && est <= room * NBINS_WIDE) {
+        } else if (!c.ts && est > room * NBINS && est <= room * NBINS_WIDE) {
           wtiles = (int)std::min<int64_t>(tiles, WIDE_TILE_ROWS);
           wrows = wtiles * hseg + term_rows;
         }
@@ -1022,10 +1026,8 @@ int Engine::run(Call& c) {
         ea.comm_rows = wtiles * hseg;
         ea.counts8 = (uint8_t*)counts;
         ea.pre16 = pre16;
-        {
-          const int rows = wrows;
-          EMIT("k_emit_count", false, NBINS_LOG_WIDE);
-        }
+        LAUNCH("k_emit_count", (k_emit<W, F32, false, NBINS_LOG_WIDE, false>), wrows, EMIT_THREADS,
+               ea);
         LAUNCH("k_scan_wide", k_scan_wide, NBINS_WIDE / 128, 1024, (const uint8_t*)counts, wrows,
                pre16, wtotal, wbase, dctl, wlook);
         TRY(read_ctl());
@@ -1227,10 +1229,10 @@ int Engine::run(Call& c) {
           LAUNCH("k_split_scatter", (k_split<W, F32, true, NBINS_LOG_MP>), SPLIT_ROWS, 1024, sp);
         else if (scattered)
           ;  // launched before the count was read
-        else if (nbl == NBINS_LOG_WIDE) {
-          const int rows = wrows;
-          EMIT("k_emit_scatter", true, NBINS_LOG_WIDE);
-        } else if (nbl == NBINS_LOG_MID)
+        else if (nbl == NBINS_LOG_WIDE)
+          LAUNCH("k_emit_scatter", (k_emit<W, F32, true, NBINS_LOG_WIDE, false>), wrows,
+                 EMIT_THREADS, ea);
+        else if (nbl == NBINS_LOG_MID)
           EMIT("k_emit_scatter", true, NBINS_LOG_MID);
         else if (nbl == NBINS_LOG)
           EMIT("k_emit_scatter", true, NBINS_LOG);
@@ -1248,8 +1250,9 @@ int Engine::run(Call& c) {
         // of them when the largest bucket fits; when most do, the full-size
         // merge takes the others from a deferral list; else the full-size merge
         // takes every bucket, and also when there are so few that all run at
-        // once (its 1024 threads finish a bucket of 1000 records in 17 us, 512
-        // take 26).
+        // once (1024 threads end a bucket sooner than 512: the merge of a
+        // 3001-string step 9.2 -> 8.2 us, of a commutator at 2^18 strings of
+        // the N = 30 chain 26.2 -> 25.1 us).
         constexpr int SCAP = small_merge_cap<W, F32>();
         const unsigned int big = hctl->maxg[g_log];
         if (final_merge) {
