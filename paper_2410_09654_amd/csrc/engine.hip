@@ -2695,7 +2695,14 @@ static int gemm_launch(hipStream_t stream, const uint16_t* A, int lda, int trans
   g.N = N;
   g.K = K;
   g.epilogue = epilogue;
-  LAUNCH("k_gemm_bf16", mlp::k_gemm_bf16, dim3((N + 31) / 32, (M + 31) / 32), 256, g);
+  // both operands read along k in 16-byte words
+  const bool nt = !transA && transB && K % 8 == 0 && lda % 8 == 0 && ldb % 8 == 0 &&
+                  ((uintptr_t)A | (uintptr_t)B) % 16 == 0;
+  if (nt)
+    LAUNCH("k_gemm_nt", mlp::k_gemm_nt,
+           dim3((N + 16 * mlp::NT_TILES - 1) / (16 * mlp::NT_TILES), (M + 63) / 64), 256, g);
+  else
+    LAUNCH("k_gemm_bf16", mlp::k_gemm_bf16, dim3((N + 31) / 32, (M + 31) / 32), 256, g);
   return PAULI_OK;
 }
 

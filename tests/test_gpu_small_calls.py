@@ -86,6 +86,25 @@ def test_training_without_transposed_weights(pk, n, batch):
     assert hist[0][-1] < hist[0][0]
 
 
+# products whose operands are both read along k in 16-byte words (k in whole words), at the edges
+# of a block's 64 rows and 64 columns and with k tails: the same bits as the kernel that takes any
+# layout, which the same product with B laid out by rows goes to; k = 20 has no whole words
+@pytest.mark.parametrize("M,N,K", [(16, 16, 8), (48, 80, 24), (64, 64, 32), (80, 48, 40),
+                                   (112, 256, 256), (1040, 16, 264), (32, 32, 20)])
+def test_gemm_along_k(pk, M, N, K):
+    import torch
+    from paper_2410_09654_amd import surrogate
+    print(f"gemm along k {M}x{N}x{K}", flush=True)
+    g = torch.Generator().manual_seed(M + N + K)
+    A = torch.randn((M, K), generator=g).bfloat16().view(torch.int16).cuda()
+    B = torch.randn((N, K), generator=g).bfloat16().view(torch.int16).cuda()
+    got = surrogate.gemm_bf16(A, B, False, True)
+    assert torch.equal(got, surrogate.gemm_bf16(A, B.t().contiguous(), False, False))
+    exact = A.view(torch.bfloat16).double() @ B.view(torch.bfloat16).double().t()
+    scale = A.view(torch.bfloat16).double().abs() @ B.view(torch.bfloat16).double().abs().t()
+    assert bool(((got.double() - exact).abs() <= 2e-6 * scale).all())
+
+
 # appended buckets of 2^F (bound of 2^(10 + F) records): filled to their room of 1408 one-word or
 # 1344 two-word records, one above it, and above it but within the merge's 1984; every pair of
 # the product with a single string is one record, half of the key range is left empty
