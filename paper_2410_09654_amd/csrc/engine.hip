@@ -1114,6 +1114,22 @@ int Engine::run(Call& c) {
     uint32_t* const* ccnt = b2.ccnt;
 
     merge_common();
+    // Its blocks wait for the rows of the buckets before them, so one bucket
+    // with long runs (strings that many pairs meet in) holds up all that run
+    // beside it.  Such a call shows by a bucket far above the mean: records
+    // that meet by ones and twos stay within 6 standard deviations, long-run
+    // calls are 11 to 17 off (product of 120,320 strings of H^3, N = 32:
+    // 1.53 ms with the output in the merge, 1.32 without; of N = 40, 5.5 and
+    // 4.1; a Runge-Kutta step of the 8 x 8 lattice at 9: 36.5 and 37.9).  Nor
+    // in several passes (product of 2.0e8 pairs 49.5 and 31.2 ms).  Buckets
+    // that all run at once wait for little.
+    if (final_merge) {
+      int g = 4;
+      while (g > 0 && hctl->maxg[g] > (unsigned int)merge_cap<W>()) g--;
+      const double nb = std::ldexp(1.0, nbl - g), mean = (double)pe_all / nb;
+      final_merge = pass_bits == 0 && (nb <= MERGE_ONE_WAVE ||
+                                       (double)hctl->maxg[g] <= mean + 10.0 * std::sqrt(mean) + 10.0);
+    }
     if (final_merge) TRY(place_output(pe_all));
     ma.bin_base = bin_base;
     ma.recs = recs;
@@ -1215,9 +1231,8 @@ int Engine::run(Call& c) {
           pass_bits++;
           counted_mp = false;
           done = false;
-          // the earlier passes' merges filled the histogram and wrote rows
+          // the earlier passes' merges filled the histogram
           TRY(zero_u32(hist0, (size_t)HREP * SEL0_BINS));
-          TRY(zero_u32(&dctl->out_total, 2));
           break;
         }
         int g_log = 4;
@@ -1257,7 +1272,7 @@ int Engine::run(Call& c) {
         const unsigned int big = hctl->maxg[g_log];
         if (final_merge) {
           ma.look = look;
-          ma.hctl = pinned && npass == 1 ? hctl : nullptr;
+          ma.hctl = pinned ? hctl : nullptr;
           if (big <= (unsigned int)SCAP && nb_pass > MERGE_ONE_WAVE)
             LAUNCH("k_merge_small",
                    (k_merge<W, F32, MERGE_SMALL_THREADS, SCAP, MERGE_SMALL, false, true>), nb_pass,

@@ -58,6 +58,20 @@ def test_products_shared_over_h(pk, n, nh, no):
     same(pk.multiply(raw(pk, H), raw(pk, O), ws=ws).to_host(), oracle.product(H, O), "product")
 
 
+# powers of a chain: many pairs meet in one string, so the largest buckets are far above the mean
+# (16-19: few buckets, 24: more than run at once, one pass), and the same size without long runs
+@pytest.mark.parametrize("n", [16, 19, 24])
+@pytest.mark.parametrize("runs", [True, False])
+def test_products_with_long_runs(pk, n, runs):
+    print(f"long runs n={n} runs={runs}", flush=True)
+    H = wl.ising_chain(n, 0.5, 2.0)
+    ws = pk.Workspace(1 << 30)
+    A = pk.multiply(raw(pk, H), pk.multiply(raw(pk, H), raw(pk, H), ws=ws), ws=ws)
+    if not runs:
+        A = raw(pk, wl.random_operator(n, A.size, seed=n, density=0.7))
+    same(pk.multiply(raw(pk, H), A, ws=ws).to_host(), oracle.product(H, A.to_host()), "product")
+
+
 # minibatches that end inside a 32-row block, longer than the 256 rows whose mask is read ahead,
 # and a workspace with no room for the transposed weights: the same bits as with it
 @pytest.mark.parametrize("n,batch", [(31, 32), (300, 256), (700, 300), (513, 512)])
