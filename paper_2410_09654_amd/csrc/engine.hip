@@ -501,23 +501,25 @@ int Engine::run(Call& c) {
   memset(&g_stats, 0, sizeof(g_stats));
   // translation-symmetric commutator: H = sum_k T_k(H0), H0 listed over its
   // N translations (entry h N + k), then the plain commutator with every
-  // product string replaced by its orbit representative
-  if (c.ts && c.has_comm && c.H.n > 0) {
-    const int64_t nf = c.H.n * c.ts;
+  // product string replaced by its orbit representative.  c.H stays the
+  // caller's H0: a call that is redone (below) expands it again.
+  OpV H = c.H;
+  if (c.ts && c.has_comm && H.n > 0) {
+    const int64_t nf = H.n * c.ts;
     uint64_t* hx = (uint64_t*)ar->take((size_t)nf * 8 * W);
     uint64_t* hz = (uint64_t*)ar->take((size_t)nf * 8 * W);
     double2* hc = (double2*)ar->take((size_t)nf * sizeof(double2));
     if (ar->short_) return PAULI_EWORKSPACE;
-    LAUNCH("k_ts_expand", (k_ts_expand<W>), (nf + 255) / 256, 256, c.H.x, c.H.z, c.H.cap,
-           (const double2*)c.H.c, c.H.n, c.ts, hx, hz, hc);
-    c.H.x = hx;
-    c.H.z = hz;
-    c.H.c = hc;
-    c.H.n = nf;
-    c.H.cap = nf;
+    LAUNCH("k_ts_expand", (k_ts_expand<W>), (nf + 255) / 256, 256, H.x, H.z, H.cap,
+           (const double2*)H.c, H.n, c.ts, hx, hz, hc);
+    H.x = hx;
+    H.z = hz;
+    H.c = hc;
+    H.n = nf;
+    H.cap = nf;
   }
   // ----- inputs --------------------------------------------------------------
-  const bool comm = c.has_comm && c.H.n > 0 && c.O.n > 0;
+  const bool comm = c.has_comm && H.n > 0 && c.O.n > 0;
   int64_t tstart[MAX_TERMS + 1];
   tstart[0] = 0;
   for (int t = 0; t < c.n_terms; t++) tstart[t + 1] = tstart[t] + c.T[t].n;
@@ -529,12 +531,12 @@ int Engine::run(Call& c) {
   if (keep && words_of(keep->n_qubits) != W) return PAULI_EINVAL;
 
   // every string's contributions must fit one merge bucket
-  if (comm && c.H.n + c.n_terms + 8 > merge_cap<W>()) {
+  if (comm && H.n + c.n_terms + 8 > merge_cap<W>()) {
     g_last_error = "H has more strings than one merge bucket holds";
     return PAULI_EINVAL;
   }
   int comm_rows = 0, term_rows = 0, hseg = 1;
-  plan_rows(comm, c.H.n, c.O.n, nterm_rec, &comm_rows, &term_rows, &hseg);
+  plan_rows(comm, H.n, c.O.n, nterm_rec, &comm_rows, &term_rows, &hseg);
   const int rows = comm_rows + term_rows;
 
   // canonical linear combinations are merged from their terms (below), calls
@@ -547,7 +549,7 @@ int Engine::run(Call& c) {
   }
   const bool want_select = tr && tr->max_strings > 0;
   const unsigned long long rec_bound =
-      (comm ? (unsigned long long)c.H.n * (unsigned long long)c.O.n : 0ull) +
+      (comm ? (unsigned long long)H.n * (unsigned long long)c.O.n : 0ull) +
       (unsigned long long)nterm_rec;
   bool append = !direct && !run_counted && rows > 0 && rec_bound <= APPEND_MAX;
   constexpr int ACAP = append_cap<W>();
@@ -555,7 +557,7 @@ int Engine::run(Call& c) {
   while (rec_bound > (1024ull << append_F)) append_F++;
   Bufs1<W> b1;
   Bufs2 b2;
-  take_bufs1<W>(*ar, comm, c.H.n, n_keep, rows, b1);
+  take_bufs1<W>(*ar, comm, H.n, n_keep, rows, b1);
   if (append && !ar->short_) {
     const size_t mark_bottom = ar->bottom, mark_need = ar->need;
     // the records lie where the count matrix would
@@ -616,10 +618,10 @@ int Engine::run(Call& c) {
     PrepArgs pr;
     memset(&pr, 0, sizeof(pr));
     if (comm) {
-      pr.x = c.H.x;
-      pr.z = c.H.z;
-      pr.cap = c.H.cap;
-      pr.n = (int)c.H.n;
+      pr.x = H.x;
+      pr.z = H.z;
+      pr.cap = H.cap;
+      pr.n = (int)H.n;
     }
     pr.packed = Hk;
     pr.hidx = Hidx;
@@ -808,8 +810,8 @@ int Engine::run(Call& c) {
     ea.Hidx = Hidx;
     ea.hstart = hstart;
     ea.hspan = hspan;
-    ea.Hc = comm ? (const double2*)c.H.c : nullptr;
-    ea.nH = comm ? (int)c.H.n : 0;
+    ea.Hc = comm ? (const double2*)H.c : nullptr;
+    ea.nH = comm ? (int)H.n : 0;
     ea.has_comm = comm ? 1 : 0;
     ea.product = c.product ? 1 : 0;
     ea.ts_n = c.ts;
@@ -889,7 +891,7 @@ int Engine::run(Call& c) {
     uint32_t *wtotal = nullptr, *wbase = nullptr;
     unsigned long long* wlook = nullptr;
     uint32_t* defer = b1.defer;
-    if (rec_bound <= (1ull << (NBINS_LOG_MID + 10)) && (!comm || c.H.n < (1 << (NBINS_LOG_MID - 3))))
+    if (rec_bound <= (1ull << (NBINS_LOG_MID + 10)) && (!comm || H.n < (1 << (NBINS_LOG_MID - 3))))
       nbl = NBINS_LOG_MID;
     auto count_pass = [&](int pass_bits, uint32_t pass_id, bool read = true,
                           unsigned long long spec_cap = 0ull) -> int {
@@ -914,7 +916,7 @@ int Engine::run(Call& c) {
     // (9 bits over 2^12 bins)
     auto wide_for = [&](int bins_log) {
       const int64_t max_h = (1 << (std::min(bins_log, NBINS_LOG) - 3)) - 1;
-      bool w = comm && (c.H.n > max_h || c.ts);
+      bool w = comm && (H.n > max_h || c.ts);
       for (int t = 0; t < c.n_terms; t++) w = w || c.tlist[t];
       return w;
     };
@@ -996,7 +998,7 @@ int Engine::run(Call& c) {
         se.nO = WIDE_SAMPLE;
         se.n_terms = 0;
         se.hseg = (int)std::max<int64_t>(
-            1, std::min<int64_t>(HSEG_ROWS * EMIT_THREADS / WIDE_SAMPLE, c.H.n / HSEG_MIN));
+            1, std::min<int64_t>(HSEG_ROWS * EMIT_THREADS / WIDE_SAMPLE, H.n / HSEG_MIN));
         se.comm_rows = (int)(WIDE_SAMPLE / EMIT_THREADS) * se.hseg;
         {
           const EmitArgs& ea = se;
