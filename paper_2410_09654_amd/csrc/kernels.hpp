@@ -974,19 +974,29 @@ DEV Key<W> load_raw(const uint64_t* x, const uint64_t* z, int64_t cap, int64_t i
 // their order in any case, and for short ones, whose binary search below is a
 // chain of dependent loads (9 us for 16384 strings, and 2 us for the check as
 // a kernel of its own; 3.9 us here).
+// More than STREAM_GAP buckets between two strings (short terms beside a long
+// one, the ends of a term) are filled by the whole wave: a thread for each gap
+// took 147 us for 4 M one-word strings plus one, now 35.  A wave that sees a
+// descent, or the flag of one that did, fills nothing: with every string
+// filling the gap to its predecessor, two terms of 2^20 shuffled strings took
+// 3.2 ms, now 16 us.
+constexpr int STREAM_GAP = 8;
 template <int W>
 __global__ __launch_bounds__(256) void k_term_stream(TermView v, uint32_t mask, uint32_t* bounds,
                                                      unsigned int* flag) {
   const uint32_t nb = 1u << v.F;
+  const int lane = threadIdx.x & 63;
   int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
   bool bad = false;
+  const bool known =
+      __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
 #pragma unroll
   for (int t = 0; t < MAX_TERMS; t++) {
     if (t >= v.n_terms || !((mask >> t) & 1u)) continue;
     const int64_t n = v.tn[t];
+    int64_t from = 0, to = -1;  // bounds [from, to] are id
     if (id >= 0 && id <= n) {
-      uint32_t* bt = bounds + (size_t)t * (nb + 1);
-      int64_t from = 0, to = nb;  // bounds [from, to] are i
+      to = nb;
       if (id > 0) {
         const Key<W> p = mix_key<W>(load_raw<W>(v.tx[t], v.tz[t], v.tcap[t], id - 1));
         from = (v.F ? (int64_t)(p.w[0] >> (64 - v.F)) : 0) + 1;
@@ -999,11 +1009,26 @@ __global__ __launch_bounds__(256) void k_term_stream(TermView v, uint32_t mask, 
         const Key<W> m = mix_key<W>(load_raw<W>(v.tx[t], v.tz[t], v.tcap[t], 0));
         to = v.F ? (int64_t)(m.w[0] >> (64 - v.F)) : 0;
       }
-      for (int64_t b = from; b <= to; b++) bt[b] = (uint32_t)id;
+    }
+    if (!known && !__ballot(bad)) {
+      uint32_t* bt = bounds + (size_t)t * (nb + 1);
+      const bool wide = to - from >= STREAM_GAP;
+      if (!wide)
+        for (int64_t b = from; b <= to; b++) bt[b] = (uint32_t)id;
+      for (uint64_t m = __ballot(wide); m; m &= m - 1) {
+        const int l = __builtin_ctzll(m);
+        const uint32_t b0 = __shfl((uint32_t)from, l, 64), b1 = __shfl((uint32_t)to, l, 64);
+        const uint32_t first = __shfl((uint32_t)id, l, 64);
+        for (uint32_t b = b0 + lane; b <= b1; b += 64) bt[b] = first;
+      }
     }
     id -= n + 1;
   }
-  if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(flag, 1u);
+  // one store a block, and none when it is there already: an atomic from every
+  // wave in flight queued up for 0.1 ms
+  if (__syncthreads_or(bad ? 1 : 0) && threadIdx.x == 0 &&
+      __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)
+    st_agent(flag, 1u);
 }
 
 // bounds[t][b], b = 0 .. 2^F: the first string of term t whose bucket is at

@@ -96,3 +96,89 @@ def test_crowded_symmetric_call(pk, n, nh):
     assert pk.last_stats()["host_syncs"] == 2
     assert not broke and bg == b
     same(got.to_host(), want, "Lanczos step")
+
+
+def spread(pk, n, m, seed):
+    """A canonical operator of about m distinct strings of random letters on n sites."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    op = pk.PauliOp(n, m)
+    rows = lambda: torch.randint(0, 1 << 62, (op.W, m), generator=g, device="cuda")
+    for w in range(op.W):
+        sites = min(n - 64 * w, 62)
+        op.x[w] = rows()[0] & ((1 << sites) - 1)
+        op.z[w] = rows()[0] & ((1 << sites) - 1)
+    op.coef.copy_(torch.randint(1, 9, (m, 2), generator=g, device="cuda"))
+    op.size = m
+    return pk.canonicalize(op)
+
+
+def shuffled(pk, op, seed):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    p = torch.randperm(op.size, generator=g, device="cuda")
+    r = pk.PauliOp(op.n_qubits, op.size)
+    r.x, r.z, r.coef, r.size = op.x[:, p].contiguous(), op.z[:, p].contiguous(), op.coef[p], op.size
+    return r
+
+
+def kernel_us(pk, name, call, reps=5):
+    """Least time of one call's launches of a kernel."""
+    call()
+    best = np.inf
+    for _ in range(reps):
+        pk.profile_enable(True, only=[name])
+        call()
+        best = min(best, pk.profile_read()[name][1] * 1e3)
+    pk.profile_enable(False)
+    return best
+
+
+def equal(a, b):
+    import torch
+    m = a.size
+    return m == b.size and torch.equal(a.x[:, :m], b.x[:, :m]) and \
+        torch.equal(a.z[:, :m], b.z[:, :m]) and torch.equal(a.coef[:m], b.coef[:m])
+
+
+# The one pass over the terms of a linear combination reads every string twice and, in order,
+# writes each bucket bound once, so terms out of order (redone by emission) and terms of a few
+# strings beside a long one cost no more than a small multiple of it
+@pytest.mark.parametrize("n", [50, 100])
+@pytest.mark.parametrize("m", [1 << 20, (1 << 22) + 3])
+def test_term_pass_is_linear(pk, n, m):
+    ws = pk.Workspace(2 << 30)
+    A, B = spread(pk, n, m, 1), spread(pk, n, m // 2, 2)
+    A = pk.PauliOp.from_raw(n, *A.to_numpy())  # (as a program's own operator: order not known)
+    B = pk.PauliOp.from_raw(n, *B.to_numpy())
+    SA, SB = shuffled(pk, A, 3), shuffled(pk, B, 4)
+    out, out2 = pk.PauliOp(n, A.size + B.size), pk.PauliOp(n, A.size + B.size)
+    both = kernel_us(pk, "k_term_stream", lambda: pk.add(A, 0.5, B, 2.0, out=out, ws=ws))
+    mixed = kernel_us(pk, "k_term_stream", lambda: pk.add(SA, 0.5, SB, 2.0, out=out2, ws=ws))
+    print(f"terms n={n} m={m}: in order {both:.1f} us, shuffled {mixed:.1f} us", flush=True)
+    assert equal(out, out2)
+    assert mixed <= 3 * both + 50
+    t = pk.Trunc(max_strings=m // 3)
+    assert equal(pk.truncate(A, t, ws=ws), pk.truncate(SA, t, ws=ws))
+    for few in (0, 1, 77):
+        F = spread(pk, n, few, 5) if few else pk.PauliOp(n, 1)
+        us = kernel_us(pk, "k_term_stream", lambda: pk.add(A, 0.5, F, 2.0, out=out, ws=ws))
+        print(f"  with {few} strings {us:.1f} us", flush=True)
+        assert us <= 1.5 * both + 50
+        assert equal(out, pk.add(SA, 0.5, F, 2.0, out=out2, ws=ws))
+        assert out.size == A.size + few  # (no string in common)
+
+
+# one descent anywhere in a term of whole waves and tails is seen: at the first and last string,
+# inside a wave, across waves and across blocks
+@pytest.mark.parametrize("m", [2, 64, 65, 1000, 40000])
+def test_one_descent_is_seen(pk, m):
+    ws = pk.Workspace(256 << 20)
+    A = spread(pk, 50, m, 7)
+    want = pk.add(A, 0.5, A, 2.0, ws=ws)
+    for at in sorted({0, A.size - 2, min(62, A.size - 2), min(63, A.size - 2), min(255, A.size - 2)}):
+        r = np.arange(A.size)
+        r[[at, at + 1]] = r[[at + 1, at]]
+        x, z, c = A.to_numpy()
+        S = pk.PauliOp.from_raw(50, x[r], z[r], c[r])
+        assert equal(pk.add(S, 0.5, S, 2.0, ws=ws), want), at
