@@ -441,6 +441,20 @@ void take_bufs2(Arena& ar, size_t ptot, bool wide, bool partitioned, uint32_t ma
     }
 }
 
+// rows of an output at the top of the workspace
+struct OutRows {
+  uint64_t *x, *z;
+  void* c;
+};
+template <int W>
+OutRows take_rows(Arena& ar, size_t n, int f32) {
+  OutRows r;
+  r.x = (uint64_t*)ar.take_top(n * 8 * W);
+  r.z = (uint64_t*)ar.take_top(n * 8 * W);
+  r.c = ar.take_top(n * (f32 ? 8 : 16));
+  return r;
+}
+
 struct Engine {
   Arena* ar;
   hipStream_t stream;
@@ -551,6 +565,15 @@ int Engine::run(Call& c) {
   const unsigned long long rec_bound =
       (comm ? (unsigned long long)H.n * (unsigned long long)c.O.n : 0ull) +
       (unsigned long long)nterm_rec;
+  // rows of an output at the top of the workspace: it never exceeds the records
+  // emitted, nor max(M, |keep|) when a top-M cut is asked for
+  auto arena_rows = [&](unsigned long long records) -> size_t {
+    unsigned long long bound = records;
+    if (want_select)
+      bound = std::min<unsigned long long>(
+          bound, (unsigned long long)std::max<long long>((long long)tr->max_strings, n_keep));
+    return (size_t)std::max<unsigned long long>(bound, 1);
+  };
   bool append = !direct && !run_counted && rows > 0 && rec_bound <= APPEND_MAX;
   constexpr int ACAP = append_cap<W>();
   int append_F = 1;
@@ -566,6 +589,11 @@ int Engine::run(Call& c) {
     take_bufs2<W, F32>(*ar, (size_t)ACAP << append_F, true, false, 1u << append_F, want_select, b2,
                        false);
     b2.recs = b1.counts;
+    if (c.out.to_arena) {  // room for the output rows as well (place_output takes them)
+      const size_t mark_top = ar->top;
+      take_rows<W>(*ar, arena_rows(rec_bound), c.out.f32);
+      ar->top = mark_top;
+    }
     if (ar->short_) {  // the workspace holds the counted layout only
       ar->bottom = mark_bottom;
       ar->need = mark_need;
@@ -667,30 +695,22 @@ int Engine::run(Call& c) {
   wa.ctl = dctl;
   wa.out_f32 = c.out.f32;
   // where the output goes: the caller's operator, or the top of the workspace
-  // (it never exceeds the records emitted, nor max(M, |keep|) when a top-M cut
-  // is asked for)
   auto place_output = [&](unsigned long long records) -> int {
     if (c.out.to_arena) {
-      unsigned long long bound = records;
-      if (want_select)
-        bound = std::min<unsigned long long>(
-            bound, (unsigned long long)std::max<long long>((long long)tr->max_strings, n_keep));
-      const size_t n = (size_t)std::max<unsigned long long>(bound, 1);
-      uint64_t* ox = (uint64_t*)ar->take_top(n * 8 * W);
-      uint64_t* oz = (uint64_t*)ar->take_top(n * 8 * W);
-      void* oc = ar->take_top(n * (c.out.f32 ? 8 : 16));
+      const size_t n = arena_rows(records);
+      const OutRows rows = take_rows<W>(*ar, n, c.out.f32);
       if (ar->short_) return PAULI_EWORKSPACE;
       c.out.arena_op.W = W;
       c.out.arena_op.f32 = c.out.f32;
       c.out.arena_op.canon = 1;
       c.out.arena_op.n = 0;
       c.out.arena_op.cap = (int64_t)n;
-      c.out.arena_op.x = ox;
-      c.out.arena_op.z = oz;
-      c.out.arena_op.c = oc;
-      wa.ox = ox;
-      wa.oz = oz;
-      wa.oc = oc;
+      c.out.arena_op.x = rows.x;
+      c.out.arena_op.z = rows.z;
+      c.out.arena_op.c = rows.c;
+      wa.ox = rows.x;
+      wa.oz = rows.z;
+      wa.oc = rows.c;
       wa.ocap = (int64_t)n;
     } else {
       pauli_op* o = c.out.user;
@@ -1703,10 +1723,7 @@ void dry_call(Arena& ar, const DryCall& d, unsigned long long* pe_out) {
   take_bufs2<W, F32>(ar, (size_t)std::max<unsigned long long>(pe, 1), d.wide || (comm && (nH > max_h || d.ts)),
                      nbl == NBINS_LOG_MP, max_buckets, d.select, b2);
   if (d.out_arena >= 0) {
-    const size_t n = (size_t)std::max<int64_t>(d.out_arena, 1);
-    ar.take_top(n * 8 * W);
-    ar.take_top(n * 8 * W);
-    ar.take_top(n * (d.out_f32 ? 8 : 16));
+    take_rows<W>(ar, (size_t)std::max<int64_t>(d.out_arena, 1), d.out_f32);
   }
 }
 

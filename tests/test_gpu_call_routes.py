@@ -182,3 +182,20 @@ def test_one_descent_is_seen(pk, m):
         x, z, c = A.to_numpy()
         S = pk.PauliOp.from_raw(50, x[r], z[r], c[r])
         assert equal(pk.add(S, 0.5, S, 2.0, ws=ws), want), at
+
+
+# A call of at most 2^18 possible records is laid out for them in fixed buckets where that fits the
+# workspace together with an intermediate operator kept there, else counted: 51,754,240 bytes hold
+# the re-orthogonalised step's O' by the counted layout alone
+def test_small_step_in_its_least_workspace(pk):
+    n = 64
+    H = wl.random_local_strings(n, 127, 4, seed=1)
+    O = wl.random_local_strings(n, 1033, 10, seed=2)
+    O = oracle.canonicalize(wl.HostOp(n, O.x, O.z, O.coef))
+    assert H.n == 127 and O.n == 1033
+    dH, dO = raw(pk, H), pk.PauliOp.from_host(O)
+    want, b, _ = pk.lanczos_step(dH, None, dO, 0.0, ws=pk.Workspace(1 << 30), reorth=True)
+    least = pk.Workspace(51754240)
+    got, bl, _ = pk.lanczos_step(dH, None, dO, 0.0, ws=least, reorth=True)
+    assert least.nbytes == 51754240  # not refused (a refused call grows it)
+    assert bl == b and equal(got, want)
