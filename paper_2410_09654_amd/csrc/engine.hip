@@ -441,6 +441,18 @@ void take_bufs2(Arena& ar, size_t ptot, bool wide, bool partitioned, uint32_t ma
     }
 }
 
+// An append call (at most APPEND_MAX possible records): 2^append_bits buckets whose mean stays
+// within 1024 records, with room for append_cap each; the records lie where the count matrix would.
+inline int append_bits(unsigned long long rec_bound) {
+  int F = 1;
+  while (rec_bound > (1024ull << F)) F++;
+  return F;
+}
+template <int W, bool F32>
+void take_append(Arena& ar, int F, bool want_select, Bufs2& b) {
+  take_bufs2<W, F32>(ar, (size_t)append_cap<W>() << F, true, false, 1u << F, want_select, b, false);
+}
+
 // rows of an output at the top of the workspace
 struct OutRows {
   uint64_t *x, *z;
@@ -576,8 +588,7 @@ int Engine::run(Call& c) {
   };
   bool append = !direct && !run_counted && rows > 0 && rec_bound <= APPEND_MAX;
   constexpr int ACAP = append_cap<W>();
-  int append_F = 1;
-  while (rec_bound > (1024ull << append_F)) append_F++;
+  const int append_F = append_bits(rec_bound);
   Bufs1<W> b1;
   Bufs2 b2;
   take_bufs1<W>(*ar, comm, H.n, n_keep, rows, b1);
@@ -586,8 +597,7 @@ int Engine::run(Call& c) {
     // the records lie where the count matrix would
     static_assert(((size_t)ACAP << 8) * RB <= (size_t)256 * NBINS_MP * 4,
                   "the records of an append call fit the count matrix");
-    take_bufs2<W, F32>(*ar, (size_t)ACAP << append_F, true, false, 1u << append_F, want_select, b2,
-                       false);
+    take_append<W, F32>(*ar, append_F, want_select, b2);
     b2.recs = b1.counts;
     if (c.out.to_arena) {  // room for the output rows as well (place_output takes them)
       const size_t mark_top = ar->top;
@@ -1718,12 +1728,15 @@ void dry_call(Arena& ar, const DryCall& d, unsigned long long* pe_out) {
   const int table_bits = std::min(pass_bits + 2, MAX_PASS_BITS);
   const uint32_t max_buckets = (uint32_t)(1u << nbl) << table_bits;
   Bufs2 b2;
-  // source ids aside as the engine decides (7-bit H indices over 2^10 bins)
-  const int64_t max_h = pe <= APPEND_MAX ? 127 : 2047;
-  take_bufs2<W, F32>(ar, (size_t)std::max<unsigned long long>(pe, 1), d.wide || (comm && (nH > max_h || d.ts)),
+  const size_t mark_bottom = ar.bottom;
+  // source ids aside as the engine decides (wide_for)
+  take_bufs2<W, F32>(ar, (size_t)std::max<unsigned long long>(pe, 1), d.wide || (comm && (nH > 2047 || d.ts)),
                      nbl == NBINS_LOG_MP, max_buckets, d.select, b2);
-  if (d.out_arena >= 0) {
-    take_rows<W>(ar, (size_t)std::max<int64_t>(d.out_arena, 1), d.out_f32);
+  if (d.out_arena >= 0) take_rows<W>(ar, (size_t)std::max<int64_t>(d.out_arena, 1), d.out_f32);
+  if (pe <= APPEND_MAX) {
+    // the fixed buckets that such a call takes when they fit (up to 2.75 times the records)
+    ar.bottom = mark_bottom;
+    take_append<W, F32>(ar, append_bits(pe), d.select, b2);
   }
 }
 

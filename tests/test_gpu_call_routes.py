@@ -199,3 +199,24 @@ def test_small_step_in_its_least_workspace(pk):
     got, bl, _ = pk.lanczos_step(dH, None, dO, 0.0, ws=least, reorth=True)
     assert least.nbytes == 51754240  # not refused (a refused call grows it)
     assert bl == b and equal(got, want)
+
+
+# A workspace of the queried size lets a call of at most 2^18 possible records run with one wait:
+# bounds just above and at a power of two, one and two words, with and without a top-M cut
+@pytest.mark.parametrize("n", [50, 100])
+@pytest.mark.parametrize("na,nb", [(1, 1), (1, 2049), (5, 26215), (1, 131073), (1, 262144), (900, 200)])
+def test_queried_workspace_takes_one_wait(pk, n, na, nb):
+    A, B = spread(pk, n, na, 1), spread(pk, n, nb, 2)
+    assert A.size * B.size <= 1 << 18
+    big = pk.Workspace(1 << 30)
+    cut = pk.Trunc(max_strings=nb)
+    for op, t, fn in ((pk.PAULI_Q_MULTIPLY, None, lambda w: pk.multiply(A, B, ws=w)),
+                      (pk.PAULI_Q_MULTIPLY, cut, lambda w: pk.multiply(A, B, cut, ws=w)),
+                      (pk.PAULI_Q_COMMUTATOR, cut, lambda w: pk.commutator(A, B, cut, ws=w)),
+                      (pk.PAULI_Q_CANONICALIZE, None, lambda w: pk.canonicalize(B, ws=w))):
+        nbytes, _ = pk.workspace_query(op, A if op != pk.PAULI_Q_CANONICALIZE else None, B, None, t)
+        print(f"query n={n} {na} x {nb} op={op}: {nbytes}", flush=True)
+        ws = pk.Workspace(nbytes)
+        got = fn(ws)
+        assert ws.nbytes == nbytes and pk.last_stats()["host_syncs"] == 1, op
+        assert equal(got, fn(big)), op
