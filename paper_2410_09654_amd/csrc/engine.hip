@@ -323,7 +323,8 @@ static_assert(SPLIT_ROWS <= SC_ROWS_MAX, "k_scan_cols covers every split row");
 
 // An operator of few tiles would leave most CUs idle: its tiles are shared out
 // over H (*hseg workgroups each, at least HSEG_MIN entries of H per share), up
-// to HSEG_ROWS rows, which the count matrix holds room for in any case.  Ten
+// to HSEG_ROWS rows with those of the operator terms, which the count matrix
+// holds room for in any case.  Ten
 // noisy steps at 2^14 strings (16 tiles, |H| = 180) spent 102 + 61 us per
 // commutator in the scatter and the count on 16 of 256 CUs: 16.5 -> 11.7 ms;
 // a commutator of 77,777 two-word strings 304 -> 229 us (2^12 bins below 2^22
@@ -332,13 +333,14 @@ constexpr int64_t HSEG_ROWS = 256, HSEG_MIN = 8;
 inline void plan_rows(bool comm, int64_t nH, int64_t nO, int64_t nterm_rec, int* comm_rows,
                       int* term_rows, int* hseg) {
   const int64_t tiles = comm ? std::min<int64_t>((nO + EMIT_THREADS - 1) / EMIT_THREADS, COMM_ROWS_MAX) : 0;
-  *hseg = 1;
-  if (comm)
-    *hseg = (int)std::max<int64_t>(1, std::min<int64_t>(HSEG_ROWS / tiles, nH / HSEG_MIN));
-  *comm_rows = (int)tiles * *hseg;
   *term_rows = nterm_rec > 0
                    ? (int)std::min<int64_t>((nterm_rec + EMIT_THREADS - 1) / EMIT_THREADS, TERM_ROWS_MAX)
                    : 0;
+  *hseg = 1;
+  if (comm)
+    *hseg = (int)std::max<int64_t>(
+        1, std::min<int64_t>((HSEG_ROWS - *term_rows) / tiles, nH / HSEG_MIN));
+  *comm_rows = (int)tiles * *hseg;
 }
 
 // Hash passes from the largest bin of the NBINS_LOG-bin count: one pass when
@@ -394,9 +396,11 @@ void take_bufs1(Arena& ar, bool comm, int64_t nH, int64_t n_keep, int rows, Bufs
   b.hsum = (uint32_t*)ar.take(SEL_BINS * 4);
   b.h0sum = (uint32_t*)ar.take(SEL0_BINS * 4);
   b.psum = (unsigned long long*)ar.take(PLAN_PARTS * 4 * 8);
-  // (a merge defers buckets or looks back, never both)
-  b.look = (unsigned long long*)ar.take(NBINS_MP * 8);
-  b.defer = (uint32_t*)b.look;
+  b.defer = (uint32_t*)ar.take(NBINS_MP * 4);
+  // look-back states are in use where nothing is selected, this histogram
+  // (cleared before each use) where the host finishes a select
+  static_assert((size_t)HREP * SEL_BINS * 4 >= (size_t)NBINS_MP * 8, "a state per bin");
+  b.look = (unsigned long long*)b.histL[0];
 }
 
 // scratch taken after the count pass: records (and their partitions),
