@@ -35,6 +35,10 @@ constexpr int merge_cap() { return W == 1 ? MERGE_CAP : 1344; }
 // Records a bucket of an append call has room for: at most 1024 on average.
 template <int W>
 constexpr int append_cap() { return W == 1 ? 1408 : 1344; }
+// Words between the cursors of such buckets: a line each, since the atomics on one line run one
+// after the other (side by side, 16 or 32 to a line, the emission of 65536 listed strings took
+// 105 us, of 2^18 126; now 19 and 22).
+constexpr int CURSOR_STRIDE = 32;
 constexpr int MERGE_THREADS = 1024;   // 16 waves; two merge blocks per CU (8 waves/SIMD)
 // Small-bucket merge: 512 threads and an LDS footprint of at most 53 KiB
 // (keys, values and source ids per record plus the 8 KiB digit table), so

@@ -121,7 +121,8 @@ struct EmitArgs {
   const unsigned int* skip;  // scatter: nothing to do when *skip != 0 (nullable)
   // append mode (small calls, no count pass): bucket b (top append_F key bits)
   // holds up to append_cap records from b append_cap on, taken in any order by
-  // atomics on cursor[b], which counts on beyond append_cap; wide ids
+  // atomics on cursor[b CURSOR_STRIDE], which counts on beyond append_cap; wide
+  // ids
   uint32_t* cursor;
   int append_F;
   uint32_t append_cap;
@@ -222,7 +223,7 @@ __attribute__((amdgpu_waves_per_eu(W == 1 && NBL <= 14 ? 8 : 4))) void k_emit(Em
     if constexpr (append) {
       const int AF = a.append_F;
       const uint32_t b = (uint32_t)(mk.w[0] >> (64 - AF));
-      const uint32_t at = atomicAdd(&a.cursor[b], 1u);
+      const uint32_t at = atomicAdd(&a.cursor[b * CURSOR_STRIDE], 1u);
       if (at < a.append_cap) {
         const size_t pos = (size_t)b * a.append_cap + at;
         mk.w[0] &= ~0ull >> AF;
@@ -1057,7 +1058,7 @@ __global__ __launch_bounds__(256) void k_term_bounds(TermView v, uint32_t mask, 
 
 struct MergeArgs {
   const uint32_t* bin_base;
-  const uint32_t* bin_count;  // append mode: records of bucket j (from j append_cap on)
+  const uint32_t* bin_count;  // append mode: the cursors (bucket j lies from j append_cap on)
   uint32_t append_cap;
   int nbins_log;  // hash bins of the call: 2^nbins_log per pass
   int g_log;
@@ -1369,7 +1370,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
     }
     if (a.ctl->unsorted) b0 = b1 = 0u;  // the call is redone by emission
   } else if (MODE == MERGE_GRID && a.bin_count) {
-    const uint32_t cnt = a.bin_count[j];
+    const uint32_t cnt = a.bin_count[j * CURSOR_STRIDE];
     b0 = j * a.append_cap;
     // records beyond the bucket's room were not written: the call is redone
     b1 = b0 + (cnt > a.append_cap ? (uint32_t)CAP + 1u : cnt);
@@ -2654,7 +2655,7 @@ __global__ __launch_bounds__(1024) void k_prep(PrepArgs a) {
   __shared__ int bad;
   for (uint32_t q = t; q < sizeof(Ctl) / 4; q += 1024) reinterpret_cast<uint32_t*>(a.ctl)[q] = 0u;
   for (int q = t; q < SITES + 2; q += 1024) cnt[q] = 0u;
-  if (t < a.n_cursor) a.cursor[t] = 0u;
+  if (t < a.n_cursor) a.cursor[t * CURSOR_STRIDE] = 0u;
   if (t < a.n_look) a.look[t] = 0ull;
   if (t == 0) {
     span = 0;

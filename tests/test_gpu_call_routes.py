@@ -220,3 +220,15 @@ def test_queried_workspace_takes_one_wait(pk, n, na, nb):
         got = fn(ws)
         assert ws.nbytes == nbytes and pk.last_stats()["host_syncs"] == 1, op
         assert equal(got, fn(big)), op
+
+
+# the appended records of a call with up to 1024 to a bucket do not queue up at the bucket cursors
+@pytest.mark.parametrize("n", [50, 100])
+@pytest.mark.parametrize("m", [65536, 1 << 18])
+def test_appended_records_do_not_queue(pk, n, m):
+    ws = pk.Workspace(256 << 20)
+    ops = [shuffled(pk, spread(pk, n, k, k), 3) for k in (1000, m)]
+    few, many = (kernel_us(pk, "k_emit_append", lambda: pk.canonicalize(o, ws=ws)) for o in ops)
+    print(f"appended n={n}: 1000 strings {few:.1f} us, {m} strings {many:.1f} us", flush=True)
+    assert many <= 4 * few + 20
+    assert equal(pk.canonicalize(ops[1], ws=ws), spread(pk, n, m, m))
