@@ -12,7 +12,7 @@
  *   - Every pointer inside pauli_op and pauli_ws is a DEVICE pointer owned by
  *     the caller.  The library never allocates or frees device memory and
  *     keeps no pointer to caller memory after a call returns.  State kept
- *     between calls: a pinned host block (under 16 KiB) per calling thread
+ *     between calls: a pinned host block (under 32 KiB) per calling thread
  *     (allocated with hipHostMalloc on the thread's first call, kept until the
  *     process ends), two events and a side stream of default priority per
  *     calling thread (created on its first call, on the device then current;

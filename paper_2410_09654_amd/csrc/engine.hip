@@ -140,6 +140,8 @@ struct HostBlock {
   unsigned int bad;                          // an operand is not in canonical order
   double2 part[RED_SUMS * RED_BLOCKS];
 };
+static_assert(sizeof(HostBlock) < (32 << 10), "as the header says");
+constexpr int64_t LOOKUP_PINNED = 768;  // results of a lookup that go straight to pinned memory
 thread_local HostBlock* t_host = nullptr;
 thread_local hipEvent_t t_ctl_event = nullptr, t_scan_event = nullptr;
 thread_local hipStream_t t_side_stream = nullptr;  // on device t_side_dev
@@ -2589,8 +2591,8 @@ int pauli_coefficients(const pauli_op* A, const pauli_op* Q, double* out, pauli_
   if (ar.short_) return ws_short(ar, ws);
   HostBlock* h = nullptr;
   TRY(host_block(&h));
-  // few results go straight to pinned memory
-  const bool direct = Q->size <= RED_SUMS * RED_BLOCKS;
+  static_assert(LOOKUP_PINNED <= RED_SUMS * RED_BLOCKS, "results take the partials' room");
+  const bool direct = Q->size <= LOOKUP_PINNED;
   if (direct) res = h->part;
   const int64_t bq = (Q->size + 63) / 64;
   const int af32 = A->dtype == PAULI_C64K ? 1 : 0;

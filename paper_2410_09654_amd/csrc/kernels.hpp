@@ -2872,8 +2872,10 @@ __global__ __launch_bounds__(256) void k_ts_expand(const uint64_t* x, const uint
 // Reductions over an operator's strings: at most RED_BLOCKS blocks of
 // RED_THREADS threads leave double-double partials in pinned host memory, which
 // the host adds up after its one wait (a second kernel and a copy of its result
-// took longer than the sum).
-constexpr int RED_BLOCKS = 128, RED_THREADS = 1024;
+// took longer than the sum).  A block for every CU: with 128, half of them were
+// idle, and the inner product of 2^22 one-word strings took 254 us, now 168
+// (2^18: 48 and 43).
+constexpr int RED_BLOCKS = 256, RED_THREADS = 1024;
 DEV void red_part(dd s, double2* part) {
   __shared__ double rh[RED_THREADS / 64], rl[RED_THREADS / 64];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;

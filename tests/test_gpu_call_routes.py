@@ -232,3 +232,20 @@ def test_appended_records_do_not_queue(pk, n, m):
     print(f"appended n={n}: 1000 strings {few:.1f} us, {m} strings {many:.1f} us", flush=True)
     assert many <= 4 * few + 20
     assert equal(pk.canonicalize(ops[1], ws=ws), spread(pk, n, m, m))
+
+
+# reductions at the edge of one string per thread of their 256 blocks: integer sums, so exact
+@pytest.mark.parametrize("n", [50, 100])
+@pytest.mark.parametrize("m", [(1 << 18) - 1, 1 << 18, (1 << 18) + 1, (1 << 20) + 77])
+def test_reductions_around_their_grid(pk, n, m):
+    ws = pk.Workspace(256 << 20)
+    A = spread(pk, n, m, 1)
+    B = spread(pk, n, m, 1)
+    B.coef = (17 - A.coef[:, [1, 0]]).contiguous()  # the same strings
+    assert A.size == m
+    ar, ai, br, bi = (c[:m, k].double() for c in (A.coef, B.coef) for k in (0, 1))
+    norm = float((ar * ar + ai * ai).sum())
+    want = complex(float((ar * br + ai * bi).sum()), float((ar * bi - ai * br).sum()))
+    assert pk.norm2(A, ws=ws) == norm and pk.inner(A, B, ws=ws) == want
+    got = pk.correlator(A, B, ws=ws)
+    assert got == complex(want.real / norm, want.imag / norm)
