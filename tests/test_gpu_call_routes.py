@@ -249,3 +249,36 @@ def test_reductions_around_their_grid(pk, n, m):
     assert pk.norm2(A, ws=ws) == norm and pk.inner(A, B, ws=ws) == want
     got = pk.correlator(A, B, ws=ws)
     assert got == complex(want.real / norm, want.imag / norm)
+
+
+def part(pk, op, lo, hi):
+    r = pk.PauliOp(op.n_qubits, hi - lo, op.dtype)
+    r.x, r.z = op.x[:, lo:hi].contiguous(), op.z[:, lo:hi].contiguous()
+    r.coef, r.size = op.coef[lo:hi].contiguous(), hi - lo
+    return r
+
+
+def sum_of_parts(pk, H, O, parts, ws):
+    total = None
+    for k in range(parts):
+        c = pk.commutator(H, part(pk, O, O.size * k // parts, O.size * (k + 1) // parts), ws=ws)
+        total = c if total is None else pk.add(total, 1.0, c, 1.0, ws=ws)
+    return total
+
+
+# one pass over 2^15 bins after a count over 2^14 that some bin of was too full for: the merge
+# writes the output itself when the buckets are even
+def test_output_merge_after_a_second_count(pk):
+    ws = pk.Workspace(8 << 30)
+    H, O = spread(pk, 50, 40, 1), spread(pk, 50, 1750003, 2)
+    out = pk.PauliOp(50, H.size * O.size)
+    pk.commutator(H, O, out=out, ws=ws)
+    pk.profile_enable(True)
+    pk.commutator(H, O, out=out, ws=ws)
+    kernels = pk.profile_read()
+    pk.profile_enable(False)
+    st = pk.last_stats()
+    print(f"second count: {st}", flush=True)
+    assert st["passes"] == 1 and st["buckets"] == 1 << 15 and kernels["k_emit_count"][0] == 2
+    assert "k_write_out" not in kernels
+    assert equal(out, sum_of_parts(pk, H, O, 4, ws))
