@@ -2972,7 +2972,10 @@ int pauli_mlp_train(const pauli_mlp* net, const float* x, const float* t, const 
       sa.order = order + e * n + s0;
       sa.rows = rows;
       sa.o = so;
-      LAUNCH("k_mlp_step", k_mlp_step, so.Bp / SB, STEP_THREADS, sa);
+      if ((uintptr_t)net->params_bf16 % 16 == 0)
+        LAUNCH("k_mlp_step", k_mlp_step<true>, so.Bp / SB, STEP_THREADS, sa);
+      else
+        LAUNCH("k_mlp_step", k_mlp_step<false>, so.Bp / SB, STEP_THREADS, sa);
       step++;
       GradArgs ga;
       ga.o = so;

@@ -308,6 +308,12 @@ __device__ __forceinline__ bf16x8 bf8_strided(const uint16_t* p, int stride) {
   for (int q = 0; q < 8; q++) v[q] = __builtin_bit_cast(__bf16, p[q * stride]);
   return v;
 }
+// 8 consecutive bf16 weights, in one load where ALIGNED says that the weights start on 16 bytes
+template <bool ALIGNED>
+__device__ __forceinline__ bf16x8 bf8_weights(const uint16_t* p) {
+  if constexpr (ALIGNED) return *reinterpret_cast<const bf16x8*>(p);
+  else return bf8_strided(p, 1);
+}
 __device__ __forceinline__ floatx4 mfma(bf16x8 a, bf16x8 b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
@@ -329,6 +335,10 @@ __device__ __forceinline__ void tree256(double* d, int tid) {
   lds_barrier();
 }
 
+// ALIGNED: the caller's bf16 weights start on 16 bytes (each matrix of the
+// vector then does, see the offsets)
+static_assert(OFF_W1 % 8 == 0 && OFF_W2 % 8 == 0 && OFF_W3 % 8 == 0, "whole 16-byte words");
+template <bool ALIGNED>
 __global__ __launch_bounds__(STEP_THREADS) void k_mlp_step(StepArgs a) {
   constexpr int RS = NHID + 8;  // row of a tile (16-bit words; 16-byte aligned, off the bank stride)
   static_assert(NHID == 16 * (STEP_THREADS / 64) && SB == 16, "one column tile per wave, one row tile");
@@ -365,12 +375,12 @@ __global__ __launch_bounds__(STEP_THREADS) void k_mlp_step(StepArgs a) {
   int mid[4];
 #pragma unroll
   for (int q = 0; q < 4; q++) mid[q] = a.order[min(q * STEP_THREADS + tid, nmask - 1) / NOUT];
-  const bf16x8 w1 = kq < NIN ? *reinterpret_cast<const bf16x8*>(W1 + n * NIN + kq) : bf8_zero();
+  const bf16x8 w1 = kq < NIN ? bf8_weights<ALIGNED>(W1 + n * NIN + kq) : bf8_zero();
   const float bias1 = a.params[OFF_B1 + n], bias2 = a.params[OFF_B2 + n];
   bf16x8 w2[NHID / 32], w2c[NHID / 32];
 #pragma unroll
   for (int k = 0; k < NHID / 32; k++)
-    w2[k] = *reinterpret_cast<const bf16x8*>(W2 + n * NHID + k * 32 + kq);
+    w2[k] = bf8_weights<ALIGNED>(W2 + n * NHID + k * 32 + kq);
   const float tx = a.X[(size_t)id * NIN + xj];
   const float tt = a.T[(size_t)id * NOUT + xj], tm = a.Mk[(size_t)id * NOUT + xj];
   // the minibatch's mask, summed further down (every block sums the same
@@ -431,8 +441,7 @@ __global__ __launch_bounds__(STEP_THREADS) void k_mlp_step(StepArgs a) {
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int k0 = 0; k0 < NHID; k0 += 32)
-      acc = mfma(bf8_lds(&y2b[r][k0 + kq]),
-                 *reinterpret_cast<const bf16x8*>(W3 + r * NHID + k0 + kq), acc);
+      acc = mfma(bf8_lds(&y2b[r][k0 + kq]), bf8_weights<ALIGNED>(W3 + r * NHID + k0 + kq), acc);
     const float bias3 = a.params[OFF_B3 + r];
 #pragma unroll
     for (int q = 0; q < 4; q++) yv[rq + q][r] = acc[q] + bias3;

@@ -282,3 +282,25 @@ def test_output_merge_after_a_second_count(pk):
     assert st["passes"] == 1 and st["buckets"] == 1 << 15 and kernels["k_emit_count"][0] == 2
     assert "k_write_out" not in kernels
     assert equal(out, sum_of_parts(pk, H, O, 4, ws))
+
+
+# bf16 weights that do not start on 16 bytes (a program's own buffers, any element of them): the
+# same training run as with weights that do
+@pytest.mark.parametrize("at", [1, 4])
+def test_training_with_weights_off_16_bytes(pk, at):
+    import torch
+    from paper_2410_09654_amd import surrogate
+    g = torch.Generator().manual_seed(at)
+    x = 1.0 + 0.2 * torch.randn((300, 16), generator=g)
+    t = 1.0 + 0.2 * torch.randn((300, 16), generator=g)
+    m = (torch.rand((300, 16), generator=g) < 0.7).float()
+    nets = [surrogate.BnSurrogate(seed=1) for _ in range(2)]
+    own = torch.zeros(nets[1].n + 8, dtype=torch.int16, device="cuda")
+    own[at:at + nets[1].n] = nets[1].params_bf16
+    nets[1].params_bf16 = own[at:at + nets[1].n]
+    assert nets[0].params_bf16.data_ptr() % 16 == 0 and nets[1].params_bf16.data_ptr() % 16 == 2 * at
+    hist = [net.train(x, t, m, epochs=3, batch=96, seed=2) for net in nets]
+    assert hist[0] == hist[1] and hist[0][-1] < hist[0][0]
+    for k in ("params", "params_bf16", "grads", "adam_m", "adam_v"):
+        assert torch.equal(getattr(nets[0], k), getattr(nets[1], k)), k
+    assert torch.equal(nets[0].forward(x), nets[1].forward(x))
