@@ -597,6 +597,14 @@ def run_surrogate(args):
         "host": host_info()}), flush=True)
 
 
+def emission_kernel(name: str) -> bool:
+    """Kernels up to the records in their buckets: H preparation, sampling, count
+    passes and their scans, scatters, partitions and their binning."""
+    return name.startswith(("k_emit_", "k_split_")) or name in (
+        "k_prep", "k_mix_keys", "k_fill_u32", "k_ts_expand", "k_scan", "k_scan_wide",
+        "k_scan_cols", "k_scan_part", "k_part_from_bins")
+
+
 def main():
     args = parse()
     if args.calibrate_copy:
@@ -688,14 +696,11 @@ def main():
                     "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                     "traffic": measured_traffic(dom), "alg_bytes_per_launch": alg_bytes[dom],
                     "avg_ms_timed_region": ms / c, "launches_timed_region": c}
-        # merge + truncate stage: every kernel after the scatter (the
-        # emission stage is H preparation, the count pass, its two scans and
-        # the scatter), from the per-kernel pass
+        # merge + truncate stage: every kernel after the records lie in their
+        # buckets, from the per-kernel pass
         np_steps = min(args.steps, 10)
-        emission = ("k_prep", "k_mix_keys", "k_fill_u32", "k_emit_count", "k_scan",
-                    "k_emit_scatter")
         mt_ms = sum(per_kernel[k]["total_ms"] for k in per_kernel
-                    if k not in emission) / np_steps
+                    if not emission_kernel(k)) / np_steps
         mt_bytes = (pe + 2 * u + m_out) * R_BYTES
         roofline["merge_truncate"] = {"ms_per_step": round(mt_ms, 4),
                                       "alg_bytes": mt_bytes,
