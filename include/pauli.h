@@ -361,11 +361,11 @@ int pauli_mlp_adam(const pauli_mlp *net, double lr, double beta1, double beta2, 
 /* Minibatch training with the fused step kernels: for every epoch e and
  * minibatch k (rows order[e n + k batch ...], batch rows, the last one of an
  * epoch shorter when batch does not divide n), one kernel runs the forward
- * pass, the masked MSE and the backward pass of 32 rows per block with the
+ * pass, the masked MSE and the backward pass of 16 rows per block with the
  * activations in LDS and every product on the matrix cores (the BF16
- * operands and FP32 epilogues of pauli_mlp_loss_grad), a second sums the
- * blocks' gradient shares in block order and takes the Adam step (step
- * index t0 + 1, t0 + 2, ...).  x, t, mask: device [n][16]; order: device
+ * operands and FP32 epilogues of pauli_mlp_loss_grad), a second takes the
+ * weight gradients tile by tile, in shares of 32 rows added in order, and with
+ * each the Adam step (step index t0 + 1, t0 + 2, ...).  x, t, mask: device [n][16]; order: device
  * int32 [epochs][n], each a permutation of 0..n-1 (not checked); losses:
  * device double [epochs][ceil(n / batch)] receives every minibatch's loss;
  * net->grads holds the last minibatch's gradient.  1 <= batch <= 4096.

@@ -311,6 +311,7 @@ constexpr int EMIT_WINDOW_TILES = 32;
 // One-pass calls over 2^17 bins: strings whose pairs are counted for the
 // estimate, and rows of O tiles (one workgroup to a CU by LDS, two rounds)
 constexpr int64_t WIDE_SAMPLE = 64 * EMIT_THREADS, WIDE_TILE_ROWS = 512;
+static_assert(WIDE_SAMPLE <= 7 * NBINS, "an O of the sample's length never makes such a call");
 static_assert(WIDE_TILE_ROWS + TERM_ROWS_MAX <= SW_ROWS_MAX, "k_scan_wide covers every row");
 constexpr int MAX_PASS_BITS = 12;
 constexpr int DIRECT_MAX_F = 22;  // at most 2^22 buckets in a direct merge
@@ -439,7 +440,7 @@ void take_bufs2(Arena& ar, size_t ptot, bool wide, bool partitioned, uint32_t ma
   uint32_t** tabs[8] = {&b.b_ubase, &b.b_slots, &b.b_surv,  &b.b_keep,
                         &b.b_unique, &b.b_abv,  &b.b_bcnt, &b.b_obase};
   for (auto t : tabs) *t = (uint32_t*)ar.take((size_t)max_buckets * 4);
-  b.norm_part = (double2*)ar.take((size_t)max_buckets * sizeof(double2));
+  b.norm_part = (double2*)ar.take((size_t)NORM_BLOCKS * sizeof(double2));
   if (want_select)
     for (int k = 0; k < 3; k++) {
       b.cand[k] = (uint32_t*)ar.take(ptot * 4);
@@ -771,7 +772,6 @@ int Engine::run(Call& c) {
     ma.b_keep = b2.b_keep;
     ma.b_unique = b2.b_unique;
     ma.hist0 = hist0;
-    ma.norm_part = b2.norm_part;
     ma.ctl = dctl;
     ma.defer = nullptr;
   };
@@ -970,8 +970,8 @@ int Engine::run(Call& c) {
       const uint32_t mb = (1u << nbl) << 2;
       const size_t per = RB + KB + sizeof(double2) + (w14 ? 4 : 0) + (want_select ? 12 : 0) +
                          (c.out.to_arena ? (size_t)(16 * W + 16) : 0);
-      const size_t fixed = (size_t)mb * (9 * 4 + sizeof(double2) + (want_select ? 12 : 0)) +
-                           ((size_t)64 << 10);
+      const size_t fixed = (size_t)mb * (9 * 4 + (want_select ? 12 : 0)) +
+                           NORM_BLOCKS * sizeof(double2) + ((size_t)64 << 10);
       const size_t used = align256(ar->bottom) + ar->top;
       const size_t avail = ar->cap > used + fixed ? ar->cap - used - fixed : 0;
       const unsigned long long cap_rec =
@@ -1012,7 +1012,9 @@ int Engine::run(Call& c) {
     } else {
       // A call of more possible records than that: the number is estimated
       // from the pairs of the first WIDE_SAMPLE strings (45 us, host included),
-      // and the bins chosen by it.
+      // and the bins chosen by it.  (With no more strings of O than the sample
+      // takes, H, which is shorter than a bucket, cannot make that many
+      // records: they are operator terms, and go to the partitions.)
       //  - One pass over 2^15 bins: counted over those at once (a count over
       //    2^14 bins first took 0.21 of 2.43 ms for 23 M two-word FP32 records).
       //  - More, up to one pass over 2^17: counted over those, in bytes (which
@@ -1147,7 +1149,6 @@ int Engine::run(Call& c) {
     uint32_t* b_abv = b2.b_abv;
     uint32_t* b_bcnt = b2.b_bcnt;
     uint32_t* b_obase = b2.b_obase;
-    double2* norm_part = b2.norm_part;
     uint32_t* const* cand = b2.cand;
     uint32_t* const* ccnt = b2.ccnt;
 
@@ -1845,12 +1846,8 @@ int workspace_query(int op, const pauli_op* A, const pauli_op* B, const pauli_op
       d1.out_arena = (int64_t)std::max<unsigned long long>(
           (unsigned long long)d1.nH * (unsigned long long)d1.nO + (unsigned long long)d1.nterm, 1);
       dry(W, f32, ar, d1, &pe1);
-      // projections: flags, results, partials, order keys of O_cur / O_prev
+      // projections: order keys of O_cur / O_prev
       ar.bottom = 0;
-      ar.take(16);
-      ar.take(6 * 16);
-      ar.take((size_t)1024 * 16);
-      ar.take((size_t)1024 * 16);
       ar.take((size_t)std::max<int64_t>(std::max(sz(B), sz(C)), 1) * 16 * W);
       d.nterm = d1.out_arena + sz(B) + sz(C);
       d.n_terms = 3;
@@ -1889,14 +1886,9 @@ int workspace_query(int op, const pauli_op* A, const pauli_op* B, const pauli_op
       break;
     }
     case PAULI_Q_REDUCTION: {
-      // norm2, inner, trace, coefficients, norm2_ts1d: partials and order keys
-      const int64_t n = std::max(sz(A), sz(B));
-      ar.take(sizeof(Ctl));
-      ar.take((size_t)std::max<int64_t>(n, 1) * 16 * W);
-      ar.take((size_t)std::max<int64_t>(std::max(sz(A), sz(B)), 1) * 16);
-      ar.take((size_t)1024 * 16);
-      ar.take((size_t)1024 * 16);
-      ar.take(32);
+      // inner, correlator: order keys; coefficients: results (fewer bytes a
+      // string); the sums go to the thread's pinned block
+      ar.take((size_t)std::max<int64_t>(std::max(sz(A), sz(B)), 1) * 16 * W);
       cap = 0;
       break;
     }

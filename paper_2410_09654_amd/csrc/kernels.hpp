@@ -1089,7 +1089,6 @@ struct MergeArgs {
   uint32_t* b_keep;
   uint32_t* b_unique;
   uint32_t* hist0;
-  double2* norm_part;
   uint32_t* defer;  // buckets above the small variant's capacity (nullptr: none deferred)
   Ctl* ctl;
   TermView tv;      // direct merges: the canonical terms and their bucket runs
@@ -2077,39 +2076,6 @@ __global__ __launch_bounds__(256) void k_norm(const uint32_t* b_ubase, const uin
   if (tid == 0) {
     ctl->norm_hi = v.hi;
     ctl->norm_lo = v.lo;
-  }
-}
-
-// Totals of the per-bucket counters (one block): slots, survivors, keep-set
-// survivors, nonzero uniques.
-__global__ __launch_bounds__(1024) void k_bucket_totals(const uint32_t* b_slots,
-                                                        const uint32_t* b_surv,
-                                                        const uint32_t* b_keep,
-                                                        const uint32_t* b_unique, uint32_t nb,
-                                                        Ctl* ctl) {
-  __shared__ unsigned long long red[4][16];
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  unsigned long long v[4] = {0, 0, 0, 0};
-  for (uint32_t b = t; b < nb; b += 1024) {
-    v[0] += b_slots[b];
-    v[1] += b_surv[b];
-    v[2] += b_keep[b];
-    if (b_unique) v[3] += b_unique[b];
-  }
-  for (int q = 0; q < 4; q++) {
-    unsigned long long x = v[q];
-    for (int d = 32; d >= 1; d >>= 1) x += __shfl_down(x, d, 64);
-    if (lane == 0) red[q][wv] = x;
-  }
-  __syncthreads();
-  if (t == 0) {
-    unsigned long long tot[4] = {0, 0, 0, 0};
-    for (int q = 0; q < 4; q++)
-      for (int w = 0; w < 16; w++) tot[q] += red[q][w];
-    ctl->u_slots = tot[0];
-    ctl->surv_total = tot[1];
-    ctl->keep_total = tot[2];
-    if (b_unique) ctl->u_unique = tot[3];
   }
 }
 

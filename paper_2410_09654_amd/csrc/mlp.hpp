@@ -112,7 +112,6 @@ __global__ __launch_bounds__(256) void k_gemm_nt(GemmArgs g) {
   const uint16_t* pb = g.B + (size_t)(n0 + r) * g.ldb;
   const bf16x8 zero = {};
   floatx4 acc[NT_TILES] = {};
-#pragma unroll 4
   for (int k0 = 0; k0 < g.K; k0 += 32) {
     const int k = k0 + kq;
     const bool in = k < g.K;  // K is a multiple of 8
