@@ -98,8 +98,9 @@ def test_crowded_symmetric_call(pk, n, nh):
     same(got.to_host(), want, "Lanczos step")
 
 
-def spread(pk, n, m, seed):
-    """A canonical operator of about m distinct strings of random letters on n sites."""
+def spread(pk, n, m, seed, thin=0):
+    """A canonical operator of about m distinct strings of random letters on n sites, each bit of
+    the masks set with probability 2^-(1 + thin)."""
     import torch
     g = torch.Generator(device="cuda").manual_seed(seed)
     op = pk.PauliOp(n, m)
@@ -108,6 +109,9 @@ def spread(pk, n, m, seed):
         sites = min(n - 64 * w, 62)
         op.x[w] = rows()[0] & ((1 << sites) - 1)
         op.z[w] = rows()[0] & ((1 << sites) - 1)
+        for _ in range(thin):
+            op.x[w] &= rows()[0]
+            op.z[w] &= rows()[0]
     op.coef.copy_(torch.randint(1, 9, (m, 2), generator=g, device="cuda"))
     op.size = m
     return pk.canonicalize(op)
@@ -304,3 +308,66 @@ def test_training_with_weights_off_16_bytes(pk, at):
     for k in ("params", "params_bf16", "grads", "adam_m", "adam_v"):
         assert torch.equal(getattr(nets[0], k), getattr(nets[1], k)), k
     assert torch.equal(nets[0].forward(x), nets[1].forward(x))
+
+
+def kernels_of(pk, call):
+    call()
+    pk.profile_enable(True)
+    call()
+    k = pk.profile_read()
+    pk.profile_enable(False)
+    return {name: v[0] for name, v in k.items()}
+
+
+# calls too large for one pass over 2^14 bins take the route that their sampled estimate says: one
+# count over 2^15 bins, one over 2^17 in bytes, or, when 400 records of one string are more than a
+# byte counts, back to 2^14 and the partitions
+@pytest.mark.parametrize("n,no,thin,route", [(50, 2400001, 2, "2^15"), (50, 2400001, 0, "2^17"),
+                                             (100, 1700001, 0, "2^17"), (48, 640000, 0, "back")])
+def test_large_call_takes_its_route(pk, n, no, thin, route):
+    import torch
+    ws = pk.Workspace(24 << 30)
+    O = spread(pk, n, no, 2, thin)
+    if route == "back":
+        H, P = wl.same_key_runs(n, np.full(400, 2.0))
+        H, P = raw(pk, H), pk.PauliOp.from_host(P)
+        joined = pk.PauliOp(n, P.size + O.size)
+        joined.x[:] = torch.cat([P.x, O.x[:, :O.size]], 1)
+        joined.z[:] = torch.cat([P.z, O.z[:, :O.size]], 1)
+        joined.coef[:] = torch.cat([P.coef, O.coef[:O.size]])
+        joined.size = joined.capacity
+        O = joined
+    elif thin:  # one-site strings, which few thin strings anticommute with
+        H = raw(pk, wl.from_terms(n, [(0.5 * (1 + j % 3), [(p, j)]) for j in range(1, n + 1)
+                                      for p in "XZ"]))
+    else:
+        H = spread(pk, n, 100, 1)
+    assert H.size * O.size > 7 * (1 << 14) * (1984 if n <= 64 else 1344)
+    out = pk.PauliOp(n, 140 << 20)
+    k = kernels_of(pk, lambda: pk.commutator(H, O, out=out, ws=ws))
+    st = pk.last_stats()
+    print(f"route n={n} no={no}: {st} {k}", flush=True)
+    assert k["k_emit_sample"] == 1
+    assert ("k_scan_wide" in k) == (route != "2^15") and ("k_emit_part_scatter" in k) == (route == "back")
+    if route != "back":
+        assert st["passes"] == 1 and k["k_emit_count"] == 1 and k["k_emit_scatter"] == 1
+    else:
+        assert st["passes"] > 1 and k["k_emit_count"] == 2
+    total = sum_of_parts(pk, H, O, 16, ws)
+    assert equal(out, total)
+
+
+# the same with operator terms beside the pairs: a Lanczos step over 2^17 bins against its parts
+def test_large_step_with_terms(pk):
+    n, M = 100, 100000
+    ws = pk.Workspace(24 << 30)
+    H, O, P = spread(pk, n, 80, 1), spread(pk, n, 2200003, 2), spread(pk, n, 300001, 3)
+    out = pk.PauliOp(n, M)
+    got = []
+    k = kernels_of(pk, lambda: got.append(pk.lanczos_step(H, P, O, 2.0, pk.Trunc(max_strings=M), out=out, ws=ws)))
+    print(f"step {pk.last_stats()} {k}", flush=True)
+    assert k["k_scan_wide"] == 1 and "k_emit_part_scatter" not in k
+    full = pk.add(sum_of_parts(pk, H, O, 8, ws), 1.0, P, -2.0, ws=ws)
+    b = float(np.sqrt(pk.norm2(full, ws=ws)))
+    assert got[-1][1] == b and not got[-1][2]
+    assert equal(out, pk.truncate(pk.divide(full, b, ws=ws), pk.Trunc(max_strings=M), ws=ws))
