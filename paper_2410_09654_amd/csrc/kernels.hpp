@@ -1260,11 +1260,13 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
   // word (the next 32 key bits, then the source id), read from `swd` (which
   // aliases mk until the keys are written).  mk / sx then hold the keys and
   // SX words (group, position in the bucket) in sorted order; the values stay
-  // in sv where their records lie in the bucket, so each record is read from
-  // memory once, key and value together.  (Values written in sorted order were
+  // in sv where their records lie in the bucket, so a one-word record is read
+  // from memory once, key and value together.  (Values written in sorted order were
   // read a second time for it: 7 us of a block's 33 us, and in direct merges,
   // whose values lie in arrays of their own, from memory: 4.82 -> 3.59 ms for
-  // 137 M term strings, with the terms' pointers in LDS.)  dh holds the digit counts and starts, then the
+  // 137 M term strings, with the terms' pointers in LDS.)  Two-word records are
+  // read twice in any case, the value with the second read (with the first
+  // one the merge of 27 M of them took 0.84 ms, so 0.79).  dh holds the digit counts and starts, then the
   // level-0 histogram of |c|^2.  Two distinct keys of one digit group with
   // equal sort bits show up as adjacent entries with equal windows but
   // different keys; the block then ranks by full keys (merge_full_rank).
@@ -1558,7 +1560,6 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
         m = mix_key<W>(m);
       } else {
         m = recs[pos].k;
-        sv[i] = recs[pos].v;
         if (a.wide) rsx[k] = a.rsrc_wide[pos];
       }
       if constexpr (!DIRECT) {
@@ -1647,7 +1648,9 @@ __attribute__((amdgpu_waves_per_eu(MODE == MERGE_SMALL ? 6 : 8))) void k_merge(M
       } else if constexpr (DIRECT) {
         mk[fpos[k]] = mix_key<W>(term_raw(term_pos(i)));  // second read (cache)
       } else {
-        mk[fpos[k]] = order_key(b0 + i, recs[b0 + i].k);  // second read (cache)
+        const Rec<W, F32> r = recs[b0 + i];  // second read (cache)
+        mk[fpos[k]] = order_key(b0 + i, r.k);
+        sv[i] = r.v;
       }
       sx[fpos[k]] = (rsx[k] & ~SX_POS & ~(DIRECT ? 0u : SX_LONG)) | i;
     }
