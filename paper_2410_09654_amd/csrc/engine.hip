@@ -310,7 +310,9 @@ static_assert(COMM_ROWS_MAX + TERM_ROWS_MAX <= SC_ROWS_MAX, "k_scan_cols covers 
 constexpr int EMIT_WINDOW_TILES = 32;
 // One-pass calls over 2^17 bins: strings whose pairs are counted for the
 // estimate, and rows of O tiles (one workgroup to a CU by LDS, two rounds)
-constexpr int64_t WIDE_SAMPLE = 64 * EMIT_THREADS, WIDE_TILE_ROWS = 512;
+// (64 tiles took 130 us of a translation-symmetric call of 53 M two-word
+// records, 8 take 42; the estimate's spread stays far inside its 5 % margin)
+constexpr int64_t WIDE_SAMPLE = 8 * EMIT_THREADS, WIDE_TILE_ROWS = 512;
 static_assert(WIDE_SAMPLE <= 7 * NBINS, "an O of the sample's length never makes such a call");
 static_assert(WIDE_TILE_ROWS + TERM_ROWS_MAX <= SW_ROWS_MAX, "k_scan_wide covers every row");
 constexpr int MAX_PASS_BITS = 12;
@@ -1011,7 +1013,7 @@ int Engine::run(Call& c) {
       }
     } else {
       // A call of more possible records than that: the number is estimated
-      // from the pairs of the first WIDE_SAMPLE strings (45 us, host included),
+      // from the pairs of the first WIDE_SAMPLE strings (12 us and a host wait),
       // and the bins chosen by it.  (With no more strings of O than the sample
       // takes, H, which is shorter than a bucket, cannot make that many
       // records: they are operator terms, and go to the partitions.)
