@@ -929,7 +929,10 @@ int Engine::run(Call& c) {
     uint32_t *wtotal = nullptr, *wbase = nullptr;
     unsigned long long* wlook = nullptr;
     uint32_t* defer = b1.defer;
-    if (rec_bound <= (1ull << (NBINS_LOG_MID + 10)) && (!comm || H.n < (1 << (NBINS_LOG_MID - 3))))
+    // (an H index of 512 or more would need ids aside there, which
+    // translation-symmetric calls keep in any case)
+    if (rec_bound <= (1ull << (NBINS_LOG_MID + 10)) &&
+        (!comm || c.ts || H.n < (1 << (NBINS_LOG_MID - 3))))
       nbl = NBINS_LOG_MID;
     auto count_pass = [&](int pass_bits, uint32_t pass_id, bool read = true,
                           unsigned long long spec_cap = 0ull) -> int {
@@ -969,7 +972,7 @@ int Engine::run(Call& c) {
       // or a bin exceeds the merge capacity; the host then plans from the
       // count it has read, as below.
       const bool w14 = wide_for(nbl);
-      const uint32_t mb = (1u << nbl) << 2;
+      const uint32_t mb = 1u << nbl;
       const size_t per = RB + KB + sizeof(double2) + (w14 ? 4 : 0) + (want_select ? 12 : 0) +
                          (c.out.to_arena ? (size_t)(16 * W + 16) : 0);
       const size_t fixed = (size_t)mb * (9 * 4 + (want_select ? 12 : 0)) +
@@ -1124,7 +1127,9 @@ int Engine::run(Call& c) {
     if (nbl == NBINS_LOG_MP && pass_bits > 0 &&
         (double)hctl->maxg[0] <= std::ldexp(0.8 * merge_cap<W>(), pass_bits))
       pnbl = NBINS_LOG;
-    const int table_bits = wrows ? 0 : std::min(pass_bits + 2, MAX_PASS_BITS);
+    // tables for two more pass bits where a pass can still turn out too full; up
+    // to 2^14 bins the count has measured the one pass there is
+    const int table_bits = wrows || nbl < NBINS_LOG_MP ? 0 : std::min(pass_bits + 2, MAX_PASS_BITS);
     const size_t ptot = (size_t)std::max<unsigned long long>(pe_all, 1);
     const uint32_t max_buckets = (uint32_t)(1u << nbl) << table_bits;
     // ----- records, U, bucket tables, candidate lists -------------------------

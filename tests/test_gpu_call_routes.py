@@ -371,3 +371,51 @@ def test_large_step_with_terms(pk):
     b = float(np.sqrt(pk.norm2(full, ws=ws)))
     assert got[-1][1] == b and not got[-1][2]
     assert equal(out, pk.truncate(pk.divide(full, b, ws=ws), pk.Trunc(max_strings=M), ws=ws))
+
+
+# workspaces, found by growing them to what the refusals asked for, that held these small calls
+# when they were binned over 2^10 bins: the tables of 2^12 and 2^14 bins have to fit them too
+SMALL_CALLS = [("commutator", 100, 0, 3, 14842, 1), ("commutator", 64, 0, 600, 400, 0),
+               ("reorth", 50, 0, 20, 4390, 0), ("reorth", 100, 1, 1, 8369, 1),
+               ("ts", 50, 0, 13, 33, 0), ("ts", 100, 1, 12, 116, 1), ("ts_step", 100, 0, 9, 10, 1),
+               ("ts_step", 50, 0, 24, 15, 1), ("ts_step", 64, 1, 12, 73, 0)]
+LEAST = [38813952, 44178944, 40215808, 37154304, 35852032, 43418112, 35894272, 35880192, 37743616]
+
+
+def small_call(pk, kind, n, dtype, nh, no, top):
+    H, O = spread(pk, n, nh, 1, 2), spread(pk, n, no, 2)
+    if dtype:
+        O.coef, O.dtype = O.coef.float(), dtype
+    t = pk.Trunc(max_strings=max(1, no // 2)) if top else None
+    if kind.startswith("ts"):
+        O = pk.canonicalize_ts1d(O)
+    return {"commutator": lambda w: (pk.commutator(H, O, t, ws=w), 0),
+            "reorth": lambda w: pk.lanczos_step(H, None, O, 0.0, t, ws=w, reorth=True),
+            "ts": lambda w: (pk.commutator_ts1d(H, O, t, ws=w), 0),
+            "ts_step": lambda w: pk.lanczos_step(H, O, O, 0.5, t, ws=w, ts1d=True)}[kind]
+
+
+class Exact:
+    """A workspace of exactly the bytes given."""
+
+    def __init__(self, nbytes):
+        import torch
+        self.buf, self.grown = torch.empty(nbytes, dtype=torch.uint8, device="cuda"), 0
+
+    def c_struct(self):
+        from paper_2410_09654_amd import _lib
+        return _lib.PauliWsC(self.buf.data_ptr(), self.buf.numel(), 0)
+
+    def grow(self, required):
+        self.__init__(int(required))
+        self.grown = int(required)
+
+
+@pytest.mark.parametrize("case,nbytes", list(zip(SMALL_CALLS, LEAST)))
+def test_small_calls_in_their_least_workspace(pk, case, nbytes):
+    call = small_call(pk, *case)
+    ws = Exact(nbytes)
+    got = call(ws)
+    assert not ws.grown, ws.grown
+    want = call(pk.Workspace(1 << 30))
+    assert got[1] == want[1] and equal(got[0], want[0])
