@@ -1030,7 +1030,10 @@ int Engine::run(Call& c) {
       //    fit an L2, those of 2^17 do not (23 M records 0.80 -> 1.19 ms).  Nor
       //    translation-symmetric calls, whose binning runs beside the search
       //    for the representatives on one workgroup per CU: a step of 102 M
-      //    one-word records 11.9 ms by partitions, 13.2 ms so.
+      //    one-word records 11.9 ms by partitions, 13.2 ms so.  Nor one-word FP32
+      //    records, 24 bytes that straddle the lines they are scattered to:
+      //    top-M commutators of 60, 111 and 200 M 4.4, 8.2 and 14.2 ms by
+      //    partitions, 4.9, 9.3 and 17.0 so.
       //  - Otherwise, and when a count does not fit after all: the count over
       //    2^14 bins, and partitions.
       const int64_t tiles = (c.O.n + EMIT_THREADS - 1) / EMIT_THREADS;
@@ -1054,7 +1057,7 @@ int Engine::run(Call& c) {
                            (double)nterm_rec;
         if (est > room * NBINS && est <= room * NBINS_MP) {
           nbl = NBINS_LOG_MP;
-        } else if (!c.ts && est > room * NBINS && est <= room * NBINS_WIDE) {
+        } else if (!c.ts && !(W == 1 && F32) && est > room * NBINS && est <= room * NBINS_WIDE) {
           wtiles = (int)std::min<int64_t>(tiles, WIDE_TILE_ROWS);
           wrows = wtiles * hseg + term_rows;
         }

@@ -320,14 +320,18 @@ def kernels_of(pk, call):
 
 
 # calls too large for one pass over 2^14 bins take the route that their sampled estimate says: one
-# count over 2^15 bins, one over 2^17 in bytes, or, when 400 records of one string are more than a
-# byte counts, back to 2^14 and the partitions
-@pytest.mark.parametrize("n,no,thin,route", [(50, 2400001, 2, "2^15"), (50, 2400001, 0, "2^17"),
-                                             (100, 1700001, 0, "2^17"), (48, 640000, 0, "back")])
-def test_large_call_takes_its_route(pk, n, no, thin, route):
+# count over 2^15 bins, one over 2^17 in bytes (one-word FP32 records: the partitions), or, when
+# 400 records of one string are more than a byte counts, back to 2^14 and the partitions
+@pytest.mark.parametrize("n,no,thin,dtype,route", [(50, 2400001, 2, 0, "2^15"), (50, 2400001, 0, 0, "2^17"),
+                                                   (100, 1700001, 0, 0, "2^17"), (48, 640000, 0, 0, "back"),
+                                                   (100, 1700001, 0, 1, "2^17"), (50, 2400001, 2, 1, "2^15"),
+                                                   (50, 2400001, 0, 1, "partitions")])
+def test_large_call_takes_its_route(pk, n, no, thin, dtype, route):
     import torch
     ws = pk.Workspace(24 << 30)
     O = spread(pk, n, no, 2, thin)
+    if dtype:
+        O.coef, O.dtype = O.coef.float(), dtype
     if route == "back":
         H, P = wl.same_key_runs(n, np.full(400, 2.0))
         H, P = raw(pk, H), pk.PauliOp.from_host(P)
@@ -343,16 +347,14 @@ def test_large_call_takes_its_route(pk, n, no, thin, route):
     else:
         H = spread(pk, n, 100, 1)
     assert H.size * O.size > 7 * (1 << 14) * (1984 if n <= 64 else 1344)
-    out = pk.PauliOp(n, 140 << 20)
+    out = pk.PauliOp(n, 140 << 20, dtype)
     k = kernels_of(pk, lambda: pk.commutator(H, O, out=out, ws=ws))
     st = pk.last_stats()
     print(f"route n={n} no={no}: {st} {k}", flush=True)
-    assert k["k_emit_sample"] == 1
-    assert ("k_scan_wide" in k) == (route != "2^15") and ("k_emit_part_scatter" in k) == (route == "back")
-    if route != "back":
-        assert st["passes"] == 1 and k["k_emit_count"] == 1 and k["k_emit_scatter"] == 1
-    else:
-        assert st["passes"] > 1 and k["k_emit_count"] == 2
+    assert k["k_emit_sample"] == 1 and k["k_emit_count"] == (2 if route == "back" else 1)
+    assert ("k_scan_wide" in k) == (route in ("2^17", "back"))
+    assert ("k_emit_part_scatter" in k) == (route in ("back", "partitions"))
+    assert (st["passes"] > 1) == (route in ("back", "partitions"))
     total = sum_of_parts(pk, H, O, 16, ws)
     assert equal(out, total)
 
