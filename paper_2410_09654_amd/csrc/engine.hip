@@ -9,6 +9,7 @@
 // Runge-Kutta step live at the top end of the same workspace.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -961,11 +962,68 @@ int Engine::run(Call& c) {
       for (int t = 0; t < c.n_terms; t++) w = w || c.tlist[t];
       return w;
     };
-    if (ctl_event &&
-               rec_bound <= 7ull * (1ull << NBINS_LOG) * (unsigned long long)merge_cap<W>()) {
+    // seven passes' worth of possible records: see below
+    const unsigned long long few = 7ull * (1ull << NBINS_LOG) * (unsigned long long)merge_cap<W>();
+    bool spec = ctl_event && rec_bound <= few;
+    if (rec_bound > few) {
+      // A call of more possible records than that: the number is estimated
+      // from the pairs of the first WIDE_SAMPLE strings (12 us and a host wait),
+      // and the bins chosen by it.  (With no more strings of O than the sample
+      // takes, H, which is shorter than a bucket, cannot make that many
+      // records: they are operator terms, and go to the partitions.)
+      //  - One pass over 2^14 bins: as a call of fewer possible records (19 M
+      //    two-word records 1.65 ms, over 2^15 bins 1.75).
+      //  - One pass over 2^15 bins: counted over those at once (a count over
+      //    2^14 bins first took 0.21 of 2.43 ms for 23 M two-word FP32 records).
+      //  - More, up to one pass over 2^17: counted over those, in bytes (which
+      //    is what LDS holds of them), and scattered straight to the buckets,
+      //    where the partitions below write and read every record twice: 96 M
+      //    two-word records 6.8 -> 5.0 ms with the binning, the step 11.9 ->
+      //    10.3 ms.  Not below 2^15 bins' worth: the open lines of 2^15 bins
+      //    fit an L2, those of 2^17 do not (23 M records 0.80 -> 1.19 ms).  Nor
+      //    translation-symmetric calls, whose binning runs beside the search
+      //    for the representatives on one workgroup per CU: a step of 102 M
+      //    one-word records 11.9 ms by partitions, 13.2 ms so.  Nor one-word FP32
+      //    records, 24 bytes that straddle the lines they are scattered to:
+      //    top-M commutators of 60, 111 and 200 M 4.4, 8.2 and 14.2 ms by
+      //    partitions, 4.9, 9.3 and 17.0 so.
+      //  - Otherwise, and when a count does not fit after all: the count over
+      //    2^14 bins, and partitions.
+      const int64_t tiles = (c.O.n + EMIT_THREADS - 1) / EMIT_THREADS;
+      if (comm && c.O.n > WIDE_SAMPLE) {
+        const double room = 0.85 * merge_cap<W>();
+        EmitArgs se = ea;
+        se.nO = WIDE_SAMPLE;
+        se.n_terms = 0;
+        se.hseg = (int)std::max<int64_t>(
+            1, std::min<int64_t>(HSEG_ROWS * EMIT_THREADS / WIDE_SAMPLE, H.n / HSEG_MIN));
+        se.comm_rows = (int)(WIDE_SAMPLE / EMIT_THREADS) * se.hseg;
+        {
+          const EmitArgs& ea = se;
+          const int rows = se.comm_rows;
+          EMIT("k_emit_sample", false, NBINS_LOG_MID);
+          SCAN(NBINS_LOG_MID, counts, rows, 0ull, 0u);
+        }
+        TRY(read_ctl());
+        const double mean = (double)hctl->pe_total * ((double)c.O.n / (double)WIDE_SAMPLE) +
+                            (double)nterm_rec;
+        const double est = 1.05 * mean;
+        // (the largest of 2^14 bins lies some 4.2 standard deviations above their mean)
+        if (mean <= (merge_cap<W>() - 4.2 * std::sqrt((double)merge_cap<W>())) * NBINS) {
+          spec = ctl_event != nullptr;
+        } else if (est <= room * NBINS_MP) {
+          nbl = NBINS_LOG_MP;
+        } else if (!c.ts && !(W == 1 && F32) && est <= room * NBINS_WIDE) {
+          wtiles = (int)std::min<int64_t>(tiles, WIDE_TILE_ROWS);
+          wrows = wtiles * hseg + term_rows;
+        }
+      }
+    }
+    if (spec) {
       // A call that may fit one pass over 2^12 or 2^14 bins (at most seven passes'
-      // worth of possible records) is laid out for as many records as the
-      // workspace holds beside the rest of that pass; the count's control
+      // worth of possible records, or estimated to fit) is laid out for as many
+      // records as the workspace holds beside the rest of that pass, up to what
+      // the bins can hold; the count's control
       // block goes to the host behind an event and the scatter is launched
       // at once, so the GPU does not wait for the host's plan.  The bin scan
       // makes the scatter stand down when the records do not fit the layout
@@ -980,7 +1038,8 @@ int Engine::run(Call& c) {
       const size_t used = align256(ar->bottom) + ar->top;
       const size_t avail = ar->cap > used + fixed ? ar->cap - used - fixed : 0;
       const unsigned long long cap_rec =
-          std::min<unsigned long long>(rec_bound, (unsigned long long)(avail / per));
+          std::min<unsigned long long>({rec_bound, (unsigned long long)(avail / per),
+                                        (unsigned long long)mb * merge_cap<W>()});
       const size_t mark_bottom = ar->bottom, mark_need = ar->need;
       if (cap_rec >= (1ull << 16))
         take_bufs2<W, F32>(*ar, (size_t)cap_rec, w14, false, mb, want_select, b2);
@@ -1015,53 +1074,6 @@ int Engine::run(Call& c) {
         }
       }
     } else {
-      // A call of more possible records than that: the number is estimated
-      // from the pairs of the first WIDE_SAMPLE strings (12 us and a host wait),
-      // and the bins chosen by it.  (With no more strings of O than the sample
-      // takes, H, which is shorter than a bucket, cannot make that many
-      // records: they are operator terms, and go to the partitions.)
-      //  - One pass over 2^15 bins: counted over those at once (a count over
-      //    2^14 bins first took 0.21 of 2.43 ms for 23 M two-word FP32 records).
-      //  - More, up to one pass over 2^17: counted over those, in bytes (which
-      //    is what LDS holds of them), and scattered straight to the buckets,
-      //    where the partitions below write and read every record twice: 96 M
-      //    two-word records 6.8 -> 5.0 ms with the binning, the step 11.9 ->
-      //    10.3 ms.  Not below 2^15 bins' worth: the open lines of 2^15 bins
-      //    fit an L2, those of 2^17 do not (23 M records 0.80 -> 1.19 ms).  Nor
-      //    translation-symmetric calls, whose binning runs beside the search
-      //    for the representatives on one workgroup per CU: a step of 102 M
-      //    one-word records 11.9 ms by partitions, 13.2 ms so.  Nor one-word FP32
-      //    records, 24 bytes that straddle the lines they are scattered to:
-      //    top-M commutators of 60, 111 and 200 M 4.4, 8.2 and 14.2 ms by
-      //    partitions, 4.9, 9.3 and 17.0 so.
-      //  - Otherwise, and when a count does not fit after all: the count over
-      //    2^14 bins, and partitions.
-      const int64_t tiles = (c.O.n + EMIT_THREADS - 1) / EMIT_THREADS;
-      if (comm && rec_bound > 7ull * (1ull << NBINS_LOG) * (unsigned long long)merge_cap<W>() &&
-          c.O.n > WIDE_SAMPLE) {
-        const double room = 0.85 * merge_cap<W>();
-        EmitArgs se = ea;
-        se.nO = WIDE_SAMPLE;
-        se.n_terms = 0;
-        se.hseg = (int)std::max<int64_t>(
-            1, std::min<int64_t>(HSEG_ROWS * EMIT_THREADS / WIDE_SAMPLE, H.n / HSEG_MIN));
-        se.comm_rows = (int)(WIDE_SAMPLE / EMIT_THREADS) * se.hseg;
-        {
-          const EmitArgs& ea = se;
-          const int rows = se.comm_rows;
-          EMIT("k_emit_sample", false, NBINS_LOG_MID);
-          SCAN(NBINS_LOG_MID, counts, rows, 0ull, 0u);
-        }
-        TRY(read_ctl());
-        const double est = 1.05 * (double)hctl->pe_total * ((double)c.O.n / (double)WIDE_SAMPLE) +
-                           (double)nterm_rec;
-        if (est > room * NBINS && est <= room * NBINS_MP) {
-          nbl = NBINS_LOG_MP;
-        } else if (!c.ts && !(W == 1 && F32) && est > room * NBINS && est <= room * NBINS_WIDE) {
-          wtiles = (int)std::min<int64_t>(tiles, WIDE_TILE_ROWS);
-          wrows = wtiles * hseg + term_rows;
-        }
-      }
       const size_t mark_bottom = ar->bottom, mark_need = ar->need;
       if (wrows) {
         pre16 = (uint16_t*)ar->take((size_t)wrows * NBINS_WIDE * 2);

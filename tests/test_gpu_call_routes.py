@@ -319,12 +319,13 @@ def kernels_of(pk, call):
     return {name: v[0] for name, v in k.items()}
 
 
-# calls too large for one pass over 2^14 bins take the route that their sampled estimate says: one
-# count over 2^15 bins, one over 2^17 in bytes (one-word FP32 records: the partitions), or, when
+# calls of more possible records than seven passes over 2^14 bins hold take the route that their
+# sampled estimate says: one pass over 2^14 bins, one count over 2^15, one over 2^17 in bytes (one-word FP32 records: the partitions), or, when
 # 400 records of one string are more than a byte counts, back to 2^14 and the partitions
 @pytest.mark.parametrize("n,no,thin,dtype,route", [(50, 2400001, 2, 0, "2^15"), (50, 2400001, 0, 0, "2^17"),
                                                    (100, 1700001, 0, 0, "2^17"), (48, 640000, 0, 0, "back"),
                                                    (100, 1700001, 0, 1, "2^17"), (50, 2400001, 2, 1, "2^15"),
+                                                   (100, 900001, 3, 0, "2^14"), (62, 2400001, 3, 1, "2^14"),
                                                    (50, 2400001, 0, 1, "partitions")])
 def test_large_call_takes_its_route(pk, n, no, thin, dtype, route):
     import torch
@@ -355,6 +356,7 @@ def test_large_call_takes_its_route(pk, n, no, thin, dtype, route):
     assert ("k_scan_wide" in k) == (route in ("2^17", "back"))
     assert ("k_emit_part_scatter" in k) == (route in ("back", "partitions"))
     assert (st["passes"] > 1) == (route in ("back", "partitions"))
+    assert (st["buckets"] <= 1 << 14) == (route == "2^14") and (st["buckets"] == 1 << 15 or route != "2^15")
     total = sum_of_parts(pk, H, O, 16, ws)
     assert equal(out, total)
 
