@@ -393,7 +393,8 @@ typedef struct pauli_stats {
   int32_t buckets;   /* merge buckets */
   int32_t host_syncs; /* times the host waited for the stream (control-block
                          reads): one for a call planned from its sizes (at most
-                         2^18 possible records, workspace for that bound), more
+                         2^18 possible records, 2^17 of a list to
+                         canonicalise, workspace for that bound), more
                          when the count must be read first or the top-M select
                          needs the host */
   int32_t reserved;

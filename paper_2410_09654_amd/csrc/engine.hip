@@ -451,15 +451,22 @@ void take_bufs2(Arena& ar, size_t ptot, bool wide, bool partitioned, uint32_t ma
     }
 }
 
-// An append call (at most APPEND_MAX possible records): 2^append_bits buckets whose mean stays
+// An append call (at most append_max possible records): 2^append_bits buckets whose mean stays
 // within 1024 records, with room for append_cap each; the records lie where the count matrix would.
-inline int append_bits(unsigned long long rec_bound) {
+// Lists, which repeat strings and emit every record, get twice the buckets, and are counted above
+// half the records: 100,000 entries of 1000 strings overflowed 2^7 buckets and were redone (112 us
+// with the count over 2^10 bins before, 160 redone, 63 in 2^8), 200,000 of 2000 strings 2^8.
+inline unsigned long long append_max(bool list) { return list ? APPEND_MAX / 2 : APPEND_MAX; }
+inline int append_bits(unsigned long long rec_bound, bool list) {
   int F = 1;
-  while (rec_bound > (1024ull << F)) F++;
+  while (rec_bound > ((list ? 512ull : 1024ull) << F)) F++;
   return F;
 }
 template <int W, bool F32>
 void take_append(Arena& ar, int F, bool want_select, Bufs2& b) {
+  static_assert(((size_t)append_cap<W>() << 8) * sizeof(Rec<W, F32>) <= (size_t)256 * NBINS_MP * 4 &&
+                    (1024ull << 8) == APPEND_MAX,
+                "the records of the longest call fit the count matrix");
   take_bufs2<W, F32>(ar, (size_t)append_cap<W>() << F, true, false, 1u << F, want_select, b, false);
 }
 
@@ -596,17 +603,15 @@ int Engine::run(Call& c) {
           bound, (unsigned long long)std::max<long long>((long long)tr->max_strings, n_keep));
     return (size_t)std::max<unsigned long long>(bound, 1);
   };
-  bool append = !direct && !run_counted && rows > 0 && rec_bound <= APPEND_MAX;
-  constexpr int ACAP = append_cap<W>();
-  const int append_F = append_bits(rec_bound);
+  bool list = false;
+  for (int t = 0; t < c.n_terms; t++) list = list || c.tlist[t];
+  bool append = !direct && !run_counted && rows > 0 && rec_bound <= append_max(list);
+  const int append_F = append_bits(append ? rec_bound : 0, list);
   Bufs1<W> b1;
   Bufs2 b2;
   take_bufs1<W>(*ar, comm, H.n, n_keep, rows, b1);
   if (append && !ar->short_) {
     const size_t mark_bottom = ar->bottom, mark_need = ar->need;
-    // the records lie where the count matrix would
-    static_assert(((size_t)ACAP << 8) * RB <= (size_t)256 * NBINS_MP * 4,
-                  "the records of an append call fit the count matrix");
     take_append<W, F32>(*ar, append_F, want_select, b2);
     b2.recs = b1.counts;
     if (c.out.to_arena) {  // room for the output rows as well (place_output takes them)
@@ -894,7 +899,7 @@ int Engine::run(Call& c) {
       ea.wide = 1;
       ea.cursor = bin_base;
       ea.append_F = append_F;
-      ea.append_cap = (uint32_t)ACAP;
+      ea.append_cap = (uint32_t)append_cap<W>();
       EMIT("k_emit_append", true, NBL_APPEND);
       merge_common();
       ma.bin_count = bin_base;
@@ -1770,10 +1775,10 @@ void dry_call(Arena& ar, const DryCall& d, unsigned long long* pe_out) {
   take_bufs2<W, F32>(ar, (size_t)std::max<unsigned long long>(pe, 1), d.wide || (comm && (nH > 2047 || d.ts)),
                      nbl == NBINS_LOG_MP, max_buckets, d.select, b2);
   if (d.out_arena >= 0) take_rows<W>(ar, (size_t)std::max<int64_t>(d.out_arena, 1), d.out_f32);
-  if (pe <= APPEND_MAX) {
+  if (pe <= append_max(d.wide)) {
     // the fixed buckets that such a call takes when they fit (up to 2.75 times the records)
     ar.bottom = mark_bottom;
-    take_append<W, F32>(ar, append_bits(pe), d.select, b2);
+    take_append<W, F32>(ar, append_bits(pe, d.wide), d.select, b2);
   }
 }
 

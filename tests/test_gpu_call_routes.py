@@ -205,8 +205,9 @@ def test_small_step_in_its_least_workspace(pk):
     assert bl == b and equal(got, want)
 
 
-# A workspace of the queried size lets a call of at most 2^18 possible records run with one wait:
-# bounds just above and at a power of two, one and two words, with and without a top-M cut
+# A workspace of the queried size lets a call of at most 2^18 possible records (a list of at most
+# 2^17 entries) run with one wait: bounds just above and at a power of two, one and two words, with
+# and without a top-M cut
 @pytest.mark.parametrize("n", [50, 100])
 @pytest.mark.parametrize("na,nb", [(1, 1), (1, 2049), (5, 26215), (1, 131073), (1, 262144), (900, 200)])
 def test_queried_workspace_takes_one_wait(pk, n, na, nb):
@@ -222,13 +223,14 @@ def test_queried_workspace_takes_one_wait(pk, n, na, nb):
         print(f"query n={n} {na} x {nb} op={op}: {nbytes}", flush=True)
         ws = pk.Workspace(nbytes)
         got = fn(ws)
-        assert ws.nbytes == nbytes and pk.last_stats()["host_syncs"] == 1, op
+        waits = 2 if op == pk.PAULI_Q_CANONICALIZE and nb > 1 << 17 else 1
+        assert ws.nbytes == nbytes and pk.last_stats()["host_syncs"] == waits, op
         assert equal(got, fn(big)), op
 
 
 # the appended records of a call with up to 1024 to a bucket do not queue up at the bucket cursors
 @pytest.mark.parametrize("n", [50, 100])
-@pytest.mark.parametrize("m", [65536, 1 << 18])
+@pytest.mark.parametrize("m", [65536, 1 << 17])
 def test_appended_records_do_not_queue(pk, n, m):
     ws = pk.Workspace(256 << 20)
     ops = [shuffled(pk, spread(pk, n, k, k), 3) for k in (1000, m)]
@@ -423,3 +425,18 @@ def test_small_calls_in_their_least_workspace(pk, case, nbytes):
     assert not ws.grown, ws.grown
     want = call(pk.Workspace(1 << 30))
     assert got[1] == want[1] and equal(got[0], want[0])
+
+
+# lists that repeat their strings a hundred times fit the appended buckets of up to 2^17 entries
+# (one wait); longer ones are counted; the oracle's sums (in list order; integers)
+@pytest.mark.parametrize("n", [50, 100])
+@pytest.mark.parametrize("m,u", [(2000, 20), (100000, 1000), (131072, 2000), (60000, 900),
+                                 (131073, 2000), (1 << 18, 3000)])
+def test_lists_with_repeats(pk, n, m, u):
+    A = spread(pk, n, u, 3).to_host()
+    i = np.random.default_rng(m).integers(0, u, m)
+    c = np.random.default_rng(u).integers(-8, 9, m).astype(complex)
+    L = wl.HostOp(n, A.x[i], A.z[i], c)
+    got = pk.canonicalize(raw(pk, L), ws=pk.Workspace(256 << 20))
+    assert pk.last_stats()["host_syncs"] == (1 if m <= 1 << 17 else 2)
+    same(got.to_host(), oracle.canonicalize(L), "list")
